@@ -96,6 +96,11 @@ struct Plan {
     size_t off_rowoff, off_offP_r, off_offB_r;
     int64_t total_rowgroups;
     int preset; // compile-time window preset of the stream kernel, or -1
+    // resident sweeps: every replica fits a workgroup's LDS; lanes per trial
+    // and threads per workgroup
+    bool resident;
+    int res_lanes, res_block;
+    LdsLayout res;
     std::vector<Replica> reps;
     int LP, WY, WZ;
     LdsLayout lds;
@@ -421,6 +426,44 @@ int make_plan(const smcx_desc* d, Plan& P)
         }
     }
 
+    // resident sweeps (persistent mode): the replica in LDS as basis-planar
+    // rows with its 2-cell halo, after the integer dE table, the partner table
+    // and the cell origins.  An edge below 4 would give a site two images on
+    // one axis.
+    P.resident = true;
+    {
+        int64_t win_max = 0;
+        int org_max = 0, cell_max = 0;
+        for (const Replica& R : P.reps) {
+            int64_t w = P.m;
+            int n = 0, c = 1;
+            for (int a = 0; a < 3; ++a) {
+                P.resident &= R.L[a] >= 2 * kHalo;
+                w = std::min<int64_t>(w * (R.L[a] + 2 * kHalo), 1 << 24);
+                n += (int)R.origin[a].size();
+                c = (int)std::min<int64_t>((int64_t)c * (int64_t)R.edges[a].size(), 1 << 24);
+            }
+            win_max = std::max(win_max, w);
+            org_max = std::max(org_max, n);
+            cell_max = std::max(cell_max, c);
+        }
+        auto al = [](int64_t v) { return (v + 15) & ~(int64_t)15; };
+        int64_t ro = 0;
+        P.res = LdsLayout{};
+        P.res.q_off = (int)ro;    ro = al(ro + 4 * qtab_entries(P.K, P.S));
+        P.res.pd_off = (int)ro;   ro = al(ro + 4 * P.m * P.Z1);
+        P.res.offb_off = (int)ro; ro = al(ro + 4 * (int64_t)org_max);
+        P.res.win_off = (int)ro;  ro = al(ro + win_max);
+        P.resident &= ro + 64 <= 160 * 1024;
+        P.res.win_bytes = (int)win_max;
+        P.res.total = (int)std::min<int64_t>(ro, 160 * 1024);
+        // as many lanes per trial as give every link cell its own lanes
+        int G = 16;
+        while (G > P.m && (int64_t)cell_max * G > 1024) G /= 2;
+        P.res_lanes = G;
+        P.res_block = (int)std::min<int64_t>(1024, ((int64_t)cell_max * G + 63) / 64 * 64);
+    }
+
     // workspace layout
     size_t o = 0;
     P.off_reps = o; o = align256(o + sizeof(RepDev) * P.R);
@@ -492,6 +535,7 @@ struct smcx_lattice {
     const void* k_stream = nullptr;
     const void* k_persistent = nullptr;
     const void* k_rows = nullptr;
+    const void* k_resident = nullptr;
     int rows_wgs = 8;
     int static_dev = -1;  // device whose static workspace this handle uses, else -1
 };
@@ -511,6 +555,7 @@ SweepArgs base_args(smcx_lattice* h)
     a.Dtab = (const double*)(h->ws + P.off_D);
     a.Qtab = (const int32_t*)(h->ws + P.off_Q);
     a.ws = h->ws;
+    a.occ = h->occ;
     a.R = P.R;
     a.K = P.K;
     a.S = P.S;
@@ -609,6 +654,24 @@ int pack_all(smcx_lattice* h, bool unpack, bool planar, hipStream_t st)
     for (int r = 0; r < P.R; ++r)
         SMCX_HIP(launch_pack(P.lattice, P.K, unpack, planar, h->occ, h->ws, reps, r, rows_of(P.reps[r]), 1, st));
     return SMCX_OK;
+}
+
+// The persistent launch of a call: whole replicas in LDS where they fit,
+// else tile windows staged from the packed copies.
+int persistent_launch(smcx_lattice* h, SweepArgs a, hipStream_t st)
+{
+    const Plan& P = h->P;
+    a.nb = P.group;
+    if (!P.resident) {
+        if (int rc = pack_all(h, false, false, st)) return rc;
+        if (int rc = timed_launch(h, h->k_persistent, dim3(P.R), P.block, P.lds.total, st, a)) return rc;
+        return pack_all(h, true, false, st);
+    }
+    a.lds_q = P.res.q_off;
+    a.lds_pd = P.res.pd_off;
+    a.lds_offb = P.res.offb_off;
+    a.lds_win = P.res.win_off;
+    return timed_launch(h, h->k_resident, dim3(P.R), P.res_block, P.res.total, st, a);
 }
 
 // The handle that currently owns each device's static workspace (a later
@@ -830,6 +893,10 @@ int smcx_lattice_init(smcx_lattice** out, const smcx_desc* desc, uint8_t* occ_de
     }
     SMCX_HIP(set_sweep_lds_limit(h->k_stream, P.lds.total));
     SMCX_HIP(set_sweep_lds_limit(h->k_persistent, P.lds.total));
+    if (P.resident) {
+        h->k_resident = resident_kernel(P.lattice, P.K, P.S, P.res_lanes);
+        SMCX_HIP(set_sweep_lds_limit(h->k_resident, P.res.total));
+    }
     // stream grid: every CU filled to the occupancy the LDS footprint allows
     int dev = 0, cus = 256, per_cu = 1;
     SMCX_HIP(hipGetDevice(&dev));
@@ -1095,18 +1162,20 @@ static int run_sweeps(smcx_lattice* h, int32_t n_sweeps, uint64_t seed, uint32_t
     // index from it and first_sweep counts from 0
     if (sweep_counter) first_sweep = 0;
     const Plan& P = h->P;
-    // auto: one persistent launch for lattices too small to fill a launch per
-    // mini-step group; row windows where they apply (the ladder of 256 BCC
-    // replicas runs 10x faster in row launches than in one workgroup per
-    // replica); otherwise persistent for several replicas
-    if (mode == SMCX_MODE_AUTO)
-        mode = P.total_sites <= (1 << 16) ? SMCX_MODE_PERSISTENT
-                                          : (P.rows || P.R == 1 ? SMCX_MODE_STREAM : SMCX_MODE_PERSISTENT);
+    // auto: whole replicas in LDS for lattices too small to fill a launch per
+    // mini-step group, and where there is about a replica for every four CUs
+    // (256 BCC 32^3 replicas: 370 us per sweep against 583 in row launches);
+    // else row windows where they apply; else tile windows, persistent for
+    // several replicas
+    if (mode == SMCX_MODE_AUTO) {
+        if (P.resident && (P.total_sites <= (1 << 16) || P.R >= 64)) mode = SMCX_MODE_PERSISTENT;
+        else if (P.rows) mode = SMCX_MODE_STREAM;
+        else mode = P.total_sites <= (1 << 16) || P.R > 1 ? SMCX_MODE_PERSISTENT : SMCX_MODE_STREAM;
+    }
     // the row kernel reads basis-planar rows; replicas of different
     // decompositions share its launches only over whole sweeps
     const bool rows = mode == SMCX_MODE_STREAM && P.rows && (!P.rows_mixed || (tau_begin == 0 && tau_end >= P.max_nA));
     const bool planar = rows;
-    if (int rc = pack_all(h, false, planar, st)) return rc;
     SweepArgs a = base_args(h);
     a.seed = seed;
     a.stats = stats_dev;
@@ -1123,9 +1192,10 @@ static int run_sweeps(smcx_lattice* h, int32_t n_sweeps, uint64_t seed, uint32_t
         a.first_sweep = first_sweep;
         a.beta = beta_dev;
         a.beta_stride = bstride;
-        a.nb = P.group;
-        if (int rc = timed_launch(h, h->k_persistent, dim3(P.R), P.block, P.lds.total, st, a)) return rc;
-    } else if (rows) {
+        return persistent_launch(h, a, st);
+    }
+    if (int rc = pack_all(h, false, planar, st)) return rc;
+    if (rows) {
         // one launch per (o_y, o_z) group: every o_x and basis site
         SweepArgs ra = row_args(h);
         ra.seed = a.seed;
@@ -1486,12 +1556,9 @@ int smcx_ladder_capture(smcx_lattice* h, int32_t n_sweeps, uint64_t seed, const 
     a.beta_stride = 0;
     a.tau_begin = 0;
     a.tau_end = P.max_nA;
-    a.nb = P.group;
-    int rc = pack_all(h, false, false, st);
+    int rc = persistent_launch(h, a, st);
     hipError_t e = hipSuccess;
-    if (rc == SMCX_OK) e = launch_sweep(h->k_persistent, dim3(P.R), P.block, P.lds.total, st, a);
-    if (rc == SMCX_OK && e == hipSuccess) e = launch_advance_counter(sweep_counter_dev, (uint32_t)n_sweeps, st);
-    if (rc == SMCX_OK && e == hipSuccess) rc = pack_all(h, true, false, st);
+    if (rc == SMCX_OK) e = launch_advance_counter(sweep_counter_dev, (uint32_t)n_sweeps, st);
     hipGraph_t graph = nullptr;
     hipError_t e2 = hipStreamEndCapture(st, &graph);
     if (rc != SMCX_OK) {

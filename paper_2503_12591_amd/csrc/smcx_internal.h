@@ -231,6 +231,7 @@ struct SweepArgs {
     const double* Dtab;        // [S][K][K][K]: D[s][t][p][q] = V_s[q][t] - V_s[p][t]
     const int32_t* Qtab;       // [S][K][K][K] D in integer units, [K][K] bias sums, then the unit and
                                // the error bound as float bits (qtab_entries + 2 words)
+    uint8_t* occ;              // occupancy, natural layout (resident sweeps)
     uint8_t* ws;               // workspace base (padded copies)
     const double* beta;        // beta[js * beta_stride + r]
     int64_t* stats;            // [R][3]
