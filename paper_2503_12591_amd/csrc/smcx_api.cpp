@@ -104,7 +104,7 @@ struct Plan {
     std::vector<Replica> reps;
     int LP, WY, WZ;
     LdsLayout lds;
-    size_t off_reps, off_origins, off_tileoff, off_offP, off_offB, off_pd, off_D, off_Q, off_V, off_misc, off_pad, total;
+    size_t off_reps, off_origins, off_tileoff, off_offP, off_offB, off_pd, off_D, off_Q, off_V, off_misc, off_slots, off_pad, total;
     // qSRO model: affected-set and neighbour tables, V, W, Z
     size_t off_qaff, off_qnbr, off_qV, off_qW, off_qZ, off_qslots;
     int qnaff;   // largest affected set
@@ -479,6 +479,7 @@ int make_plan(const smcx_desc* d, Plan& P)
     P.off_Q = o; o = align256(o + sizeof(int32_t) * (qtab_entries(P.K, P.S) + 2));
     P.off_V = o; o = align256(o + sizeof(double) * P.S * P.K * P.K);
     P.off_misc = o; o = align256(o + 256);
+    P.off_slots = o; o = align256(o + sizeof(int64_t) * kStatStride * stat_parts_of(P.R) * P.R);
     P.off_qaff = o; o = align256(o + sizeof(int32_t) * P.m * P.Z1 * (1 + kQsroMaxAff));
     P.off_qnbr = o; o = align256(o + sizeof(int32_t) * P.m * P.sumZ);
     P.off_qV = o; o = align256(o + sizeof(double) * P.S * P.K * P.K);
@@ -556,6 +557,9 @@ SweepArgs base_args(smcx_lattice* h)
     a.Qtab = (const int32_t*)(h->ws + P.off_Q);
     a.ws = h->ws;
     a.occ = h->occ;
+    a.stats = (int64_t*)(h->ws + P.off_slots);
+    a.stat_parts = stat_parts_of(P.R);
+    a.stat_stride = kStatStride;
     a.R = P.R;
     a.K = P.K;
     a.S = P.S;
@@ -635,9 +639,11 @@ int timed_launch(smcx_lattice* h, const void* kernel, dim3 grid, int block, size
     return SMCX_OK;
 }
 
-int pack_all(smcx_lattice* h, bool unpack, bool planar, hipStream_t st)
+int pack_all(smcx_lattice* h, bool unpack, bool planar, int64_t* stats_dev, hipStream_t st)
 {
     const Plan& P = h->P;
+    int64_t* slots = (int64_t*)(h->ws + P.off_slots);
+    const int parts = stat_parts_of(P.R);
     // natural rows to unpack, padded rows (halo rows included) to pack
     auto rows_of = [&](const Replica& R) {
         return unpack ? (int64_t)R.L[1] * R.L[2] : (int64_t)R.prows * (R.L[2] + 2 * kHalo);
@@ -648,25 +654,29 @@ int pack_all(smcx_lattice* h, bool unpack, bool planar, hipStream_t st)
         // launch each would cost more than their copies)
         int64_t most = 0;
         for (const Replica& R : P.reps) most = std::max(most, rows_of(R));
-        SMCX_HIP(launch_pack(P.lattice, P.K, unpack, planar, h->occ, h->ws, reps, -1, most, P.R, st));
+        SMCX_HIP(launch_pack(P.lattice, P.K, unpack, planar, h->occ, h->ws, reps, -1, most, P.R, slots, parts, stats_dev, st));
         return SMCX_OK;
     }
     for (int r = 0; r < P.R; ++r)
-        SMCX_HIP(launch_pack(P.lattice, P.K, unpack, planar, h->occ, h->ws, reps, r, rows_of(P.reps[r]), 1, st));
+        SMCX_HIP(launch_pack(P.lattice, P.K, unpack, planar, h->occ, h->ws, reps, r, rows_of(P.reps[r]), 1, slots, parts, stats_dev, st));
     return SMCX_OK;
 }
 
 // The persistent launch of a call: whole replicas in LDS where they fit,
 // else tile windows staged from the packed copies.
-int persistent_launch(smcx_lattice* h, SweepArgs a, hipStream_t st)
+int persistent_launch(smcx_lattice* h, SweepArgs a, int64_t* stats_dev, hipStream_t st)
 {
     const Plan& P = h->P;
     a.nb = P.group;
     if (!P.resident) {
-        if (int rc = pack_all(h, false, false, st)) return rc;
+        if (int rc = pack_all(h, false, false, stats_dev, st)) return rc;
         if (int rc = timed_launch(h, h->k_persistent, dim3(P.R), P.block, P.lds.total, st, a)) return rc;
-        return pack_all(h, true, false, st);
+        return pack_all(h, true, false, stats_dev, st);
     }
+    // one workgroup per replica: no counters shared
+    a.stats = stats_dev;
+    a.stat_parts = 1;
+    a.stat_stride = 3;
     a.lds_q = P.res.q_off;
     a.lds_pd = P.res.pd_off;
     a.lds_offb = P.res.offb_off;
@@ -875,6 +885,7 @@ int smcx_lattice_init(smcx_lattice** out, const smcx_desc* desc, uint8_t* occ_de
         SMCX_HIP(hipMemcpyAsync(h->ws + P.off_qZ, Zs, sizeof(Zs), hipMemcpyHostToDevice, st));
         SMCX_HIP(hipStreamSynchronize(st));  // the host tables go out of scope
     }
+    SMCX_HIP(launch_fill_i64((int64_t*)(h->ws + P.off_slots), (int64_t)kStatStride * stat_parts_of(P.R) * P.R, 0, st));
     int32_t* bad = (int32_t*)(h->ws + P.off_misc);
     SMCX_HIP(launch_fill_i32(bad, 1, 0, st));
     SMCX_HIP(launch_validate(occ_dev, P.total_sites, P.K, bad, st));
@@ -1178,7 +1189,6 @@ static int run_sweeps(smcx_lattice* h, int32_t n_sweeps, uint64_t seed, uint32_t
     const bool planar = rows;
     SweepArgs a = base_args(h);
     a.seed = seed;
-    a.stats = stats_dev;
     a.ties = ties_dev;
     a.tie_cap = tie_cap;
     a.tie_count = tie_count_dev;
@@ -1192,14 +1202,13 @@ static int run_sweeps(smcx_lattice* h, int32_t n_sweeps, uint64_t seed, uint32_t
         a.first_sweep = first_sweep;
         a.beta = beta_dev;
         a.beta_stride = bstride;
-        return persistent_launch(h, a, st);
+        return persistent_launch(h, a, stats_dev, st);
     }
-    if (int rc = pack_all(h, false, planar, st)) return rc;
+    if (int rc = pack_all(h, false, planar, stats_dev, st)) return rc;
     if (rows) {
         // one launch per (o_y, o_z) group: every o_x and basis site
         SweepArgs ra = row_args(h);
         ra.seed = a.seed;
-        ra.stats = a.stats;
         ra.ties = a.ties;
         ra.tie_cap = a.tie_cap;
         ra.tie_count = a.tie_count;
@@ -1255,7 +1264,7 @@ static int run_sweeps(smcx_lattice* h, int32_t n_sweeps, uint64_t seed, uint32_t
             }
         }
     }
-    return pack_all(h, true, planar, st);
+    return pack_all(h, true, planar, stats_dev, st);
 }
 
 int smcx_sweep(smcx_lattice* h, int32_t n_sweeps, uint64_t seed, uint32_t first_sweep, const double* beta_dev,
@@ -1545,7 +1554,6 @@ int smcx_ladder_capture(smcx_lattice* h, int32_t n_sweeps, uint64_t seed, const 
     SMCX_HIP(hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal));
     SweepArgs a = base_args(h);
     a.seed = seed;
-    a.stats = stats_dev;
     a.ties = ties_dev;
     a.tie_cap = tie_cap;
     a.tie_count = tie_count_dev;
@@ -1556,7 +1564,7 @@ int smcx_ladder_capture(smcx_lattice* h, int32_t n_sweeps, uint64_t seed, const 
     a.beta_stride = 0;
     a.tau_begin = 0;
     a.tau_end = P.max_nA;
-    int rc = persistent_launch(h, a, st);
+    int rc = persistent_launch(h, a, stats_dev, st);
     hipError_t e = hipSuccess;
     if (rc == SMCX_OK) e = launch_advance_counter(sweep_counter_dev, (uint32_t)n_sweeps, st);
     hipGraph_t graph = nullptr;

@@ -400,6 +400,12 @@ struct Stats {
     int att = 0, acc = 0, tie = 0;
 };
 
+// This workgroup's counters of replica r.
+__device__ __forceinline__ unsigned long long* stat_slot(const SweepArgs& A, int r)
+{
+    return (unsigned long long*)(A.stats + ((int64_t)r * A.stat_parts + blockIdx.x % A.stat_parts) * A.stat_stride);
+}
+
 __device__ __forceinline__ int wave_sum_i(int v)
 {
 #pragma unroll
@@ -411,7 +417,7 @@ __device__ __forceinline__ void flush_stats(const SweepArgs& A, int r, Stats& st
 {
     const int a = wave_sum_i(st.att), c = wave_sum_i(st.acc), t = wave_sum_i(st.tie);
     if ((threadIdx.x & 63) == 0 && r >= 0) {
-        unsigned long long* p = (unsigned long long*)(A.stats + 3 * (int64_t)r);
+        unsigned long long* p = stat_slot(A, r);
         if (a) atomicAdd(p + 0, (unsigned long long)a);
         if (c) atomicAdd(p + 1, (unsigned long long)c);
         if (t) atomicAdd(p + 2, (unsigned long long)t);
@@ -435,7 +441,7 @@ __device__ __forceinline__ void flush_stats_block(const SweepArgs& A, int r, Sta
     }
     __syncthreads();
     if (threadIdx.x == 0 && r >= 0) {
-        unsigned long long* p = (unsigned long long*)(A.stats + 3 * (int64_t)r);
+        unsigned long long* p = stat_slot(A, r);
         if (red[0]) atomicAdd(p + 0, (unsigned long long)red[0]);
         if (red[1]) atomicAdd(p + 1, (unsigned long long)red[1]);
         if (red[2]) atomicAdd(p + 2, (unsigned long long)red[2]);

@@ -220,6 +220,14 @@ constexpr int preset_WY(const Preset& p) { return preset_w(p.ty, p.ell); }
 constexpr int preset_WZ(const Preset& p) { return preset_w(p.tz, p.ell); }
 constexpr bool preset_ok(const Preset& p) { return (p.tx * p.ell * preset_m(p)) % 16 == 0; }
 
+// Counter slots of the launches that many workgroups of one replica flush
+// into: atomics of the whole chip on one address run one after another at the
+// memory side (about 10 ns each: a launch of 256 workgroups over one replica
+// ended 5 us late), so each replica's counters are spread over this many
+// slots, 128 bytes apart, and added up once per call.
+constexpr int kStatStride = 16;  // int64 words per slot
+constexpr int stat_parts_of(int R) { return R >= 256 ? 1 : (R <= 4 ? 64 : 256 / R); }
+
 // Arguments of the sweep kernels (passed by value).
 struct SweepArgs {
     const RepDev* reps;
@@ -234,7 +242,8 @@ struct SweepArgs {
     uint8_t* occ;              // occupancy, natural layout (resident sweeps)
     uint8_t* ws;               // workspace base (padded copies)
     const double* beta;        // beta[js * beta_stride + r]
-    int64_t* stats;            // [R][3]
+    int64_t* stats;            // counters: slot (r, blockIdx % stat_parts) at stat_stride words each
+    int32_t stat_parts, stat_stride;
     smcx_tie* ties;
     int32_t* tie_count;
     const uint32_t* sweep_counter;  // when set, first sweep index is read here

@@ -1080,9 +1080,21 @@ __global__ void k_pack(const uint8_t* occ, uint8_t* ws, const RepDev* reps, int 
 // Padded copy interior -> natural layout: a workgroup per natural row, a
 // thread per site byte.
 template <int M, bool PLANAR>
-__global__ void k_unpack(uint8_t* occ, const uint8_t* ws, const RepDev* reps, int r, int F)
+__global__ void k_unpack(uint8_t* occ, const uint8_t* ws, const RepDev* reps, int r, int F, int64_t* slots, int parts,
+                         int64_t* stats)
 {
-    const RepDev& rep = reps[r < 0 ? (int)blockIdx.y : r];  // r < 0: one replica per grid row
+    const int ri = r < 0 ? (int)blockIdx.y : r;  // r < 0: one replica per grid row
+    if (blockIdx.x == 0 && threadIdx.x < 3) {
+        // the sweep launches' counter slots, added up and cleared
+        int64_t* s = slots + (int64_t)ri * parts * kStatStride + threadIdx.x;
+        int64_t v = 0;
+        for (int i = 0; i < parts; ++i) {
+            v += s[i * kStatStride];
+            s[i * kStatStride] = 0;
+        }
+        stats[3 * (int64_t)ri + threadIdx.x] += v;
+    }
+    const RepDev& rep = reps[ri];
     const uint8_t* pad = ws + rep.pad_off;
     uint8_t* o = occ + rep.occ_off;
     const int L0 = rep.L[0], L1 = rep.L[1], L2 = rep.L[2];
@@ -1707,7 +1719,8 @@ hipError_t sweep_occupancy(const void* kernel, int block, size_t lds, int* block
 }
 
 hipError_t launch_pack(int lattice, int K, bool unpack, bool planar, uint8_t* occ, uint8_t* ws,
-                       const RepDev* reps, int r, int64_t nrows, int nrep, hipStream_t st)
+                       const RepDev* reps, int r, int64_t nrows, int nrep, int64_t* slots, int parts,
+                       int64_t* stats, hipStream_t st)
 {
     // a workgroup per row (padded rows to pack, natural rows to unpack) of
     // replica r, or with r < 0 a grid row per replica (nrep of them, nrows
@@ -1721,7 +1734,7 @@ hipError_t launch_pack(int lattice, int K, bool unpack, bool planar, uint8_t* oc
     auto go = [&](auto mt, auto pt) {
         constexpr int M = decltype(mt)::value;
         constexpr bool PL = decltype(pt)::value;
-        if (unpack) hipLaunchKernelGGL((k_unpack<M, PL>), g, b, 0, st, occ, ws, reps, r, F);
+        if (unpack) hipLaunchKernelGGL((k_unpack<M, PL>), g, b, 0, st, occ, ws, reps, r, F, slots, parts, stats);
         else hipLaunchKernelGGL((k_pack<M, PL>), g, b, 0, st, occ, ws, reps, r, F);
     };
     using T2 = std::integral_constant<int, 2>;
