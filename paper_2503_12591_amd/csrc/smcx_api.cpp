@@ -91,6 +91,7 @@ struct Plan {
     bool rows;
     bool rows_mixed;  // replicas differ in mini-step decomposition: row launches only for whole sweeps
     int RT[3], rblock, rLP, rWY, rWZ;
+    int rlanes;  // lanes per trial (1: k_rows, more: k_rows_coop)
     int row_preset;  // compile-time row window matching the plan, or -1
     LdsLayout rlds;
     size_t off_rowoff, off_offP_r, off_offB_r;
@@ -98,7 +99,7 @@ struct Plan {
     int preset; // compile-time window preset of the stream kernel, or -1
     // resident sweeps: every replica fits a workgroup's LDS; lanes per trial
     // and threads per workgroup
-    bool resident;
+    bool resident, auto_resident;  // fits; auto mode takes it
     int res_lanes, res_block;
     LdsLayout res;
     std::vector<Replica> reps;
@@ -307,6 +308,7 @@ int make_plan(const smcx_desc* d, Plan& P)
     P.rows = false;
     P.rows_mixed = false;
     P.row_preset = -1;
+    P.rlanes = 1;
     if (P.group == P.m && P.nbuf == 1 && !(d->flags & SMCX_FLAG_TILES)) {
         bool same_m = true, same_cp = true;
         // basis-planar rows in the window; a pitch that is a multiple of 256
@@ -320,6 +322,24 @@ int make_plan(const smcx_desc* d, Plan& P)
             prowp = std::max(prowp, R.prowp);
             same_cp &= R.cp == P.reps[0].cp;
         }
+        // window depths of ry x rz rows of cells; false where a window would be
+        // taller than a lattice
+        auto rows_fit = [&](int ry, int rz, int& wy, int& wz) {
+            bool fits = true;
+            wy = wz = 0;
+            for (const Replica& R : P.reps) {
+                int wyr = 0, wzr = 0;
+                const int ncy = (int)R.edges[1].size(), ncz = (int)R.edges[2].size();
+                for (int c0 = 0; c0 < ncy; c0 += ry)
+                    wyr = std::max(wyr, R.origin[1][std::min(c0 + ry, ncy) - 1] - R.origin[1][c0] + 1 + 2 * kHalo);
+                for (int c0 = 0; c0 < ncz; c0 += rz)
+                    wzr = std::max(wzr, R.origin[2][std::min(c0 + rz, ncz) - 1] - R.origin[2][c0] + 1 + 2 * kHalo);
+                fits &= wyr <= R.L[1] && wzr <= R.L[2];
+                wy = std::max(wy, wyr);
+                wz = std::max(wz, wzr);
+            }
+            return fits;
+        };
         // score: busy lanes per block x waves per CU (12 make up for latency)
         // x a penalty when a single workgroup per CU leaves its staging
         // exposed x a small one for the 128-byte pitch
@@ -357,18 +377,7 @@ int make_plan(const smcx_desc* d, Plan& P)
                     const int lanes = ncx * ry * rz;
                     if (lanes > kMaxRowBlock) continue;
                     int wy = 0, wz = 0;
-                    bool fits = true;
-                    for (const Replica& R : P.reps) {
-                        int wyr = 0, wzr = 0;
-                        const int ncy = (int)R.edges[1].size(), ncz = (int)R.edges[2].size();
-                        for (int c0 = 0; c0 < ncy; c0 += ry)
-                            wyr = std::max(wyr, R.origin[1][std::min(c0 + ry, ncy) - 1] - R.origin[1][c0] + 1 + 2 * kHalo);
-                        for (int c0 = 0; c0 < ncz; c0 += rz)
-                            wzr = std::max(wzr, R.origin[2][std::min(c0 + rz, ncz) - 1] - R.origin[2][c0] + 1 + 2 * kHalo);
-                        fits &= wyr <= R.L[1] && wzr <= R.L[2];
-                        wy = std::max(wy, wyr);
-                        wz = std::max(wz, wzr);
-                    }
+                    const bool fits = rows_fit(ry, rz, wy, wz);
                     const int winb = prow * wy * wz;
                     // FCC partners count through a table of 16-bit window offsets
                     if (!fits || (P.lattice == SMCX_FCC &&
@@ -395,6 +404,46 @@ int make_plan(const smcx_desc* d, Plan& P)
                         best[0] = ry; best[1] = rz; best[2] = wy; best[3] = wz;
                     }
                 }
+        // Several lanes per trial where the launch's link cells alone would
+        // leave the chip's 65536 lane slots (one wave per SIMD) idle.  The
+        // most lanes that keep a launch within two waves per SIMD, and two
+        // lanes (BCC) up to eight waves: BCC 64^3 16 lanes 215 us per sweep (one lane
+        // 397), 96^3 8 lanes 287 (398), 128^3 4 lanes 321 (403), 160^3 2 lanes
+        // 449 (471), 256 replicas of 16^3 to 48^3 2 lanes 1512 (1784),
+        // 256^3 2 lanes 967 (1001), 320^3 2 lanes 1944 (1489); FCC 64^3
+        // 16 lanes 297 (734), 128^3 4 lanes 509 (775), 160^3 4 lanes 970 (908).
+        int64_t cells = 0;
+        bool images_fit = true;  // a row shorter than twice the halo would hold a site's image on both sides
+        for (const Replica& R : P.reps) {
+            cells += (int64_t)R.edges[0].size() * (int64_t)R.edges[1].size() * (int64_t)R.edges[2].size();
+            images_fit &= R.L[0] >= 2 * kHalo;
+        }
+        int G = 16;
+        while (G > P.m && (cells * G > 131072 || ncx * G > kMaxCoopRowBlock)) G /= 2;
+        const int64_t most = P.lattice == SMCX_BCC ? 524288 : 196608;
+        if (images_fit && cells * G <= most && ncx * G <= kMaxCoopRowBlock) {
+            // whole rows per workgroup: the fewest that keep three lanes in
+            // four busy (few rows: many workgroups, little to stage before the
+            // first trial), at the smallest pitch
+            const int prow = (prowp + 15) & ~15;
+            double best_busy = 0.0;
+            for (const auto& g : {std::array<int, 2>{1, 1}, {2, 1}, {1, 2}, {2, 2}, {4, 1}, {4, 2}, {4, 4}, {8, 4}, {8, 8}}) {
+                const int lanes = ncx * g[0] * g[1] * G;
+                int wy = 0, wz = 0;
+                if (best_busy >= 0.75 || lanes > kMaxCoopRowBlock || !rows_fit(g[0], g[1], wy, wz)) continue;
+                const double busy = (double)lanes / ((lanes + 63) / 64 * 64);
+                const int64_t winb = (int64_t)prow * wy * wz;
+                if (busy <= best_busy + 1e-12 || winb > 128 * 1024 ||
+                    coop_layout(P.K, P.S, P.m * P.Z1, 0, (int)winb).total + 64 > 160 * 1024)
+                    continue;
+                best_busy = busy;
+                best_lanes = lanes;
+                best_win = (int)winb;
+                best_prow = prow;
+                best[0] = g[0]; best[1] = g[1]; best[2] = wy; best[3] = wz;
+                P.rlanes = G;
+            }
+        }
         if (best_lanes > 0) {
             P.rows = true;
             P.RT[0] = ncx;
@@ -404,7 +453,8 @@ int make_plan(const smcx_desc* d, Plan& P)
             P.rLP = best_prow;
             P.rWY = best[2];
             P.rWZ = best[3];
-            P.rlds = lds_layout(P.lattice, P.K, P.S, P.Z1, P.sumZ, best_win, 1);
+            P.rlds = P.rlanes > 1 ? coop_layout(P.K, P.S, P.m * P.Z1, 0, best_win)
+                                  : lds_layout(P.lattice, P.K, P.S, P.Z1, P.sumZ, best_win, 1);
             P.row_preset = -1;
             // presets assume no partner has images in other shells
             bool images = false;
@@ -413,7 +463,7 @@ int make_plan(const smcx_desc* d, Plan& P)
                     for (int k = 0; k < P.Z1; ++k) images |= R.mult[s][k] != (s == 0 ? 1 : 0);
             for (int pi = 0; pi < kNumRowPresets; ++pi) {
                 const RowPreset& q = kRowPresets[pi];
-                if (same_cp && !images && q.lattice == P.lattice && q.K == P.K && q.S == P.S && q.cp == P.reps[0].cp && q.LP == P.rLP &&
+                if (P.rlanes == 1 && same_cp && !images && q.lattice == P.lattice && q.K == P.K && q.S == P.S && q.cp == P.reps[0].cp && q.LP == P.rLP &&
                     q.WY == P.rWY && q.WZ == P.rWZ && q.rt0 == P.RT[0] && q.rt1 == P.RT[1] && q.rt2 == P.RT[2])
                     P.row_preset = pi;
             }
@@ -447,21 +497,31 @@ int make_plan(const smcx_desc* d, Plan& P)
             org_max = std::max(org_max, n);
             cell_max = std::max(cell_max, c);
         }
-        auto al = [](int64_t v) { return (v + 15) & ~(int64_t)15; };
-        int64_t ro = 0;
-        P.res = LdsLayout{};
-        P.res.q_off = (int)ro;    ro = al(ro + 4 * qtab_entries(P.K, P.S));
-        P.res.pd_off = (int)ro;   ro = al(ro + 4 * P.m * P.Z1);
-        P.res.offb_off = (int)ro; ro = al(ro + 4 * (int64_t)org_max);
-        P.res.win_off = (int)ro;  ro = al(ro + win_max);
-        P.resident &= ro + 64 <= 160 * 1024;
-        P.res.win_bytes = (int)win_max;
-        P.res.total = (int)std::min<int64_t>(ro, 160 * 1024);
+        P.res = coop_layout(P.K, P.S, P.m * P.Z1, std::min(org_max, 1 << 16), (int)win_max);
+        P.resident &= P.res.total + 64 <= 160 * 1024;
         // as many lanes per trial as give every link cell its own lanes
         int G = 16;
         while (G > P.m && (int64_t)cell_max * G > 1024) G /= 2;
         P.res_lanes = G;
         P.res_block = (int)std::min<int64_t>(1024, ((int64_t)cell_max * G + 63) / 64 * 64);
+        // Auto mode: us per mini-step of either form, fitted to measurements.
+        // Resident: the largest replica on its CU (8 link cells 0.6, 64 1.1,
+        // 216 1.7, 512 2.85; FCC about an eighth more), 256 replicas at a
+        // time.  Row launches: 7.6 us each, and mini-steps of 0.6 us growing
+        // with the link cells of all replicas (14 thousand 1.3, 65 thousand
+        // 2.3).  BCC 20^3 177 (resident) against 197 us per sweep, 24^3 222
+        // against 194, 64 x 32^3 370 against 307, 256 x 32^3 370 against 668;
+        // FCC 12^3 193 against 275, 16^3 290 against 281.
+        const double c = cell_max, fcc = P.lattice == SMCX_FCC ? 1.12 : 1.0;
+        const double t_res = fcc * (0.55 + 0.0085 * std::min(c, 64.0) + 0.004 * std::max(c - 64.0, 0.0)) * ((P.R + 255) / 256);
+        double kcells = 0.0;
+        int per_launch = 1 << 30;
+        for (const Replica& R : P.reps) {
+            kcells += 1e-3 * (double)R.edges[0].size() * (double)R.edges[1].size() * (double)R.edges[2].size();
+            per_launch = std::min(per_launch, R.M[0] * P.m);
+        }
+        const double t_rows = 7.6 / per_launch + 0.6 + 0.05 * std::min(kcells, 14.0) + 0.02 * std::max(kcells - 14.0, 0.0);
+        P.auto_resident = P.resident && (!P.rows || t_res <= t_rows);
     }
 
     // workspace layout
@@ -915,7 +975,8 @@ int smcx_lattice_init(smcx_lattice** out, const smcx_desc* desc, uint8_t* occ_de
     SMCX_HIP(sweep_occupancy(h->k_stream, P.block, P.lds.total, &per_cu));
     h->stream_wgs = 8 * std::max(1, (cus / 8) * std::max(1, per_cu));
     if (P.rows) {
-        h->k_rows = row_kernel(P.lattice, P.K, P.S, P.rblock, P.row_preset);
+        h->k_rows = P.rlanes > 1 ? row_coop_kernel(P.lattice, P.K, P.S, P.rlanes)
+                                 : row_kernel(P.lattice, P.K, P.S, P.rblock, P.row_preset);
         SMCX_HIP(set_sweep_lds_limit(h->k_rows, P.rlds.total));
         int rcu = 1;
         SMCX_HIP(sweep_occupancy(h->k_rows, P.rblock, P.rlds.total, &rcu));
@@ -1173,16 +1234,12 @@ static int run_sweeps(smcx_lattice* h, int32_t n_sweeps, uint64_t seed, uint32_t
     // index from it and first_sweep counts from 0
     if (sweep_counter) first_sweep = 0;
     const Plan& P = h->P;
-    // auto: whole replicas in LDS for lattices too small to fill a launch per
-    // mini-step group, and where there is about a replica for every four CUs
-    // (256 BCC 32^3 replicas: 370 us per sweep against 583 in row launches);
-    // else row windows where they apply; else tile windows, persistent for
-    // several replicas
-    if (mode == SMCX_MODE_AUTO) {
-        if (P.resident && (P.total_sites <= (1 << 16) || P.R >= 64)) mode = SMCX_MODE_PERSISTENT;
-        else if (P.rows) mode = SMCX_MODE_STREAM;
-        else mode = P.total_sites <= (1 << 16) || P.R > 1 ? SMCX_MODE_PERSISTENT : SMCX_MODE_STREAM;
-    }
+    // auto: whole replicas in LDS where that is faster; row windows where they
+    // apply; else tile windows, persistent for small lattices and several
+    // replicas
+    if (mode == SMCX_MODE_AUTO)
+        mode = P.auto_resident ? SMCX_MODE_PERSISTENT
+               : P.rows || (P.R == 1 && P.total_sites > (1 << 16)) ? SMCX_MODE_STREAM : SMCX_MODE_PERSISTENT;
     // the row kernel reads basis-planar rows; replicas of different
     // decompositions share its launches only over whole sweeps
     const bool rows = mode == SMCX_MODE_STREAM && P.rows && (!P.rows_mixed || (tau_begin == 0 && tau_end >= P.max_nA));

@@ -333,12 +333,8 @@ struct Coop {
         const uint32_t qacc = group_sum<G, uint32_t>(part);
         int f = 0;
         if (p8 != q8) {
-            bool settled;
-            f = screen(qacc, qscale, qeps, beta, d.w1, settled);
-            if (!settled) {
-                f = decide_binary64<E>(D + pq, dsh[0], dsh[1], dsh[2], dsh[3], K, S, beta, d.w1, d.w2);
-                if (f & 2) on_tie(f & 1);
-            }
+            f = metropolis<E>(qacc, qscale, qeps, D + pq, dsh[0], dsh[1], dsh[2], dsh[3], K, S, beta, d.w1, d.w2);
+            if (f & 2) on_tie(f & 1);
         }
         if (f & 1) {
             // the lane's site takes the other's species; its images are
@@ -392,8 +388,10 @@ __device__ __forceinline__ void step_barrier(bool waves)
 // offset, one lane per trial: BCC 8^3 588 -> 67 us per sweep, FCC 18x13x11
 // 3150 -> 500 us; against row launches 256 BCC 32^3 replicas 583 -> 370 us.
 // ---------------------------------------------------------------------------
-template <int LAT, int E, int KK, int SS, int G, int MAXB>
-__global__ __launch_bounds__(MAXB) void k_resident(SweepArgs A)
+constexpr int kResidentBlock = 1024;
+
+template <int LAT, int E, int KK, int SS, int G>
+__global__ __launch_bounds__(kResidentBlock) void k_resident(SweepArgs A)
 {
     using CO = Coop<LAT, E, KK, SS, G>;
     constexpr int m = CO::m, F = Enc<E>::F;
@@ -555,36 +553,230 @@ __global__ __launch_bounds__(MAXB) void k_resident(SweepArgs A)
     }
 }
 
-template <int LAT, int E, int G, int MAXB>
-static const void* resident_kernel_e(int K, int S)
+// ---------------------------------------------------------------------------
+// Row windows with G lanes per trial: the schedule, windows and write-back of
+// k_rows (one launch per (o_y, o_z) group, whole rows of link cells per
+// workgroup), for launches with too few link cells to fill the chip.  Bound by
+// latency: of the 13 us of a BCC 64^3 launch (8 mini-steps, 16 lanes per
+// trial; 24 us with one lane) 2.8 are an empty launch, 4.8 the chain of
+// argument, table and window reads and the write-back, 0.54 each mini-step.
+// ---------------------------------------------------------------------------
+template <int LAT, int E, int KK, int SS, int G>
+__global__ __launch_bounds__(kMaxCoopRowBlock) void k_rows_coop(SweepArgs A)
+{
+    using CO = Coop<LAT, E, KK, SS, G>;
+    using Geo = GeoRow<KK, SS>;
+    constexpr int m = CO::m;
+    extern __shared__ __align__(16) uint8_t smem[];
+    const int K = KK ? KK : A.K, S = SS ? SS : A.S;
+    int32_t* Q = (int32_t*)(smem + A.lds_q);
+    int32_t* pdt = (int32_t*)(smem + A.lds_pd);
+    uint8_t* win = smem + A.lds_win;
+    const int nQ = S * K * K * K + K * K;
+    for (int i = threadIdx.x; i < nQ; i += blockDim.x) Q[i] = A.Qtab[i];
+    for (int i = threadIdx.x; i < m * CO::Z1; i += blockDim.x) pdt[i] = ((const int32_t*)A.pdisp)[i];
+    const float qscale = __int_as_float(ld_const(A.Qtab, nQ)), qeps = __int_as_float(ld_const(A.Qtab, nQ + 1));
+    const int64_t total = ld_const(A.tile_off, A.R);  // row groups of all replicas
+    const int64_t W = gridDim.x / 8;
+    const int64_t chunk = (total + 7) / 8;
+    const int64_t lo = (blockIdx.x % 8) * chunk;
+    const int64_t hi = min(lo + chunk, total);
+    CO co;
+    co.init();
+    const int T0 = A.T[0], T1 = A.T[1], T2 = A.T[2];
+    const int l = threadIdx.x / G;
+    const int lx = l % T0, ly = (l / T0) % T1, lz = l / (T0 * T1);
+    const bool waves = blockDim.x > 64;
+    const uint32_t t = A.sweep_counter ? *A.sweep_counter + A.first_sweep : A.first_sweep;
+    Stats st;
+    int r_stats = -1;
+    __syncthreads();  // the tables are in place
+    for (int64_t i = lo + blockIdx.x / 8; i < hi; i += W) {
+        int a = 0, z = A.R - 1;  // last replica with tile_off[r] <= i
+        while (a < z) {
+            const int mid = (a + z + 1) >> 1;
+            if (ld_const(A.tile_off, mid) <= i) a = mid; else z = mid - 1;
+        }
+        int r = a;
+        int64_t grp = i - ld_const(A.tile_off, a);
+        uniform(r, grp);
+        const RepDev& rep = rep_of(A, r);
+        const int Mx = scalar(rep.M[0]), My = scalar(rep.M[1]);
+        int g0 = A.g, gn = A.nb;
+        if (A.gq >= 0) {
+            // this replica's q-th (o_y, o_z) group, every offset o_x and basis site
+            if (A.gq >= My * rep.M[2]) continue;
+            gn = m * Mx;
+            g0 = A.gq * gn;
+        }
+        if (g0 >= rep.nA) continue;
+        const int rest = g0 / m / Mx, oy = rest % My, oz = rest / My;
+        const int gy = (int)grp % rep.rg[0], gz = (int)grp / rep.rg[0];
+        TileGeom tg;
+        tg.c0[0] = 0;
+        tg.c1[0] = rep.nc[0];
+        tg.c0[1] = gy * T1;
+        tg.c1[1] = min(tg.c0[1] + T1, rep.nc[1]);
+        tg.c0[2] = gz * T2;
+        tg.c1[2] = min(tg.c0[2] + T2, rep.nc[2]);
+        if (oy >= rep.emin[1] || oz >= rep.emin[2]) {
+            // uneven partitions: row groups without a cell row active at
+            // these offsets are skipped before staging
+            bool any_y = false, any_z = false;
+            for (int c = tg.c0[1]; c < tg.c1[1]; ++c)
+                any_y |= cell_origin<Geo>(A, rep, 1, c + 1) - cell_origin<Geo>(A, rep, 1, c) > oy;
+            for (int c = tg.c0[2]; c < tg.c1[2]; ++c)
+                any_z |= cell_origin<Geo>(A, rep, 2, c + 1) - cell_origin<Geo>(A, rep, 2, c) > oz;
+            if (!(any_y && any_z)) continue;
+        }
+        tg.w0[0] = -kHalo;
+        tg.n[0] = rep.L[0] + 2 * kHalo;
+        tg.gx0 = 0;
+        const int oo[3] = {0, oy, oz};
+#pragma unroll
+        for (int ax = 1; ax < 3; ++ax) {
+            tg.w0[ax] = cell_origin<Geo>(A, rep, ax, tg.c0[ax]) + oo[ax] - kHalo;
+            const int w1 = min(cell_origin<Geo>(A, rep, ax, tg.c1[ax] - 1) + oo[ax] + kHalo + 1, rep.L[ax] + kHalo);
+            tg.n[ax] = w1 - tg.w0[ax];
+        }
+        if (tg.n[1] <= 0 || tg.n[2] <= 0) continue;
+        lds_barrier();  // every lane is done with the previous window
+        stage_async<LAT, Geo>(A, rep, tg, A.ws + rep.pad_off, win);
+        // this group's cell and first draws while the loads fly
+        const int Lx = scalar(rep.L[0]), Ly = scalar(rep.L[1]);
+        const int LP = A.LP, PL = LP * A.WY, CP = scalar(rep.cp);
+        co.set_pitches(LP, PL, CP);
+        const int cx = lx, cy = tg.c0[1] + ly, cz = tg.c0[2] + lz;
+        const bool row_in = lz < T2 && cy < tg.c1[1] && cz < tg.c1[2];
+        const bool in = row_in && cx < tg.c1[0];
+        int x0 = 0, ex = 0, y = 0, z0 = 0;
+        bool row_yz = false;
+        if (row_in) {
+            const int y0 = cell_origin<Geo>(A, rep, 1, cy), ey = cell_origin<Geo>(A, rep, 1, cy + 1) - y0;
+            const int zc = cell_origin<Geo>(A, rep, 2, cz), ez = cell_origin<Geo>(A, rep, 2, cz + 1) - zc;
+            // the cell row has active sites at (o_y, o_z)
+            row_yz = oy < ey && oz < ez;
+            y = y0 + oy;
+            z0 = zc + oz;
+        }
+        if (in) {
+            x0 = cell_origin<Geo>(A, rep, 0, cx);
+            ex = row_yz ? cell_origin<Geo>(A, rep, 0, cx + 1) - x0 : 0;
+        }
+        const int64_t yz_site = (int64_t)m * Lx * ((int64_t)y + (int64_t)Ly * z0);
+        const int row_byte0 = ((z0 - tg.w0[2]) * A.WY + (y - tg.w0[1])) * LP + kHalo;
+        const double beta = ld_const(A.beta, r);
+        const int tau1 = g0 + gn, ox0 = (g0 / m) % Mx;
+        // lane i draws for mini-step tau + i
+        auto draw = [&](int tau) {
+            const int tt = tau + co.j, b = tt % m, ox = ox0 + (tt / m - g0 / m), x = x0 + ox;
+            const bool has = ox < ex && tt < tau1;
+            const int64_t site = yz_site + (b + m * x);
+            CoopDraw d;
+            uint32_t w0, w3;
+            philox4x32_10((uint32_t)site, (uint32_t)((uint64_t)site >> 32), t, (uint32_t)r, (uint32_t)A.seed,
+                          (uint32_t)(A.seed >> 32), w0, d.w1, d.w2, w3);
+            (void)w3;
+            const int pd = pdt[b * CO::Z1 + (int)__umulhi(w0, (uint32_t)CO::Z1)];
+            const int dx = (int8_t)pd, dy = (int8_t)(pd >> 8), dz = (int8_t)(pd >> 16), bt = pd >> 24;
+            const int la = row_byte0 + x + b * CP, lb = la + dz * PL + dy * LP + dx + (bt - b) * CP;
+            // the window holds images along x only
+            d.a = (uint32_t)(has ? la : 0) | (has ? kSiteActive : 0u) | (uint32_t)b << 19 | image_code(x, Lx) << 21;
+            d.b = (uint32_t)(has ? lb : 0) | (uint32_t)bt << 19 | image_code(x + dx, Lx) << 21;
+            return d;
+        };
+        CoopDraw mine = draw(g0);
+        __builtin_amdgcn_s_waitcnt(0);
+        __syncthreads();
+        if (r != r_stats) {
+            if (co.j != 0) st = Stats();
+            flush_stats_block(A, r_stats, st);
+            r_stats = r;
+        }
+        for (int tau = g0; tau < tau1; tau += G) {
+            if (tau != g0) mine = draw(tau);
+            const int n = min(G, tau1 - tau);
+            auto step = [&](const CoopDraw& d, int k) {
+                if (d.a & kSiteActive) {
+                    const int f = co.trial(win, d, beta, K, S, Lx, 0, 0, Q, qscale, qeps, A.Dtab, [&](int acc) {
+                        if (co.j != 0) return;
+                        const int tt = tau + k;
+                        log_tie(A, r, t, yz_site + (tt % m + m * (x0 + ox0 + (tt / m - g0 / m))), acc);
+                    });
+                    ++st.att;
+                    st.acc += f & 1;
+                    st.tie += f >> 1;
+                }
+                // the next offset's trials read what this one wrote
+                if ((tau + k + 1) % m == 0) step_barrier(waves);
+            };
+            if constexpr (G <= 4) {
+                step(co.template from_quad_lane<0>(mine), 0);
+                if (n > 1) step(co.template from_quad_lane<1>(mine), 1);
+                if constexpr (G == 4) {
+                    if (n > 2) step(co.template from_quad_lane<2>(mine), 2);
+                    if (n > 3) step(co.template from_quad_lane<3>(mine), 3);
+                }
+            } else {
+                CoopDraw next = co.from_lane(mine, 0);
+                for (int k = 0; k < n; ++k) {
+                    const CoopDraw d = next;
+                    next = co.from_lane(mine, min(k + 1, n - 1));
+                    step(d, k);
+                }
+            }
+        }
+        __syncthreads();  // every trial's window writes are visible
+        if (row_yz)
+            rows_writeback<LAT, Geo>(A, rep, tg, lx * G + co.j, T0 * G, y, z0, A.ws + rep.pad_off, win);
+    }
+    if (co.j != 0) st = Stats();
+    flush_stats_block(A, r_stats, st);
+}
+
+// Kernel with compile-time species / shell counts for the 4-species BCC and
+// 5-species FCC alloys with 4 or 2 shells, runtime counts otherwise.
+template <bool ROWS, int LAT, int E, int KK, int SS, int G>
+static const void* coop_kernel_ks()
+{
+    if constexpr (ROWS) return (const void*)k_rows_coop<LAT, E, KK, SS, G>;
+    else return (const void*)k_resident<LAT, E, KK, SS, G>;
+}
+
+template <bool ROWS, int LAT, int E, int G>
+static const void* coop_kernel_e(int K, int S)
 {
     if constexpr (LAT == SMCX_BCC && E == 1) {
-        if (K == 4 && S == 4) return (const void*)k_resident<LAT, E, 4, 4, G, MAXB>;
-        if (K == 4 && S == 2) return (const void*)k_resident<LAT, E, 4, 2, G, MAXB>;
+        if (K == 4 && S == 4) return coop_kernel_ks<ROWS, LAT, E, 4, 4, G>();
+        if (K == 4 && S == 2) return coop_kernel_ks<ROWS, LAT, E, 4, 2, G>();
     }
     if constexpr (LAT == SMCX_FCC && E == 3) {
-        if (K == 5 && S == 4) return (const void*)k_resident<LAT, E, 5, 4, G, MAXB>;
-        if (K == 5 && S == 2) return (const void*)k_resident<LAT, E, 5, 2, G, MAXB>;
+        if (K == 5 && S == 4) return coop_kernel_ks<ROWS, LAT, E, 5, 4, G>();
+        if (K == 5 && S == 2) return coop_kernel_ks<ROWS, LAT, E, 5, 2, G>();
     }
-    return (const void*)k_resident<LAT, E, 0, 0, G, MAXB>;
+    return coop_kernel_ks<ROWS, LAT, E, 0, 0, G>();
 }
 
-template <int LAT, int G, int MAXB>
-static const void* resident_kernel_l(int K, int S)
+template <bool ROWS, int LAT, int G>
+static const void* coop_kernel_l(int K, int S)
 {
-    return K <= 4 ? resident_kernel_e<LAT, 1, G, MAXB>(K, S)
-                  : (K == 5 ? resident_kernel_e<LAT, 3, G, MAXB>(K, S) : resident_kernel_e<LAT, 2, G, MAXB>(K, S));
+    return K <= 4 ? coop_kernel_e<ROWS, LAT, 1, G>(K, S)
+                  : (K == 5 ? coop_kernel_e<ROWS, LAT, 3, G>(K, S) : coop_kernel_e<ROWS, LAT, 2, G>(K, S));
 }
 
-const void* resident_kernel(int lattice, int K, int S, int lanes)
+template <bool ROWS>
+static const void* coop_kernel(int lattice, int K, int S, int lanes)
 {
     if (lattice == SMCX_BCC)
-        return lanes == 16 ? resident_kernel_l<SMCX_BCC, 16, 1024>(K, S)
-                           : (lanes == 8 ? resident_kernel_l<SMCX_BCC, 8, 1024>(K, S)
-                                         : (lanes == 4 ? resident_kernel_l<SMCX_BCC, 4, 1024>(K, S)
-                                                       : resident_kernel_l<SMCX_BCC, 2, 1024>(K, S)));
-    return lanes == 16 ? resident_kernel_l<SMCX_FCC, 16, 1024>(K, S)
-                       : (lanes == 8 ? resident_kernel_l<SMCX_FCC, 8, 1024>(K, S) : resident_kernel_l<SMCX_FCC, 4, 1024>(K, S));
+        return lanes == 16 ? coop_kernel_l<ROWS, SMCX_BCC, 16>(K, S)
+                           : (lanes == 8 ? coop_kernel_l<ROWS, SMCX_BCC, 8>(K, S)
+                                         : (lanes == 4 ? coop_kernel_l<ROWS, SMCX_BCC, 4>(K, S)
+                                                       : coop_kernel_l<ROWS, SMCX_BCC, 2>(K, S)));
+    return lanes == 16 ? coop_kernel_l<ROWS, SMCX_FCC, 16>(K, S)
+                       : (lanes == 8 ? coop_kernel_l<ROWS, SMCX_FCC, 8>(K, S) : coop_kernel_l<ROWS, SMCX_FCC, 4>(K, S));
 }
+
+const void* resident_kernel(int lattice, int K, int S, int lanes) { return coop_kernel<false>(lattice, K, S, lanes); }
+const void* row_coop_kernel(int lattice, int K, int S, int lanes) { return coop_kernel<true>(lattice, K, S, lanes); }
 
 }  // namespace smcx

@@ -367,7 +367,30 @@ __device__ __forceinline__ int screen(uint32_t qacc, float qscale, float qeps, d
     return (down | (up & !far & (uf < Pf))) ? 1 : 0;
 }
 
-// The decision of a trial: the screen, or decide_binary64 from the biased
+// The same for the trials the float screen leaves open (about 1 in 2e4 at the
+// benchmark's temperature, more for few shells, where two sites often have the
+// same neighbours), before the sum in binary64 with its table reads is called
+// for.  No neighbour count differs (`same`): dE is a zero, accepted.  Else
+// x = beta e log2(e) in binary64, exp2 of its fraction in float: relative
+// error below 3e-7 (the fraction's rounding, v_exp_f32's ulp, u's rounding),
+// so a margin of 1e-6 + 1.2 beta eps relative plus 1e-9 for u's truncation
+// settles u < exp(-beta dE) as above.
+__device__ __forceinline__ int screen_fine(uint32_t qacc, float qscale, float qeps, double beta, uint32_t w1, bool same,
+                                           bool& settled)
+{
+    const double e = (double)(int32_t)qacc * (double)qscale;  // exact: a 32-bit integer times a power of two
+    const double eps = (double)qeps, y = beta * eps;
+    settled = same | (e <= -eps);
+    if (settled) return 1;
+    const double x = beta * e * 1.4426950408889634, n = rint(x);
+    if (!(e > eps && y >= 0.0 && y < 0.25 && x < 100.0)) return 0;
+    const float P = ldexpf(__builtin_amdgcn_exp2f((float)(n - x)), -(int)n);
+    const float uf = (float)w1 * 0x1p-32f;
+    settled = fabsf(uf - P) > (1e-6f + 1.2f * (float)y) * P + 1e-9f;
+    return uf < P ? 1 : 0;
+}
+
+// The decision of a trial: the screens, or decide_binary64 from the biased
 // count differences d0 .. d3.  Returns bit 0: accepted, bit 1: near-tie.
 template <int E>
 __device__ __forceinline__ int metropolis(uint32_t qacc, float qscale, float qeps, const double* Dp,
@@ -375,8 +398,14 @@ __device__ __forceinline__ int metropolis(uint32_t qacc, float qscale, float qep
                                           typename Enc<E>::T d3, int K, int S, double beta, uint32_t w1, uint32_t w2)
 {
     bool settled;
-    const int f = screen(qacc, qscale, qeps, beta, w1, settled);
-    return settled ? f : decide_binary64<E>(Dp, d0, d1, d2, d3, K, S, beta, w1, w2);
+    int f = screen(qacc, qscale, qeps, beta, w1, settled);
+    if (!settled) {
+        constexpr typename Enc<E>::T z = Enc<E>::bias;
+        const bool same = ((d0 ^ z) | (S > 1 ? d1 ^ z : 0) | (S > 2 ? d2 ^ z : 0) | (S > 3 ? d3 ^ z : 0)) == 0;
+        f = screen_fine(qacc, qscale, qeps, beta, w1, same, settled);
+        if (!settled) f = decide_binary64<E>(Dp, d0, d1, d2, d3, K, S, beta, w1, w2);
+    }
+    return f;
 }
 
 // Append a near-tie to the log (counted past its capacity, stored up to it).

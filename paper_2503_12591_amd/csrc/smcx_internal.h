@@ -21,6 +21,7 @@ constexpr int kMaxZ1 = 12;
 constexpr int kMaxSumZ = 54;
 constexpr int kBlock = 256;
 constexpr int kMaxRowBlock = 1024;  // row kernel: several x-rows of link cells per workgroup
+constexpr int kMaxCoopRowBlock = 512;  // the same with several lanes per trial
 // Static workspace of smcx_lattice_init_static (bytes, per device) and the
 // device ordinals it serves.
 constexpr size_t kStaticWorkspaceBytes = (size_t)64 << 20;
@@ -292,6 +293,22 @@ inline LdsLayout lds_layout(int lattice, int K, int S, int Z1, int sumZ, int win
     L.win_bytes = al(win_bytes);
     o = al(o + nbuf * L.win_bytes);
     L.total = o;
+    return L;
+}
+
+// The same for the kernels with several lanes per trial: the integer dE table,
+// the partner table, n_origins cell origins, the window.
+inline LdsLayout coop_layout(int K, int S, int n_partners, int n_origins, int win_bytes)
+{
+    auto al = [](int v) { return (v + 15) & ~15; };
+    LdsLayout L{};
+    int o = 0;
+    L.q_off = o;    o = al(o + 4 * qtab_entries(K, S));
+    L.pd_off = o;   o = al(o + 4 * n_partners);
+    L.offb_off = o; o = al(o + 4 * n_origins);
+    L.win_off = o;
+    L.win_bytes = al(win_bytes);
+    L.total = o + L.win_bytes;
     return L;
 }
 

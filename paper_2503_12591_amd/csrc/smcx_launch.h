@@ -12,6 +12,8 @@ const void* sweep_kernel(int lattice, int K, bool persistent, int preset, int nb
 const void* row_kernel(int lattice, int K, int S, int block, int preset);
 // Resident sweep kernel with `lanes` lanes per trial (2 to 16 BCC, 4 to 16 FCC).
 const void* resident_kernel(int lattice, int K, int S, int lanes);
+// Row sweep kernel with `lanes` lanes per trial (the same range).
+const void* row_coop_kernel(int lattice, int K, int S, int lanes);
 hipError_t launch_sweep(const void* kernel, dim3 grid, int block, size_t lds, hipStream_t st, const SweepArgs& a);
 hipError_t set_sweep_lds_limit(const void* kernel, size_t lds);
 hipError_t sweep_occupancy(const void* kernel, int block, size_t lds, int* blocks_per_cu);
