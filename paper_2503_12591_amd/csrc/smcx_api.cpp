@@ -1361,12 +1361,12 @@ int smcx_pair_counts(smcx_lattice* h, int64_t* counts_dev, void* stream)
         for (int a = 0; a < 3; ++a) one_size &= R.L[a] == P.reps[0].L[a];
     if (one_size) {
         const Replica& R = P.reps[0];
-        SMCX_HIP(launch_pair_counts(P.lattice, P.K, P.S, h->occ, R.N, R.L, P.R, counts_dev, st));
+        SMCX_HIP(launch_pair_counts(P.lattice, P.K, P.S, h->occ, R.N, R.L, P.R, counts_dev, nullptr, st));
         return SMCX_OK;
     }
     for (int r = 0; r < P.R; ++r) {
         const Replica& R = P.reps[r];
-        SMCX_HIP(launch_pair_counts(P.lattice, P.K, P.S, h->occ + R.occ_off, R.N, R.L, 1, counts_dev + per * r, st));
+        SMCX_HIP(launch_pair_counts(P.lattice, P.K, P.S, h->occ + R.occ_off, R.N, R.L, 1, counts_dev + per * r, nullptr, st));
     }
     return SMCX_OK;
 }
@@ -1550,24 +1550,18 @@ int smcx_energy_backward(int32_t lattice, const int32_t* dims, int32_t n_species
     const int64_t N = (int64_t)lattice_m(lattice) * dims[0] * dims[1] * dims[2];
     hipStream_t st = (hipStream_t)stream;
     const int64_t per = (int64_t)n_shells * n_species * n_species;
-    // species check: the flag lives in the first word of counts_dev, which
-    // the counts overwrite afterwards (a species >= K would shift a counter
-    // field out of range and silently miscount)
-    {
-        int32_t* bad = (int32_t*)counts_dev;
-        SMCX_HIP(launch_fill_i32(bad, 1, 0, st));
-        SMCX_HIP(launch_validate(occ_batch_dev, N * (int64_t)B, n_species, bad, st));
-        int32_t bad_h = 0;
-        SMCX_HIP(hipMemcpyAsync(&bad_h, bad, sizeof(int32_t), hipMemcpyDeviceToHost, st));
-        SMCX_HIP(hipStreamSynchronize(st));
-        if (bad_h) return fail(SMCX_E_INVALID_ARG, "a configuration holds a species >= n_species");
-    }
     SMCX_HIP(launch_fill_i64(counts_dev, per * B, 0, st));
     for (int32_t b0 = 0; b0 < B; b0 += 65535) {
         const int nb = std::min<int32_t>(65535, B - b0);
         SMCX_HIP(launch_pair_counts(lattice, n_species, n_shells, occ_batch_dev + (int64_t)b0 * N, N, dims, nb,
-                                    counts_dev + per * b0, st));
+                                    counts_dev + per * b0, counts_dev, st));
     }
+    // species check: the counting kernel sets the top bit of the first count
+    // (a species >= K would be miscounted silently)
+    int64_t first = 0;
+    SMCX_HIP(hipMemcpyAsync(&first, counts_dev, sizeof(first), hipMemcpyDeviceToHost, st));
+    SMCX_HIP(hipStreamSynchronize(st));
+    if (first < 0) return fail(SMCX_E_INVALID_ARG, "a configuration holds a species >= n_species");
     return SMCX_OK;
 }
 

@@ -1186,424 +1186,6 @@ __global__ void k_fill_i32(int32_t* p, int64_t n, int32_t v)
 }
 
 // ---------------------------------------------------------------------------
-// Pair counts C[cfg][s][k][l] on the natural layout, periodic wrap through
-// per-site wrapped coordinates.  One thread per conventional cell (all its
-// basis sites), shells processed one after another; per-lane counts kept in
-// 16-bit fields (<= 24 per site, <= 2048 sites per lane between flushes),
-// then wave-reduced and added with 64-bit atomics.  (Pair numbers n_m^{pp'}
-// of the EPI features, Methods "The EPI and qSRO model".)
-// ---------------------------------------------------------------------------
-__device__ __forceinline__ uint32_t wave_sum(uint32_t v)
-{
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
-
-template <int LAT, int KP>
-__global__ __launch_bounds__(kBlock) void k_pair_counts(const uint8_t* occ, int64_t N, int L0, int L1, int L2,
-                                                        int K, int S, int cells_per_block, int64_t* counts)
-{
-    constexpr Geometry G = kGeom[LAT];
-    constexpr int m = G.m;
-    const int cfg = blockIdx.y;
-    const uint8_t* o = occ + (int64_t)cfg * N;
-    const int64_t ncell = (int64_t)L0 * L1 * L2;
-    const int64_t cb = (int64_t)blockIdx.x * cells_per_block;
-    const int64_t ce = min(cb + cells_per_block, ncell);
-    const int64_t plane = (int64_t)L0 * L1;
-#pragma unroll
-    for (int s = 0; s < kMaxShells; ++s) {
-        if (s >= S) break;
-        uint32_t acc[KP][KP / 2];
-#pragma unroll
-        for (int k = 0; k < KP; ++k)
-#pragma unroll
-            for (int j = 0; j < KP / 2; ++j) acc[k][j] = 0;
-        for (int64_t c = cb + threadIdx.x; c < ce; c += blockDim.x) {
-            const int x = (int)(c % L0);
-            const int64_t cr = c / L0;
-            const int y = (int)(cr % L1);
-            const int z = (int)(cr / L1);
-            int64_t X[5], Y[5], Z[5];
-#pragma unroll
-            for (int d = -2; d <= 2; ++d) {
-                int xx = x + d, yy = y + d, zz = z + d;
-                xx += xx < 0 ? L0 : (xx >= L0 ? -L0 : 0);
-                yy += yy < 0 ? L1 : (yy >= L1 ? -L1 : 0);
-                zz += zz < 0 ? L2 : (zz >= L2 ? -L2 : 0);
-                X[d + 2] = xx;
-                Y[d + 2] = (int64_t)yy * L0;
-                Z[d + 2] = (int64_t)zz * plane;
-            }
-#pragma unroll
-            for (int b = 0; b < m; ++b) {
-                const int sig = o[m * c + b];
-                uint64_t n = 0;
-#pragma unroll
-                for (int i = 0; i < G.Z[s]; ++i) {
-                    const Nb nb = nb_of(G, b, G.v[s][i][0], G.v[s][i][1], G.v[s][i][2]);
-                    const int64_t j = (int64_t)m * (X[nb.dx + 2] + Y[nb.dy + 2] + Z[nb.dz + 2]) + nb.bt;
-                    n += (uint64_t)1 << (8 * o[j]);
-                }
-#pragma unroll
-                for (int k = 0; k < KP; ++k) {
-                    const uint32_t mask = sig == k ? 0xFFFFFFFFu : 0u;
-#pragma unroll
-                    for (int jj = 0; jj < KP / 2; ++jj) {
-                        const uint32_t w = (uint32_t)((n >> (16 * jj)) & 0xFF) |
-                                           ((uint32_t)((n >> (16 * jj + 8)) & 0xFF) << 16);
-                        acc[k][jj] += w & mask;
-                    }
-                }
-            }
-        }
-        int64_t* Cs = counts + ((int64_t)cfg * S + s) * K * K;
-#pragma unroll
-        for (int k = 0; k < KP; ++k) {
-#pragma unroll
-            for (int jj = 0; jj < KP / 2; ++jj) {
-                const uint32_t lo = wave_sum(acc[k][jj] & 0xFFFFu);
-                const uint32_t hi = wave_sum(acc[k][jj] >> 16);
-                if ((threadIdx.x & 63) == 0 && k < K) {
-                    if (2 * jj < K && lo)
-                        atomicAdd((unsigned long long*)&Cs[k * K + 2 * jj], (unsigned long long)lo);
-                    if (2 * jj + 1 < K && hi)
-                        atomicAdd((unsigned long long*)&Cs[k * K + 2 * jj + 1], (unsigned long long)hi);
-                }
-            }
-        }
-    }
-}
-
-// ---------------------------------------------------------------------------
-// Pair counts of up to 4 species through LDS tiles: a block stages TX x TY x
-// 16 conventional cells plus a 2-cell periodic halo of one configuration;
-// lane (x, y) walks the 16 cells along z, forms the packed neighbour
-// histogram of each site per shell over one direction d of every +-d pair
-// (one byte read and one shift-add per neighbour, offsets fixed at compile
-// time) and adds it to 16-bit fields of the row of the site's species.  These
-// half-shell counts H give the directed counts as C[k][l] = H[k][l] +
-// H[l][k]: the pairs along -d from species k to l are those along +d from l
-// to k.  tiles_per_block keeps every field below 2^16 between flushes.
-// ---------------------------------------------------------------------------
-template <int LAT, int TX>
-__global__ __launch_bounds__(kBlock) void k_pair_counts_tiled(const uint8_t* occ, int64_t N, int L0, int L1, int L2,
-                                                              int K, int S, int tiles_per_block, int64_t* counts)
-{
-    constexpr Geometry G = kGeom[LAT];
-    constexpr int m = G.m;
-    constexpr int TY = kBlock / TX, TZ = 16;
-    constexpr int WX = TX + 2 * kHalo, WY = TY + 2 * kHalo, WZ = TZ + 2 * kHalo;
-    constexpr int LP = WX * m, PL = LP * WY;
-    __shared__ __align__(16) uint8_t win[PL * WZ];
-    const uint8_t* o = occ + (int64_t)blockIdx.y * N;
-    const int ntx = (L0 + TX - 1) / TX, nty = (L1 + TY - 1) / TY, ntz = (L2 + TZ - 1) / TZ;
-    const int64_t ntiles = (int64_t)ntx * nty * ntz;
-    const int64_t t0 = (int64_t)blockIdx.x * tiles_per_block;
-    const int64_t t1 = min(t0 + (int64_t)tiles_per_block, ntiles);
-    const int lx = threadIdx.x % TX, ly = threadIdx.x / TX;
-    auto wrap = [](int v, int L) {
-        v += v < 0 ? L : 0;
-        v -= v >= L ? L : 0;
-        return v >= L ? v % L : v;  // only lattices narrower than a tile wrap twice
-    };
-    uint32_t acc[4][kMaxShells][2];
-#pragma unroll
-    for (int k = 0; k < 4; ++k)
-#pragma unroll
-        for (int s = 0; s < kMaxShells; ++s) acc[k][s][0] = acc[k][s][1] = 0;
-    for (int64_t ti = t0; ti < t1; ++ti) {
-        const int tx = (int)(ti % ntx);
-        const int64_t tr = ti / ntx;
-        const int ty = (int)(tr % nty), tz = (int)(tr / nty);
-        const int x0 = tx * TX, y0 = ty * TY, z0 = tz * TZ;
-        __syncthreads();  // every lane is done with the previous tile
-        if constexpr (TX >= 64) {
-            // a wave per window row: its wrapped y, z and base address are
-            // wave-uniform, a lane wraps only its own x
-            const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-            for (int rr = wave; rr < WY * WZ; rr += kBlock / 64) {
-                const int wy = rr % WY, wz = rr / WY;
-                const int y = wrap(y0 + wy - kHalo, L1), z = wrap(z0 + wz - kHalo, L2);
-                const uint8_t* row = o + (int64_t)m * L0 * (y + (int64_t)L1 * z);
-                uint8_t* d = win + (wz * WY + wy) * LP;
-                for (int wx = lane; wx < WX; wx += 64) {
-                    const int x = wrap(x0 + wx - kHalo, L0);
-                    if constexpr (m == 2) *(uint16_t*)(d + 2 * wx) = *(const uint16_t*)(row + 2 * x);
-                    else *(uint32_t*)(d + 4 * wx) = *(const uint32_t*)(row + 4 * x);
-                }
-            }
-        } else {
-            for (int c = threadIdx.x; c < WX * WY * WZ; c += blockDim.x) {
-                const int wx = c % WX, wr = c / WX, wy = wr % WY, wz = wr / WY;
-                const int x = wrap(x0 + wx - kHalo, L0), y = wrap(y0 + wy - kHalo, L1), z = wrap(z0 + wz - kHalo, L2);
-                const int64_t cell = x + (int64_t)L0 * (y + (int64_t)L1 * z);
-                uint8_t* d = win + (wz * WY + wy) * LP + wx * m;
-                if constexpr (m == 2) *(uint16_t*)d = *(const uint16_t*)(o + 2 * cell);
-                else *(uint32_t*)d = *(const uint32_t*)(o + 4 * cell);
-            }
-        }
-        __syncthreads();
-        if (x0 + lx >= L0 || y0 + ly >= L1) continue;
-        for (int lz = 0; lz < TZ && z0 + lz < L2; ++lz) {
-#pragma unroll
-            for (int b = 0; b < m; ++b) {
-                const int base = ((lz + kHalo) * WY + (ly + kHalo)) * LP + (lx + kHalo) * m + b;
-                const int sig = win[base];
-#pragma unroll
-                for (int s = 0; s < kMaxShells; ++s) {
-                    if (s < S) {
-                        // one direction of every +-d pair: these half-shell
-                        // counts H give C[k][l] = H[k][l] + H[l][k] exactly
-                        constexpr int kHalfZ = kMaxZ / 2;
-                        uint32_t v[kHalfZ];
-#pragma unroll
-                        for (int n = 0; n < G.Z[s] / 2; ++n) {
-                            const Nb nb = nb_of(G, b, G.v[s][n][0], G.v[s][n][1], G.v[s][n][2]);
-                            v[n] = win[base + nb.dz * PL + nb.dy * LP + m * nb.dx + (nb.bt - b)];
-                        }
-                        uint32_t h = 0;
-#pragma unroll
-                        for (int n = 0; n < G.Z[s] / 2; ++n) h += 1u << (8 * v[n]);
-                        // 8-bit fields (<= 24 each) -> two words of 16-bit fields
-                        const uint32_t lo = (h & 0xFFu) | ((h & 0xFF00u) << 8);
-                        const uint32_t hi = ((h >> 16) & 0xFFu) | ((h >> 8) & 0xFF0000u);
-#pragma unroll
-                        for (int k = 0; k < 4; ++k) {
-                            acc[k][s][0] += sig == k ? lo : 0u;
-                            acc[k][s][1] += sig == k ? hi : 0u;
-                        }
-                    }
-                }
-            }
-        }
-    }
-    int64_t* C = counts + (int64_t)blockIdx.y * S * K * K;
-#pragma unroll
-    for (int s = 0; s < kMaxShells; ++s) {
-        if (s >= S) continue;
-        // the wave's half-shell counts H[k][l], then C[k][l] and C[l][k] each
-        // gain H[k][l] + H[l][k] in one atomic
-        uint32_t H[4][4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k)
-#pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                H[k][2 * j] = k < K ? wave_sum(acc[k][s][j] & 0xFFFFu) : 0u;
-                H[k][2 * j + 1] = k < K ? wave_sum(acc[k][s][j] >> 16) : 0u;
-            }
-        if ((threadIdx.x & 63) == 0) {
-#pragma unroll
-            for (int k = 0; k < 4; ++k)
-#pragma unroll
-                for (int l = k; l < 4; ++l) {
-                    const uint32_t c = H[k][l] + H[l][k];
-                    if (l >= K || c == 0) continue;
-                    atomicAdd((unsigned long long*)&C[(s * K + k) * K + l], (unsigned long long)c);
-                    if (l != k) atomicAdd((unsigned long long*)&C[(s * K + l) * K + k], (unsigned long long)c);
-                }
-        }
-    }
-}
-
-// ---------------------------------------------------------------------------
-// Pair counts of up to 5 species over slabs of whole x-rows: a workgroup owns
-// kSlabY consecutive rows (all of x) and a run of planes along z, and walks
-// the planes with a ring of 4 window planes in LDS: planes z .. z + 2 are
-// read while plane z + 3 comes in through registers.  Each site counts one
-// direction of every +-d pair, the one with d_z > 0 (or d_z = 0 and d_y > 0,
-// or d_z = d_y = 0 and d_x > 0), so its neighbours lie in planes z .. z + 2,
-// rows y - 2 .. y + 2 and cells x - 2 .. x + 2; as in the tiled kernel these
-// half-shell counts H give C[k][l] = H[k][l] + H[l][k].  Every byte of the
-// lattice is read (kSlabY + 4) / kSlabY times plus the ring's two extra planes
-// per run, instead of the tiles' 2-3x halo re-reads.  Planes come in by
-// LDS-direct loads while the previous plane is counted, then are scaled in
-// place to F * species, F = 8 for up to 4 species and 6 for 5 (a neighbour
-// costs one LDS byte read and one shift-add into F-bit fields, each at most
-// 12); a site's histogram goes into 16-bit fields of its species'
-// accumulators by 24-bit multiply-adds with a 0/1 factor.
-// ---------------------------------------------------------------------------
-constexpr int kSlabY = 8;
-constexpr int kSlabBlock = 512;
-
-// Positive half of shell s of a basis-b site as (dz, dy, dx, bt), in shell order.
-constexpr bool positive(const int (&v)[3]) { return v[2] > 0 || (v[2] == 0 && (v[1] > 0 || (v[1] == 0 && v[0] > 0))); }
-
-template <int LAT, int KF>
-__global__ __launch_bounds__(kSlabBlock) void k_pair_counts_slab(const uint8_t* occ, int64_t N, int L0, int L1, int L2,
-                                                               int K, int S, int ZC, int pitch, int64_t* counts)
-{
-    static_assert(KF == 4 || KF == 5, "up to 4 species in 8-bit fields, 5 in 6-bit fields");
-    constexpr int F = KF == 5 ? 6 : 8;  // field width of the site histograms
-    constexpr int NWD = (KF + 1) / 2;   // words of 16-bit fields per species accumulator
-    constexpr Geometry G = kGeom[LAT];
-    constexpr int m = G.m;
-    constexpr int NR = kSlabY + 4;
-    extern __shared__ __align__(16) uint8_t win[];  // 4 planes x NR rows x pitch
-    const int plane_bytes = NR * pitch;
-    const uint8_t* o = occ + (int64_t)blockIdx.z * N;
-    const int y0 = blockIdx.x * kSlabY;
-    const int z0 = blockIdx.y * ZC, z1 = min(z0 + ZC, L2);
-    const int rowd = (L0 * m) >> 2;  // dwords of a natural row
-    constexpr int hd = m / 2;        // dwords of a 2-cell halo
-    const int nd = rowd + 2 * hd;    // dwords of a window row: cells -2 .. L0 + 1
-    const int nitems = NR * nd;
-    auto wrap = [](int v, int L) {
-        v %= L;
-        return v < 0 ? v + L : v;
-    };
-    // plane z into ring slot `slot`: window row rr is natural row y0 - 2 + rr
-    // (wrapped), dword j of it the natural dword of cell 2 j / m - 2 (wrapped);
-    // copied straight into LDS, a wave per window row, 64 dwords per load
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    auto stage = [&](int z, int slot) {
-        const int zw = wrap(z, L2);
-        uint8_t* base = win + slot * plane_bytes;
-        for (int rr = wave; rr < NR; rr += kSlabBlock / 64) {
-            const int y = wrap(y0 - kHalo + rr, L1);
-            const uint32_t* row = (const uint32_t*)(o + (int64_t)m * L0 * (y + (int64_t)L1 * zw));
-            for (int cb = 0; cb < nd; cb += 64) {
-                const int j = cb + lane;
-                if (j < nd) {
-                    const int jj = j < hd ? rowd - hd + j : (j < hd + rowd ? j - hd : j - hd - rowd);
-                    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(row + jj),
-                                                     (__attribute__((address_space(3))) void*)(base + rr * pitch + 4 * cb),
-                                                     4, 0, 0);
-                }
-            }
-        }
-    };
-    // species -> F * species in place (F * species <= 24: no byte overflows
-    // into the next)
-    auto scale = [&](int slot) {
-        uint8_t* base = win + slot * plane_bytes;
-        for (int i = threadIdx.x; i < nitems; i += kSlabBlock) {
-            const int rr = i / nd, j = i - rr * nd;
-            uint32_t* w = (uint32_t*)(base + rr * pitch + 4 * j);
-            *w = F == 8 ? *w << 3 : *w * 6u;
-        }
-    };
-    // accumulators [species][shell][word] with 16-bit fields: for F = 8, word 0
-    // holds l = 0 and 2, word 1 l = 1 and 3; for F = 6, word w holds l = 2 w
-    // and 2 w + 1
-    uint32_t acc[KF][kMaxShells][NWD];
-#pragma unroll
-    for (int k = 0; k < KF; ++k)
-#pragma unroll
-        for (int s = 0; s < kMaxShells; ++s)
-#pragma unroll
-            for (int w = 0; w < NWD; ++w) acc[k][s][w] = 0;
-    stage(z0, 0);
-    stage(z0 + 1, 1);
-    stage(z0 + 2, 2);
-    __builtin_amdgcn_s_waitcnt(0);
-    __syncthreads();
-    scale(0);
-    scale(1);
-    scale(2);
-    __syncthreads();
-    const int ny = min(kSlabY, L1 - y0);
-    const int ncells = ny * L0;
-    for (int z = z0; z < z1; ++z) {
-        const bool more = z + 3 < z1 + 2;  // planes up to z1 + 1 are read
-        const int sl = z - z0;
-        if (more) stage(z + 3, (sl + 3) & 3);  // in flight while plane z is counted
-        const int pb0 = ((sl + 0) & 3) * plane_bytes, pb1 = ((sl + 1) & 3) * plane_bytes,
-                  pb2 = ((sl + 2) & 3) * plane_bytes;
-        int ly = threadIdx.x / L0, x = threadIdx.x - ly * L0;
-        const int dly = kSlabBlock / L0, dx = kSlabBlock - dly * L0;
-        for (int c = threadIdx.x; c < ncells; c += kSlabBlock) {
-            const int cell = (ly + kHalo) * pitch + (x + kHalo) * m;
-#pragma unroll
-            for (int b = 0; b < m; ++b) {
-                const int k8 = win[pb0 + cell + b];
-                uint32_t e[KF];
-#pragma unroll
-                for (int kk = 0; kk < KF; ++kk) e[kk] = k8 == F * kk ? 1u : 0u;
-#pragma unroll
-                for (int s = 0; s < kMaxShells; ++s) {
-                    if (s < S) {
-                        uint32_t h = 0;
-#pragma unroll
-                        for (int n = 0; n < G.Z[s]; ++n) {
-                            if (!positive(G.v[s][n])) continue;
-                            const Nb nb = nb_of(G, b, G.v[s][n][0], G.v[s][n][1], G.v[s][n][2]);
-                            const int pbz = nb.dz == 0 ? pb0 : (nb.dz == 1 ? pb1 : pb2);
-                            h = shl1_add(win[pbz + cell + nb.dy * pitch + nb.dx * m + nb.bt], h);
-                        }
-                        // F-bit fields (<= 12 each) -> words of 16-bit fields
-                        uint32_t wd[NWD];
-                        if constexpr (F == 8) {
-                            wd[0] = h & 0x00FF00FFu;
-                            wd[1] = (h >> 8) & 0x00FF00FFu;
-                        } else {
-#pragma unroll
-                            for (int w = 0; w < NWD; ++w)
-                                wd[w] = ((h >> (12 * w)) & 0x3Fu) | (((h >> (12 * w + 6)) & 0x3Fu) << 16);
-                        }
-#pragma unroll
-                        for (int kk = 0; kk < KF; ++kk)
-#pragma unroll
-                            for (int w = 0; w < NWD; ++w) acc[kk][s][w] = __umul24(wd[w], e[kk]) + acc[kk][s][w];
-                    }
-                }
-                // one site's reads at a time: registers for two workgroups per CU
-                __builtin_amdgcn_sched_barrier(0);
-            }
-            ly += dly;
-            x += dx;
-            if (x >= L0) {
-                x -= L0;
-                ++ly;
-            }
-        }
-        if (more) {
-            __builtin_amdgcn_s_waitcnt(0);
-            __syncthreads();
-            scale((sl + 3) & 3);
-        }
-        __syncthreads();
-    }
-    // wave sums of H[s][k][l] into LDS (the window is free after the last
-    // barrier), the workgroup's totals, then one atomic per directed count:
-    // a few dozen atomics per workgroup instead of that many per wave
-    constexpr int NW = kSlabBlock / 64;
-    constexpr int KK = KF * KF;                  // H[k][l] entries of one shell
-    uint32_t* red = (uint32_t*)win;              // [NW][kMaxShells][KK]
-    uint32_t* tot = red + NW * kMaxShells * KK;  // [kMaxShells][KK]
-#pragma unroll
-    for (int s = 0; s < kMaxShells; ++s) {
-#pragma unroll
-        for (int k = 0; k < KF; ++k) {
-#pragma unroll
-            for (int l = 0; l < KF; ++l) {
-                // field of l: F = 8 words hold (0, 2) and (1, 3); F = 6 words (2w, 2w + 1)
-                const int w = F == 8 ? (l & 1) : l >> 1, hi = F == 8 ? l >> 1 : l & 1;
-                const uint32_t h = wave_sum(hi ? acc[k][s][w] >> 16 : acc[k][s][w] & 0xFFFFu);
-                if (lane == 0) red[(wave * kMaxShells + s) * KK + k * KF + l] = h;
-            }
-        }
-    }
-    __syncthreads();
-    if (threadIdx.x < kMaxShells * KK) {
-        uint32_t v = 0;
-        for (int w = 0; w < NW; ++w) v += red[w * kMaxShells * KK + threadIdx.x];
-        tot[threadIdx.x] = v;
-    }
-    __syncthreads();
-    if (threadIdx.x < kMaxShells * KK) {
-        const int s = threadIdx.x / KK, k = (threadIdx.x % KK) / KF, l = threadIdx.x % KF;
-        if (s < S && k < K && l < K) {
-            const uint32_t c = tot[s * KK + KF * k + l] + tot[s * KK + KF * l + k];
-            if (c != 0)
-                atomicAdd((unsigned long long*)&counts[(int64_t)blockIdx.z * S * K * K + (s * K + k) * K + l],
-                          (unsigned long long)c);
-        }
-    }
-}
-
-// ---------------------------------------------------------------------------
 // Host-side launchers
 // ---------------------------------------------------------------------------
 // ---------------------------------------------------------------------------
@@ -2552,88 +2134,6 @@ hipError_t launch_fill_i32(int32_t* p, int64_t n, int32_t v, hipStream_t st)
 hipError_t launch_advance_counter(uint32_t* counter, uint32_t n, hipStream_t st)
 {
     hipLaunchKernelGGL(k_advance_counter, dim3(1), dim3(64), 0, st, counter, n);
-    return hipGetLastError();
-}
-
-hipError_t launch_pair_counts(int lattice, int K, int S, const uint8_t* occ, int64_t N, const int32_t* L,
-                              int B, int64_t* counts, hipStream_t st)
-{
-    const int mm = lattice == SMCX_BCC ? 2 : 4;
-    const int nd = (L[0] * mm) / 4 + mm;  // window dwords per row of the slab kernel
-    const int slab_lds = 4 * (kSlabY + 4) * ((4 * nd + 15) & ~15);
-    if (K <= 5 && L[0] >= 48 && (L[0] * mm) % 4 == 0 && slab_lds <= 80 * 1024) {
-        // slabs of kSlabY whole rows; runs of ZC planes, enough runs for ~2048
-        // workgroups, and few enough sites per thread that every 16-bit field
-        // stays exact (a site adds at most 12 to a field)
-        const int pitch = (4 * nd + 15) & ~15;
-        const int ny = (L[1] + kSlabY - 1) / kSlabY;
-        const int per_thread = (kSlabY * L[0] + kSlabBlock - 1) / kSlabBlock * mm;  // sites per plane
-        const int zc_max = std::max(1, 5000 / per_thread);
-        // ~2048 workgroups for large batches, fewer (about 16k sites each)
-        // for small ones, whose cost would otherwise be staging and flushes
-        const int64_t want = std::min<int64_t>(2048, std::max<int64_t>(1, (int64_t)B * N / 16384));
-        int64_t runs = std::max<int64_t>(1, (want + (int64_t)ny * B - 1) / ((int64_t)ny * B));
-        int zc = (int)std::min<int64_t>(L[2], std::max<int64_t>(1, (L[2] + runs - 1) / runs));
-        zc = std::min(zc, zc_max);
-        const int nz = (L[2] + zc - 1) / zc;
-        if (B > 65535) return hipErrorInvalidValue;
-        // the window, which also holds the final reduction: a row of
-        // kMaxShells x KF^2 words per wave and one of totals
-        const int kf = K <= 4 ? 4 : 5;
-        const size_t red = (size_t)(kSlabBlock / 64 + 1) * kMaxShells * kf * kf * 4;
-        const size_t lds = std::max<size_t>((size_t)4 * (kSlabY + 4) * pitch, red);
-        const dim3 g((unsigned)ny, (unsigned)nz, (unsigned)B), b(kSlabBlock);
-        auto go = [&](const void* kern) {
-            (void)hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-            void* args[] = {(void*)&occ, (void*)&N, (void*)&L[0], (void*)&L[1], (void*)&L[2], (void*)&K, (void*)&S,
-                            (void*)&zc, (void*)&pitch, (void*)&counts};
-            return hipLaunchKernel(kern, g, b, args, lds, st);
-        };
-        hipError_t e;
-        if (lattice == SMCX_BCC)
-            e = go(kf == 4 ? (const void*)k_pair_counts_slab<SMCX_BCC, 4> : (const void*)k_pair_counts_slab<SMCX_BCC, 5>);
-        else
-            e = go(kf == 4 ? (const void*)k_pair_counts_slab<SMCX_FCC, 4> : (const void*)k_pair_counts_slab<SMCX_FCC, 5>);
-        if (e != hipSuccess) return e;
-        return hipGetLastError();
-    }
-    if (K <= 4) {
-        // lanes 64 x 4 cells (16 x 16 for narrow lattices), 16 cells deep;
-        // at most 2048 sites per lane between flushes keeps every 16-bit
-        // field exact (a site adds at most 24 to a field)
-        const int m = lattice == SMCX_BCC ? 2 : 4;
-        const bool wide = L[0] >= 48;
-        const int TX = wide ? 64 : 16, TY = kBlock / TX;
-        const int64_t ntiles = (int64_t)((L[0] + TX - 1) / TX) * ((L[1] + TY - 1) / TY) * ((L[2] + 15) / 16);
-        // up to 2048 / (16 m) tiles per workgroup, fewer when the batch has
-        // too few tiles to give the chip ~2048 workgroups
-        const int64_t tpb_max = 2048 / (m * 16);
-        const int tpb = (int)std::max<int64_t>(1, std::min<int64_t>(tpb_max, (ntiles * B + 2047) / 2048));
-        const int64_t nbx = (ntiles + tpb - 1) / tpb;
-        if (nbx > 0x7fffffff || B > 65535) return hipErrorInvalidValue;
-        const dim3 g((unsigned)nbx, (unsigned)B), b(kBlock);
-        auto go = [&](auto kern) { hipLaunchKernelGGL(kern, g, b, 0, st, occ, N, L[0], L[1], L[2], K, S, tpb, counts); };
-        if (lattice == SMCX_BCC) {
-            if (wide) go(k_pair_counts_tiled<SMCX_BCC, 64>); else go(k_pair_counts_tiled<SMCX_BCC, 16>);
-        } else {
-            if (wide) go(k_pair_counts_tiled<SMCX_FCC, 64>); else go(k_pair_counts_tiled<SMCX_FCC, 16>);
-        }
-        return hipGetLastError();
-    }
-    const int64_t ncell = (int64_t)L[0] * L[1] * L[2];
-    // <= 2048 sites per lane between flushes keeps the 16-bit fields exact
-    const int m = lattice == SMCX_BCC ? 2 : 4;
-    const int cells_per_block = kBlock * (2048 / (m * 4));
-    const int64_t nbx = (ncell + cells_per_block - 1) / cells_per_block;
-    if (nbx > 0x7fffffff || B > 65535) return hipErrorInvalidValue;
-    const dim3 g((unsigned)nbx, (unsigned)B), b(kBlock);
-    if (lattice == SMCX_BCC) {
-        if (K <= 4) hipLaunchKernelGGL((k_pair_counts<SMCX_BCC, 4>), g, b, 0, st, occ, N, L[0], L[1], L[2], K, S, cells_per_block, counts);
-        else hipLaunchKernelGGL((k_pair_counts<SMCX_BCC, 8>), g, b, 0, st, occ, N, L[0], L[1], L[2], K, S, cells_per_block, counts);
-    } else {
-        if (K <= 4) hipLaunchKernelGGL((k_pair_counts<SMCX_FCC, 4>), g, b, 0, st, occ, N, L[0], L[1], L[2], K, S, cells_per_block, counts);
-        else hipLaunchKernelGGL((k_pair_counts<SMCX_FCC, 8>), g, b, 0, st, occ, N, L[0], L[1], L[2], K, S, cells_per_block, counts);
-    }
     return hipGetLastError();
 }
 
