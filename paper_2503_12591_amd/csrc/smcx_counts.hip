@@ -362,7 +362,9 @@ __global__ __launch_bounds__(kBitBlock) void k_pair_bits(const uint8_t* occ, int
             for (int j = 0; j < K; ++j)
                 if (j != k) c -= pair(k, j);
         }
-        if (c) atomicAdd((unsigned long long*)&counts[(int64_t)blockIdx.y * S * K * K + i], (unsigned long long)c);
+        // like pairs of one workgroup's sites may come out negative (its bonds
+        // reach into other workgroups' sites): only their sum is a count
+        if (c) atomicAdd((unsigned long long*)&counts[(int64_t)blockIdx.y * S * K * K + i], (unsigned long long)(int64_t)(int32_t)c);
     }
 }
 
@@ -415,7 +417,7 @@ hipError_t launch_pair_counts(int lattice, int K, int S, const uint8_t* occ, int
     if (tiles > 0x7fffffff) return hipErrorInvalidValue;
     T.tiles = (int)tiles;
     // up to about 1536 workgroups for the batch, each over several tiles; a
-    // workgroup's 32-bit counts hold 2^32 / 24 sites
+    // workgroup's signed 32-bit counts hold 2^31 / 24 sites
     int64_t gx = std::max<int64_t>(1, std::min<int64_t>(tiles, 1536 / B));
     gx = std::max(gx, std::min<int64_t>(tiles, N / (1 << 26) + 1));
     const int NU = KT * (KT - 1) / 2, NV = kMaxShells * NU + KT;

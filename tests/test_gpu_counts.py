@@ -46,6 +46,19 @@ def test_counts(smcx, lattice, dims, K, S, B):
         assert np.all(total == N * (8 if lattice == BCC else 12))
 
 
+@pytest.mark.parametrize("lattice,dims,K,axis,width", [(BCC, (40, 48, 64), 4, 2, 8), (FCC, (40, 48, 32), 5, 2, 1),
+                                                       (BCC, (96, 64, 32), 6, 1, 4), (FCC, (64, 64, 64), 3, 0, 32)])
+def test_counts_of_layers(smcx, lattice, dims, K, axis, width):
+    """Layers of one species: a workgroup may own bonds of a species it has no site of."""
+    import torch
+    m = 2 if lattice == BCC else 4
+    say(f"counts of layers lattice={lattice} dims={dims} K={K}")
+    pos = np.indices(dims[::-1])[2 - axis]  # z, y, x order
+    occ = np.repeat(((pos // width) % K).astype(np.uint8).reshape(-1), m)
+    C = smcx.energy_backward_counts(lattice, dims, K, 4, torch.from_numpy(occ[None]).cuda()).cpu().numpy()
+    assert np.array_equal(C[0], O.pair_counts(lattice, dims, K, 4, occ))
+
+
 @pytest.mark.parametrize("K", [2, 3, 4, 5, 7, 8])
 def test_species_check(smcx, K):
     import torch
