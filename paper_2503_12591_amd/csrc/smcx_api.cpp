@@ -713,12 +713,17 @@ int pack_all(smcx_lattice* h, bool unpack, bool planar, int64_t* stats_dev, hipS
         // every replica in one launch (a ladder's replicas are small: one
         // launch each would cost more than their copies)
         int64_t most = 0;
-        for (const Replica& R : P.reps) most = std::max(most, rows_of(R));
-        SMCX_HIP(launch_pack(P.lattice, P.K, unpack, planar, h->occ, h->ws, reps, -1, most, P.R, slots, parts, stats_dev, st));
+        int row16 = 1;
+        for (const Replica& R : P.reps) {
+            most = std::max(most, rows_of(R));
+            row16 = std::max(row16, R.cp / 16);
+        }
+        SMCX_HIP(launch_pack(P.lattice, P.K, unpack, planar, h->occ, h->ws, reps, -1, most, row16, P.R, slots, parts, stats_dev, st));
         return SMCX_OK;
     }
     for (int r = 0; r < P.R; ++r)
-        SMCX_HIP(launch_pack(P.lattice, P.K, unpack, planar, h->occ, h->ws, reps, r, rows_of(P.reps[r]), 1, slots, parts, stats_dev, st));
+        SMCX_HIP(launch_pack(P.lattice, P.K, unpack, planar, h->occ, h->ws, reps, r, rows_of(P.reps[r]), P.reps[r].cp / 16, 1,
+                             slots, parts, stats_dev, st));
     return SMCX_OK;
 }
 

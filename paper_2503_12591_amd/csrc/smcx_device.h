@@ -490,11 +490,12 @@ __device__ __forceinline__ void lds_barrier()
 // The replica table is read-only during a launch: reading it through the
 // constant address space (with a wave-uniform index) lets the compiler use
 // scalar loads instead of per-lane ones.
-__device__ __forceinline__ const RepDev& rep_of(const SweepArgs& A, int r)
+__device__ __forceinline__ const RepDev& rep_at(const RepDev* reps, int r)
 {
     using CRep = const __attribute__((address_space(4))) RepDev;
-    return *(const RepDev*)((CRep*)A.reps + r);
+    return *(const RepDev*)((CRep*)reps + r);
 }
+__device__ __forceinline__ const RepDev& rep_of(const SweepArgs& A, int r) { return rep_at(A.reps, r); }
 
 // Same for other tables a launch only reads (tile prefix sums, betas).
 template <typename T>

@@ -951,216 +951,200 @@ __global__ void k_advance_counter(uint32_t* counter, uint32_t n)
     if (blockIdx.x == 0 && threadIdx.x == 0) *counter += n;
 }
 
-// Natural layout -> padded copy.  A workgroup fills whole padded rows
-// (halo rows and columns included: each padded row is the natural row at the
-// wrapped y, z, each byte the site at the wrapped x), a thread one dword of
-// the row at a time; bytes past a column's L0 + 2H sites stay 0.
-// One word of a padded row byte by byte (halo columns wrap to the far side).
-template <int M, bool PLANAR>
-__device__ __forceinline__ uint32_t pack_word(const RepDev& rep, const uint8_t* src, int w, int L0, int F)
+// Natural layout <-> padded copy.
+//
+// Basis-planar rows: a thread takes 16 padded bytes of every basis column of a
+// row, cells x0 = 16 j - H .. x0 + 15, which lie next to each other in the
+// natural row (16 M bytes, at any alignment): M wide loads, a byte transpose
+// in registers, M wide stores, the other way round to unpack.  Chunks that
+// reach past a face go byte by byte.  Bound by memory: BCC 800^3 packs in
+// 641 us and unpacks in 454 us (2.1 GB each); word loads at a
+// 32-byte stride, a fifth of whose lines are used at a time, took 1110 and
+// 780 us.
+constexpr int kPackCells = 16;
+
+// d[4 i .. 4 i + 3], i < M: 16 cells of M bytes; c[b][0 .. 3]: 16 bytes of column b.
+template <int M>
+__device__ __forceinline__ void to_columns(const uint32_t (&d)[4 * M], uint32_t (&c)[M][4])
 {
-    uint32_t v = 0;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int j = 4 * w + i;
-        const int b = PLANAR ? j / rep.cp : j % M;
-        int x = (PLANAR ? j - b * rep.cp : j / M) - kHalo;
-        if (b < M && x < L0 + kHalo) {
-            x += x < 0 ? L0 : (x >= L0 ? -L0 : 0);
-            v |= (uint32_t)(src[M * x + b] * F) << (8 * i);
+    for (int w = 0; w < 4; ++w) {
+        if constexpr (M == 2) {
+            c[0][w] = __builtin_amdgcn_perm(d[2 * w + 1], d[2 * w], 0x06040200u);
+            c[1][w] = __builtin_amdgcn_perm(d[2 * w + 1], d[2 * w], 0x07050301u);
+        } else {
+            const uint32_t *q = d + 4 * w;  // four cells
+            const uint32_t t0 = __builtin_amdgcn_perm(q[1], q[0], 0x05010400u), t1 = __builtin_amdgcn_perm(q[3], q[2], 0x05010400u);
+            const uint32_t t2 = __builtin_amdgcn_perm(q[1], q[0], 0x07030602u), t3 = __builtin_amdgcn_perm(q[3], q[2], 0x07030602u);
+            c[0][w] = __builtin_amdgcn_perm(t1, t0, 0x05040100u);
+            c[1][w] = __builtin_amdgcn_perm(t1, t0, 0x07060302u);
+            c[2][w] = __builtin_amdgcn_perm(t3, t2, 0x05040100u);
+            c[3][w] = __builtin_amdgcn_perm(t3, t2, 0x07060302u);
         }
     }
-    return v;
+}
+template <int M>
+__device__ __forceinline__ void to_cells(const uint32_t (&c)[M][4], uint32_t (&d)[4 * M])
+{
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+        if constexpr (M == 2) {
+            d[2 * w] = __builtin_amdgcn_perm(c[1][w], c[0][w], 0x05010400u);
+            d[2 * w + 1] = __builtin_amdgcn_perm(c[1][w], c[0][w], 0x07030602u);
+        } else {
+            const uint32_t t0 = __builtin_amdgcn_perm(c[1][w], c[0][w], 0x05010400u), t1 = __builtin_amdgcn_perm(c[3][w], c[2][w], 0x05010400u);
+            const uint32_t t2 = __builtin_amdgcn_perm(c[1][w], c[0][w], 0x07030602u), t3 = __builtin_amdgcn_perm(c[3][w], c[2][w], 0x07030602u);
+            d[4 * w] = __builtin_amdgcn_perm(t1, t0, 0x05040100u);
+            d[4 * w + 1] = __builtin_amdgcn_perm(t1, t0, 0x07060302u);
+            d[4 * w + 2] = __builtin_amdgcn_perm(t3, t2, 0x05040100u);
+            d[4 * w + 3] = __builtin_amdgcn_perm(t3, t2, 0x07060302u);
+        }
+    }
 }
 
 template <int M, bool PLANAR>
-__global__ void k_pack(const uint8_t* occ, uint8_t* ws, const RepDev* reps, int r, int F)
+__global__ __launch_bounds__(kBlock) void k_pack(const uint8_t* occ, uint8_t* ws, const RepDev* reps, int r, int F)
 {
-    const RepDev& rep = reps[r < 0 ? (int)blockIdx.y : r];  // r < 0: one replica per grid row
+    const RepDev& rep = rep_at(reps, r < 0 ? (int)blockIdx.y : r);  // r < 0: one replica per grid row
     uint8_t* pad = ws + rep.pad_off;
     const uint8_t* o = occ + rep.occ_off;
     const int L0 = rep.L[0], L1 = rep.L[1], L2 = rep.L[2];
-    const int pitch = PLANAR ? rep.prowp : rep.prow;
     const int nrow = rep.prows * (L2 + 2 * kHalo);
-    const int words = pitch >> 2;
-    if (M == 2 && PLANAR && (rep.cp >> 4) <= (int)blockDim.x) {
-        // Two basis sites, planar rows of 16-byte aligned columns: a thread
-        // takes 16 cells of a row (x0 = 16 j - 2 .. x0 + 15, 32 natural bytes
-        // read once as 8 aligned words, or 9 shifted by 2 bytes when the row
-        // starts 2 bytes past a word boundary) and writes both basis columns'
-        // 16 bytes with one store each; blocks that wrap or pass the row's
-        // end, and the bytes past the two columns, go word by word
-        const int nblk = rep.cp >> 4, tail0 = 2 * (rep.cp >> 2);
-        const int rows_per = (int)blockDim.x / nblk;  // at least one row per pass
-        const int lr = (int)threadIdx.x / nblk, j = (int)threadIdx.x - lr * nblk;
-        for (int row0 = blockIdx.x * rows_per; row0 < nrow; row0 += gridDim.x * rows_per) {
-            const int row = row0 + lr;
-            if (lr < rows_per && row < nrow) {
-                const int yp = row % rep.prows, zp = row / rep.prows;
-                int y = yp - kHalo, z = zp - kHalo;
-                y += y < 0 ? L1 : (y >= L1 ? -L1 : 0);
-                z += z < 0 ? L2 : (z >= L2 ? -L2 : 0);
-                const uint8_t* src = o + (int64_t)M * L0 * (y + (int64_t)L1 * z);
-                uint32_t* dst = (uint32_t*)(pad + (int64_t)row * pitch);
-                const int sh = (int)((uintptr_t)src & 3);  // 0 or 2
-                const int x0 = 16 * j - kHalo;
-                if (x0 >= 0 && x0 + 16 + (sh >> 1) <= L0) {
-                    const uint32_t* s32 = (const uint32_t*)(src + 2 * x0 - sh);
-                    uint32_t d[9];
-#pragma unroll
-                    for (int i = 0; i < 8; ++i) d[i] = s32[i];
-                    if (sh) {
-                        d[8] = s32[8];
-#pragma unroll
-                        for (int i = 0; i < 8; ++i) d[i] = __builtin_amdgcn_alignbyte(d[i + 1], d[i], (uint32_t)sh);
-                    }
-#pragma unroll
-                    for (int b = 0; b < 2; ++b) {
-                        uint4 v;
-                        v.x = __builtin_amdgcn_perm(d[1], d[0], b ? 0x07050301u : 0x06040200u) * (uint32_t)F;
-                        v.y = __builtin_amdgcn_perm(d[3], d[2], b ? 0x07050301u : 0x06040200u) * (uint32_t)F;
-                        v.z = __builtin_amdgcn_perm(d[5], d[4], b ? 0x07050301u : 0x06040200u) * (uint32_t)F;
-                        v.w = __builtin_amdgcn_perm(d[7], d[6], b ? 0x07050301u : 0x06040200u) * (uint32_t)F;
-                        *(uint4*)(dst + b * (rep.cp >> 2) + 4 * j) = v;
-                    }
-                } else {
-#pragma unroll
-                    for (int b = 0; b < 2; ++b)
-#pragma unroll
-                        for (int t = 0; t < 4; ++t) {
-                            const int w = b * (rep.cp >> 2) + 4 * j + t;
-                            dst[w] = pack_word<M, PLANAR>(rep, src, w, L0, F);
-                        }
-                }
-                if (j == 0)
-                    for (int w = tail0; w < words; ++w) dst[w] = 0u;
-            }
-        }
-        return;
-    }
-    for (int row = blockIdx.x; row < nrow; row += gridDim.x) {
-        const int yp = row % rep.prows, zp = row / rep.prows;
+    // padded row -> the natural row at its wrapped y, z
+    auto source = [&](int row) {
+        const int zp = row / rep.prows, yp = row - zp * rep.prows;
         int y = yp - kHalo, z = zp - kHalo;
         y += y < 0 ? L1 : (y >= L1 ? -L1 : 0);
         z += z < 0 ? L2 : (z >= L2 ? -L2 : 0);
-        const uint8_t* src = o + (int64_t)M * L0 * (y + (int64_t)L1 * z);
-        uint32_t* dst = (uint32_t*)(pad + (int64_t)row * pitch);
-        // two basis sites, planar rows: a word of basis b at x .. x + 3 (no
-        // wrap) is bytes b, b + 2, b + 4, b + 6 of the natural row from 2 x,
-        // two natural words (or, in a row that starts 2 bytes past a word
-        // boundary -- odd L0 -- three aligned words shifted by 2 bytes), and
-        // times F byte by byte (every F * species < 256, so no carry crosses
-        // a byte)
-        const int sh = (int)((uintptr_t)src & 3);  // 0 or 2: natural rows hold an even number of bytes
-        const bool fast = M == 2 && PLANAR && (sh & 1) == 0;
-        const int cpw = rep.cp >> 2;
-        for (int w = threadIdx.x; w < words; w += blockDim.x) {
-            if (fast) {
-                const int b = w >= cpw ? 1 : 0;
-                const int xw = 4 * (w - b * cpw) - kHalo;
-                // every byte read lies in this natural row
-                if (xw >= 0 && xw + 3 + (sh >> 1) < L0) {
-                    const uint32_t* s32 = (const uint32_t*)(src + 2 * xw - sh);
-                    uint32_t lo = s32[0], hi = s32[1];
-                    if (sh) {
-                        const uint32_t h2 = s32[2];
-                        lo = __builtin_amdgcn_alignbyte(hi, lo, (uint32_t)sh);
-                        hi = __builtin_amdgcn_alignbyte(h2, hi, (uint32_t)sh);
+        return o + (int64_t)M * L0 * (y + (int64_t)L1 * z);
+    };
+    if constexpr (PLANAR) {
+        const int nblk = rep.cp >> 4;
+        const int64_t total = (int64_t)nrow * nblk;
+        for (int64_t i = blockIdx.x * (int64_t)kBlock + threadIdx.x; i < total; i += (int64_t)gridDim.x * kBlock) {
+            const int row = total < (1ll << 31) ? (int)((uint32_t)i / (uint32_t)nblk) : (int)(i / nblk);
+            const int j = (int)(i - (int64_t)row * nblk), x0 = kPackCells * j - kHalo;
+            const uint8_t* src = source(row);
+            uint32_t d[4 * M], c[M][4];
+            if (x0 >= 0 && x0 + kPackCells <= L0) {
+                __builtin_memcpy(d, src + M * x0, 16 * M);
+                to_columns<M>(d, c);
+            } else {
+#pragma unroll
+                for (int b = 0; b < M; ++b)
+#pragma unroll
+                    for (int w = 0; w < 4; ++w) {
+                        c[b][w] = 0;
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) {
+                            int x = x0 + 4 * w + k;  // bytes past the halo stay 0
+                            if (x < L0 + kHalo) {
+                                x += x < 0 ? L0 : (x >= L0 ? -L0 : 0);
+                                c[b][w] |= (uint32_t)src[M * x + b] << (8 * k);
+                            }
+                        }
                     }
-                    const uint32_t v = __builtin_amdgcn_perm(hi, lo, b ? 0x07050301u : 0x06040200u);
-                    dst[w] = v * (uint32_t)F;
-                    continue;
-                }
             }
-            dst[w] = pack_word<M, PLANAR>(rep, src, w, L0, F);
+            uint8_t* dst = pad + (int64_t)row * rep.prowp + 16 * j;
+#pragma unroll
+            for (int b = 0; b < M; ++b) {
+                uint4 v;  // F * species < 256: no carry crosses a byte
+                v.x = c[b][0] * (uint32_t)F;
+                v.y = c[b][1] * (uint32_t)F;
+                v.z = c[b][2] * (uint32_t)F;
+                v.w = c[b][3] * (uint32_t)F;
+                *(uint4*)(dst + b * rep.cp) = v;
+            }
+        }
+    } else {
+        // interleaved rows: a workgroup per row, a thread one word of it at a
+        // time; bytes past the row's M (L0 + 2H) sites stay 0
+        const int words = rep.prow >> 2;
+        for (int row = blockIdx.x; row < nrow; row += gridDim.x) {
+            const uint8_t* src = source(row);
+            uint32_t* dst = (uint32_t*)(pad + (int64_t)row * rep.prow);
+            for (int w = threadIdx.x; w < words; w += blockDim.x) {
+                uint32_t v = 0;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int j = 4 * w + i, b = j % M;
+                    int x = j / M - kHalo;
+                    if (x < L0 + kHalo) {
+                        x += x < 0 ? L0 : (x >= L0 ? -L0 : 0);
+                        v |= (uint32_t)(src[M * x + b] * F) << (8 * i);
+                    }
+                }
+                dst[w] = v;
+            }
         }
     }
 }
 
-// Padded copy interior -> natural layout: a workgroup per natural row, a
-// thread per site byte.
+// Four species from their stored form F * species: v / 6 = ((v / 2) 11) / 32
+// for v in 0, 6, .. 24, and no product leaves its byte.
+__device__ __forceinline__ uint32_t species_of4(uint32_t v, int F)
+{
+    return F == 8 ? (v >> 3) & 0x1F1F1F1Fu : ((((v >> 1) & 0x0F0F0F0Fu) * 11u) >> 5) & 0x07070707u;
+}
+
 template <int M, bool PLANAR>
-__global__ void k_unpack(uint8_t* occ, const uint8_t* ws, const RepDev* reps, int r, int F, int64_t* slots, int parts,
-                         int64_t* stats)
+__global__ __launch_bounds__(kBlock) void k_unpack(uint8_t* occ, const uint8_t* ws, const RepDev* reps, int r, int F,
+                                                   int64_t* slots, int parts, int64_t* stats)
 {
     const int ri = r < 0 ? (int)blockIdx.y : r;  // r < 0: one replica per grid row
-    if (blockIdx.x == 0 && threadIdx.x < 3) {
-        // the sweep launches' counter slots, added up and cleared
-        int64_t* s = slots + (int64_t)ri * parts * kStatStride + threadIdx.x;
-        int64_t v = 0;
-        for (int i = 0; i < parts; ++i) {
-            v += s[i * kStatStride];
-            s[i * kStatStride] = 0;
+    if (blockIdx.x == 0 && threadIdx.x < 64) {
+        // the sweep launches' counter slots (at most 64), added up and cleared
+        for (int k = 0; k < 3; ++k) {
+            int64_t* s = slots + ((int64_t)ri * parts + threadIdx.x) * kStatStride + k;
+            int64_t v = 0;
+            if ((int)threadIdx.x < parts) {
+                v = *s;
+                *s = 0;
+            }
+#pragma unroll
+            for (int d = 32; d > 0; d >>= 1) v += __shfl_xor(v, d, 64);
+            if (threadIdx.x == 0) stats[3 * (int64_t)ri + k] += v;
         }
-        stats[3 * (int64_t)ri + threadIdx.x] += v;
     }
-    const RepDev& rep = reps[ri];
+    const RepDev& rep = rep_at(reps, ri);
     const uint8_t* pad = ws + rep.pad_off;
     uint8_t* o = occ + rep.occ_off;
     const int L0 = rep.L[0], L1 = rep.L[1], L2 = rep.L[2];
-    const int pitch = PLANAR ? rep.prowp : rep.prow;
-    const int n = M * L0;
-    for (int row = blockIdx.x; row < L1 * L2; row += gridDim.x) {
-        const int y = row % L1, z = row / L1;
-        const uint8_t* src = pad + ((int64_t)(z + kHalo) * rep.prows + (y + kHalo)) * pitch;
-        uint8_t* dst = o + (int64_t)n * row;
-        // two basis sites, planar rows, F = 8, rows of a whole number of
-        // words: natural word w (x = 2w, 2w + 1, both basis sites)
-        // interleaves two bytes of each basis column, taken from the aligned
-        // word holding them (x + H is even, so the pair never straddles one)
-        if (M == 2 && PLANAR && F == 8 && (n & 3) == 0 && ((uintptr_t)dst & 3) == 0 && ((uintptr_t)src & 3) == 0) {
-            uint32_t* d32 = (uint32_t*)dst;
-            const int nw = n >> 2;
-            // a thread's two words load before either is stored
-            for (int w0 = threadIdx.x; w0 < nw; w0 += 2 * blockDim.x) {
-                uint32_t a[2] = {0u, 0u}, bb[2] = {0u, 0u};
+    if constexpr (PLANAR) {
+        const int nblk = (L0 + kHalo + kPackCells - 1) / kPackCells;  // chunks with an interior cell
+        const int64_t total = (int64_t)L1 * L2 * nblk;
+        for (int64_t i = blockIdx.x * (int64_t)kBlock + threadIdx.x; i < total; i += (int64_t)gridDim.x * kBlock) {
+            const int row = total < (1ll << 31) ? (int)((uint32_t)i / (uint32_t)nblk) : (int)(i / nblk);
+            const int j = (int)(i - (int64_t)row * nblk), x0 = kPackCells * j - kHalo;
+            const int z = row / L1, y = row - z * L1;
+            const uint8_t* src = pad + ((int64_t)(z + kHalo) * rep.prows + (y + kHalo)) * rep.prowp + 16 * j;
+            uint8_t* dst = o + (int64_t)M * ((int64_t)L0 * row + x0);
+            uint32_t c[M][4], d[4 * M];
 #pragma unroll
-                for (int u = 0; u < 2; ++u) {
-                    const int w = w0 + u * (int)blockDim.x;
-                    if (w < nw) {
-                        const int c0 = kHalo + 2 * w, c1 = rep.cp + kHalo + 2 * w;  // bytes of (2w, b = 0), (2w, b = 1)
-                        a[u] = *(const uint32_t*)(src + (c0 & ~3));
-                        bb[u] = *(const uint32_t*)(src + (c1 & ~3));
-                    }
-                }
+            for (int b = 0; b < M; ++b) {
+                const uint4 v = *(const uint4*)(src + b * rep.cp);
+                c[b][0] = species_of4(v.x, F);
+                c[b][1] = species_of4(v.y, F);
+                c[b][2] = species_of4(v.z, F);
+                c[b][3] = species_of4(v.w, F);
+            }
+            to_cells<M>(c, d);
+            if (x0 >= 0 && x0 + kPackCells <= L0) {
+                __builtin_memcpy(dst, d, 16 * M);
+            } else {
 #pragma unroll
-                for (int u = 0; u < 2; ++u) {
-                    const int w = w0 + u * (int)blockDim.x;
-                    if (w >= nw) continue;
-                    const uint32_t o = (uint32_t)((kHalo + 2 * w) & 3);  // 0 or 2, the same in both columns (cp is a multiple of 16)
-                    const uint32_t sel = o | ((4 + o) << 8) | ((o + 1) << 16) | ((5 + o) << 24);
-                    d32[w] = (__builtin_amdgcn_perm(bb[u], a[u], sel) >> 3) & 0x1F1F1F1Fu;
-                }
+                for (int k = 0; k < kPackCells * M; ++k)
+                    if (x0 + k / M >= 0 && x0 + k / M < L0) dst[k] = (uint8_t)(d[k >> 2] >> (8 * (k & 3)));
             }
-            continue;
         }
-        // rows of 2 mod 4 bytes (odd L0), every other one starting 2 bytes
-        // past a word boundary: the words from the first aligned byte (x =
-        // x0 + 2w, x0 + 1 + 2w), each column's byte pair taken from the two
-        // aligned words around it; the bytes before and after, one by one
-        if (M == 2 && PLANAR && F == 8 && (n & 3) == 2 && ((uintptr_t)dst & 1) == 0 && ((uintptr_t)src & 3) == 0) {
-            const int pos = (int)((4 - ((uintptr_t)dst & 3)) & 3);  // 0 or 2 bytes before the first word
-            const int nw = (n - pos) >> 2, x0 = pos >> 1;
-            uint32_t* d32 = (uint32_t*)(dst + pos);
-            for (int w = threadIdx.x; w < nw; w += blockDim.x) {
-                const int c0 = kHalo + x0 + 2 * w, c1 = rep.cp + c0;  // bytes of (x, b = 0), (x, b = 1)
-                const uint32_t* a32 = (const uint32_t*)(src + (c0 & ~3));
-                const uint32_t* b32 = (const uint32_t*)(src + (c1 & ~3));
-                const uint32_t pa = __builtin_amdgcn_alignbyte(a32[1], a32[0], (uint32_t)(c0 & 3));
-                const uint32_t pb = __builtin_amdgcn_alignbyte(b32[1], b32[0], (uint32_t)(c1 & 3));
-                d32[w] = (__builtin_amdgcn_perm(pb, pa, 0x05010400u) >> 3) & 0x1F1F1F1Fu;
-            }
-            const int tail = pos + 4 * nw;
-            for (int j = threadIdx.x; j < n - tail + pos; j += blockDim.x) {
-                const int jj = j < pos ? j : tail + (j - pos);
-                const int x = jj >> 1, b = jj & 1;
-                dst[jj] = (uint8_t)species_of(src[row_byte<PLANAR>(rep, M, x, b)], F);
-            }
-            continue;
-        }
-        for (int j = threadIdx.x; j < n; j += blockDim.x) {
-            const int x = j / M, b = j - x * M;
-            dst[j] = (uint8_t)species_of(src[row_byte<PLANAR>(rep, M, x, b)], F);
+    } else {
+        // interleaved rows: a workgroup per natural row, a thread per site byte
+        const int n = M * L0;
+        for (int row = blockIdx.x; row < L1 * L2; row += gridDim.x) {
+            const int z = row / L1, y = row - z * L1;
+            const uint8_t* src = pad + ((int64_t)(z + kHalo) * rep.prows + (y + kHalo)) * rep.prow;
+            uint8_t* dst = o + (int64_t)n * row;
+            for (int j = threadIdx.x; j < n; j += blockDim.x) dst[j] = (uint8_t)species_of(src[M * kHalo + j], F);
         }
     }
 }
@@ -1301,15 +1285,13 @@ hipError_t sweep_occupancy(const void* kernel, int block, size_t lds, int* block
 }
 
 hipError_t launch_pack(int lattice, int K, bool unpack, bool planar, uint8_t* occ, uint8_t* ws,
-                       const RepDev* reps, int r, int64_t nrows, int nrep, int64_t* slots, int parts,
+                       const RepDev* reps, int r, int64_t nrows, int row16, int nrep, int64_t* slots, int parts,
                        int64_t* stats, hipStream_t st)
 {
-    // a workgroup per row (padded rows to pack, natural rows to unpack) of
-    // replica r, or with r < 0 a grid row per replica (nrep of them, nrows
-    // the largest replica's rows), up to 8 rows per workgroup
-    int64_t nb = r < 0 ? (nrows + 7) / 8 : nrows;
-    if (nb > 65536) nb = 65536;
-    if (nb < 1) nb = 1;
+    // replica r, or with r < 0 a grid row per replica (nrep of them); nrows
+    // rows and row16 chunks of 16 cells per row of the largest replica
+    int64_t nb = planar ? (nrows * row16 + kBlock - 1) / kBlock : (r < 0 ? (nrows + 7) / 8 : nrows);
+    nb = std::max<int64_t>(1, std::min<int64_t>(nb, planar ? 1 << 20 : 65536));
     if (r < 0 && (nrep < 1 || nrep > 65535)) return hipErrorInvalidValue;
     const dim3 g((unsigned)nb, r < 0 ? (unsigned)nrep : 1u), b(kBlock);
     const int F = field_bits_of(K);

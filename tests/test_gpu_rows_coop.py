@@ -74,3 +74,29 @@ def test_row_ranges_and_replicas_of_different_sizes(smcx, lattice):
             assert s[r, 0] == res.stats[0] and s[r, 1] == res.stats[1]
             off += len(ref)
         lat.close()
+
+
+@pytest.mark.parametrize("lattice,dims,K,S,rows", [
+    (BCC, (17, 12, 13), 4, 4, True), (BCC, (46, 9, 10), 5, 2, True), (FCC, (14, 9, 10), 5, 4, True),
+    (FCC, (31, 8, 9), 6, 2, True), (BCC, (17, 12, 13), 4, 4, False), (FCC, (14, 9, 10), 5, 4, False),
+])
+def test_stream_sweeps_at_odd_addresses(smcx, lattice, dims, K, S, rows):
+    """Packing and unpacking an occupancy at any byte address, nothing beside it touched."""
+    import torch
+    N = (2 if lattice == BCC else 4) * int(np.prod(dims))
+    occ = rand_occ(N, K, 5, equi=False)
+    V = sym_V(S, K, 0.04, 8)
+    b = I.beta_of_T([1100.0])
+    say(f"odd addresses lattice={lattice} dims={dims} rows={rows}")
+    for shift in (1, 2, 7):
+        buf = torch.full((N + 32,), 3, dtype=torch.uint8, device="cuda")
+        buf[shift:shift + N] = torch.from_numpy(occ).cuda()
+        lat = smcx.Lattice(lattice, dims, K, S, buf[shift:shift + N], ell=4, rows=rows)
+        lat.set_epi(V)
+        cells, _ = lat.schedule(0)
+        lat.sweep(1, 5, b, first_sweep=2, mode="stream")
+        ref = occ.copy()
+        O.run(lattice, dims, K, S, cells, ref, V, 5, b, first_sweep=2, nthreads=NTHREADS)
+        assert np.array_equal(lat.occupancy(), ref)
+        assert bool((buf[:shift] == 3).all()) and bool((buf[shift + N:] == 3).all())
+        lat.close()
