@@ -1324,8 +1324,10 @@ hipError_t launch_validate(const uint8_t* occ, int64_t n, int K, int32_t* bad, h
 
 // ---------------------------------------------------------------------------
 // Replica exchange.  k_energy: E_r = 1/2 sum_{s,k,l} C_r[s][k][l] V[s][k][l],
-// accumulated s, k, l ascending in binary64, one thread per replica (the
-// order fixes the rounding, the same as the host-side energy).  k_exchange:
+// accumulated s, k, l ascending in binary64 (the order fixes the rounding, the
+// same as the host-side energy): a wave per replica forms the products, one
+// lane adds them up (a thread per replica, loading term by term, took 7 to 12
+// us where this takes 3 to 5).  k_exchange:
 // one round of trades between neighbouring temperature slots (i, i + 1),
 // i = round mod 2, round mod 2 + 2, ...: with a = rep_at[i], b = rep_at[i+1]
 // and x = (beta_slot[i] - beta_slot[i+1]) (E_a - E_b), the trade is taken
@@ -1337,14 +1339,54 @@ hipError_t launch_validate(const uint8_t* occ, int64_t n, int K, int32_t* bad, h
 // written to each of the n_rows rows the next sweeps read.  rep_at entries
 // outside [0, R) leave their pair (and their replica's beta) untouched.
 // ---------------------------------------------------------------------------
-__global__ void k_energy(const int64_t* C, const double* V, int R, int SKK, double* E)
+constexpr int kMaxTerms = kMaxShells * kMaxK * kMaxK;
+
+// acc + p[0] + p[STRIDE] + ... + p[STRIDE (n - 1)] in that order; the next
+// reads are on their way during the adds.
+template <int STRIDE>
+__device__ __forceinline__ double sum_in_order(double acc, const double* p, int n)
 {
-    const int r = blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= R) return;
-    const int64_t* c = C + (int64_t)r * SKK;
-    double acc = 0.0;
-    for (int i = 0; i < SKK; ++i) acc = acc + (double)c[i] * V[i];
-    E[r] = 0.5 * acc;
+    constexpr int U = 16;
+    const int full = n / U;
+    double v[2][U];
+    auto read = [&](int c, double(&x)[U]) {
+#pragma unroll
+        for (int k = 0; k < U; ++k) x[k] = p[STRIDE * (U * c + k)];
+    };
+    auto add = [&](const double(&x)[U]) {
+#pragma unroll
+        for (int k = 0; k < U; ++k) acc = acc + x[k];
+    };
+    if (full > 0) read(0, v[0]);
+    int c = 0;
+    for (; c + 1 < full; c += 2) {
+        read(c + 1, v[1]);
+        __builtin_amdgcn_sched_barrier(0);
+        add(v[0]);
+        read(min(c + 2, full - 1), v[0]);
+        __builtin_amdgcn_sched_barrier(0);
+        add(v[1]);
+    }
+    if (c < full) add(v[0]);
+    for (int i = full * U; i < n; ++i) acc = acc + p[STRIDE * i];
+    return acc;
+}
+
+__global__ __launch_bounds__(64) void k_energy(const int64_t* C, const double* V, int R, int SKK, double* E)
+{
+    __shared__ double p[kMaxTerms];
+    for (int r = blockIdx.x; r < R; r += gridDim.x) {
+        const int64_t* c = C + (int64_t)r * SKK;
+        double acc = 0.0;
+        for (int i0 = 0; i0 < SKK; i0 += kMaxTerms) {
+            const int n = min(kMaxTerms, SKK - i0);
+            for (int i = threadIdx.x; i < n; i += 64) p[i] = (double)c[i0 + i] * V[i0 + i];
+            __syncthreads();
+            if (threadIdx.x == 0) acc = sum_in_order<1>(acc, p, n);
+            __syncthreads();
+        }
+        if (threadIdx.x == 0) E[r] = 0.5 * acc;
+    }
 }
 
 __global__ __launch_bounds__(kBlock) void k_exchange(const double* E, const double* beta_slot, int32_t* rep_at, int R,
@@ -2063,26 +2105,51 @@ hipError_t launch_qsro_ministep(int lattice, const QsroArgs& A, int grid, hipStr
 
 hipError_t launch_energy(const int64_t* C, const double* V, int R, int SKK, double* E, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_energy, dim3((unsigned)((R + kBlock - 1) / kBlock)), dim3(kBlock), 0, st, C, V, R, SKK, E);
+    hipLaunchKernelGGL(k_energy, dim3((unsigned)std::min(R, 1 << 20)), dim3(64), 0, st, C, V, R, SKK, E);
     return hipGetLastError();
 }
 
 // Gradient of sum_b g_b E_b with respect to V for E_b = 1/2 <C_b, V>:
-// grad[i] = 1/2 sum_b g_b C_b[i], b ascending in binary64, one thread per
-// entry i of V.
-__global__ void k_energy_grad(const int64_t* C, const double* g, int B, int SKK, double* grad)
+// grad[i] = 1/2 sum_b g_b C_b[i], b ascending in binary64.  The order makes
+// the adds a chain of B, so the work is to keep it fed: a workgroup takes 8
+// entries i, its 1024 threads form the products of 1024 configurations, and 8
+// lanes add them up while the next loads are on their way (one thread per
+// entry, loading as it went, took 984 us for 4096 configurations; this
+// 37).
+constexpr int kGradEntries = 8, kGradBlock = 1024, kGradTile = 1024, kGradPer = kGradTile * kGradEntries / kGradBlock;
+
+__global__ __launch_bounds__(kGradBlock) void k_energy_grad(const int64_t* C, const double* g, int B, int SKK, double* grad)
 {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= SKK) return;
+    __shared__ double p[kGradTile * kGradEntries];  // [configuration][entry]
+    const int e = threadIdx.x % kGradEntries, b0 = threadIdx.x / kGradEntries, i = blockIdx.x * kGradEntries + e;
+    constexpr int step = kGradBlock / kGradEntries;
+    double v[kGradPer];
+    auto load = [&](int64_t first) {
+#pragma unroll
+        for (int k = 0; k < kGradPer; ++k) {
+            const int64_t b = first + b0 + k * step;
+            v[k] = b < B && i < SKK ? g[b] * (double)C[b * SKK + i] : 0.0;
+        }
+    };
     double acc = 0.0;
-    for (int b = 0; b < B; ++b) acc = acc + g[b] * (double)C[(int64_t)b * SKK + i];
-    grad[i] = 0.5 * acc;
+    load(0);
+    for (int64_t first = 0; first < B; first += kGradTile) {
+        __syncthreads();  // the tile before is added up
+#pragma unroll
+        for (int k = 0; k < kGradPer; ++k) p[(b0 + k * step) * kGradEntries + e] = v[k];
+        __syncthreads();
+        if (first + kGradTile < B) load(first + kGradTile);
+        if (threadIdx.x < kGradEntries)
+            acc = sum_in_order<kGradEntries>(acc, p + threadIdx.x, (int)min((int64_t)kGradTile, B - first));
+    }
+    const int o = blockIdx.x * kGradEntries + threadIdx.x;
+    if (threadIdx.x < kGradEntries && o < SKK) grad[o] = 0.5 * acc;
 }
 
 hipError_t launch_energy_grad(const int64_t* C, const double* g, int B, int SKK, double* grad, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_energy_grad, dim3((unsigned)((SKK + kBlock - 1) / kBlock)), dim3(kBlock), 0, st, C, g, B,
-                       SKK, grad);
+    hipLaunchKernelGGL(k_energy_grad, dim3((unsigned)((SKK + kGradEntries - 1) / kGradEntries)), dim3(kGradBlock), 0, st, C,
+                       g, B, SKK, grad);
     return hipGetLastError();
 }
 
