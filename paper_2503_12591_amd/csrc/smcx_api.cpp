@@ -107,9 +107,7 @@ struct Plan {
     LdsLayout lds;
     size_t off_reps, off_origins, off_tileoff, off_offP, off_offB, off_pd, off_D, off_Q, off_V, off_misc, off_slots, off_pad, total;
     // qSRO model: affected-set and neighbour tables, V, W, Z
-    size_t off_qaff, off_qnbr, off_qV, off_qW, off_qZ, off_qslots;
-    int qnaff;   // largest affected set
-    int qreach;  // cells per axis from the active site's cell to the farthest site a qSRO trial reads
+    size_t off_qaff, off_qnbr, off_qV, off_qW, off_qZ, off_qG, off_qslots;
     int n_origins;
     int64_t total_sites, total_tiles;
     int max_nA;
@@ -545,6 +543,7 @@ int make_plan(const smcx_desc* d, Plan& P)
     P.off_qV = o; o = align256(o + sizeof(double) * P.S * P.K * P.K);
     P.off_qW = o; o = align256(o + sizeof(double) * P.S * P.K);
     P.off_qZ = o; o = align256(o + sizeof(int32_t) * kMaxShells);
+    P.off_qG = o; o = align256(o + sizeof(double) * qsro_products(P.K, P.S));
     P.off_qslots = o; o = align256(o + sizeof(int64_t) * 3 * kQsroGrid);
     P.off_rowoff = o; o = align256(o + sizeof(int64_t) * (P.R + 1));
     P.off_offP_r = o; o = align256(o + sizeof(int16_t) * P.m * P.Z1 * P.sumZ);
@@ -904,7 +903,6 @@ int smcx_lattice_init(smcx_lattice** out, const smcx_desc* desc, uint8_t* occ_de
             for (int sh = 0; sh < P.S; ++sh)
                 for (int n = 0; n < G.Z[sh]; ++n) qnbr[(size_t)b * P.sumZ + j++] = pack(b, G.v[sh][n][0], G.v[sh][n][1], G.v[sh][n][2]);
         }
-        int largest = 0;
         for (int b = 0; b < P.m; ++b)
             for (int k = 0; k < P.Z1; ++k) {
                 std::vector<std::array<int, 3>> v;
@@ -925,24 +923,16 @@ int smcx_lattice_init(smcx_lattice** out, const smcx_desc* desc, uint8_t* occ_de
                 if ((int)v.size() > kQsroMaxAff) return fail(SMCX_E_UNSUPPORTED, "qSRO affected set too large");
                 int32_t* row = qaff.data() + (size_t)(b * P.Z1 + k) * (1 + kQsroMaxAff);
                 row[0] = (int32_t)v.size();
-                for (size_t i = 0; i < v.size(); ++i) row[1 + i] = pack(b, v[i][0], v[i][1], v[i][2]);
-                largest = std::max(largest, (int)v.size());
+                // the site's shell (from 1) that a vector from it lies in, 0 if none
+                auto shell_of = [&](int dx, int dy, int dz) {
+                    for (int sh = 0; sh < P.S; ++sh)
+                        if (dx * dx + dy * dy + dz * dz == G.r2[sh]) return sh + 1;
+                    return 0;
+                };
+                for (size_t i = 0; i < v.size(); ++i)
+                    row[1 + i] = pack(b, v[i][0], v[i][1], v[i][2]) | shell_of(v[i][0], v[i][1], v[i][2]) << 26 |
+                                 (int32_t)((uint32_t)shell_of(v[i][0] - ab[0], v[i][1] - ab[1], v[i][2] - ab[2]) << 29);
             }
-        h->P.qnaff = largest;
-        // reach of a trial in cells: the farthest affected site plus the
-        // farthest neighbour, per axis
-        int ra = 0, rn = 0;
-        for (int b = 0; b < P.m; ++b) {
-            for (int k = 0; k < P.Z1; ++k) {
-                const int32_t* row = qaff.data() + (size_t)(b * P.Z1 + k) * (1 + kQsroMaxAff);
-                for (int i = 0; i < row[0]; ++i)
-                    for (int sh = 0; sh < 3; ++sh) ra = std::max(ra, std::abs(((row[1 + i] >> (8 * sh)) & 0xff) - 8));
-            }
-            for (int j = 0; j < P.sumZ; ++j)
-                for (int sh = 0; sh < 3; ++sh)
-                    rn = std::max(rn, std::abs(((qnbr[(size_t)b * P.sumZ + j] >> (8 * sh)) & 0xff) - 8));
-        }
-        h->P.qreach = ra + rn;
         int32_t Zs[kMaxShells] = {0, 0, 0, 0};
         for (int sh = 0; sh < P.S; ++sh) Zs[sh] = G.Z[sh];
         SMCX_HIP(hipMemcpyAsync(h->ws + P.off_qnbr, qnbr.data(), sizeof(int32_t) * qnbr.size(), hipMemcpyHostToDevice, st));
@@ -1132,6 +1122,19 @@ int smcx_set_qsro(smcx_lattice* h, const double* V, const double* W, void* strea
             }
         }
     hipStream_t st = (hipStream_t)stream;
+    // every product of the local energies over the neighbour counts, rounded
+    // as the trial's own multiplications would be
+    std::vector<double> G((size_t)qsro_products(K, S), 0.0);
+    for (int s = 0; s < S; ++s) {
+        const int Z = kGeom[P.lattice].Z[s];
+        for (int p = 0; p < K; ++p)
+            for (int n = 0; n <= Z; ++n) {
+                const double f = (double)n / (double)Z;
+                for (int t = 0; t < K; ++t) G[(size_t)((s * K + p) * K + t) * kQsroFrac + n] = V[(s * K + p) * K + t] * f;
+                G[(size_t)(S * K * K + s * K + p) * kQsroFrac + n] = W[s * K + p] * (f * f);
+            }
+    }
+    SMCX_HIP(hipMemcpyAsync(h->ws + P.off_qG, G.data(), sizeof(double) * G.size(), hipMemcpyHostToDevice, st));
     SMCX_HIP(hipMemcpyAsync(h->ws + P.off_qV, V, sizeof(double) * S * K * K, hipMemcpyHostToDevice, st));
     SMCX_HIP(hipMemcpyAsync(h->ws + P.off_qW, W, sizeof(double) * S * K, hipMemcpyHostToDevice, st));
     SMCX_HIP(hipStreamSynchronize(st));
@@ -1183,7 +1186,6 @@ int smcx_sweep_qsro(smcx_lattice* h, int32_t n_sweeps, uint64_t seed, uint32_t f
             A.L0 = R.L[0]; A.L1 = R.L[1]; A.L2 = R.L[2];
             A.K = P.K; A.S = P.S; A.Z1 = P.Z1; A.sumZ = P.sumZ; A.naff_max = kQsroMaxAff;
             A.ncx = (int)R.edges[0].size(); A.ncy = (int)R.edges[1].size(); A.ncz = (int)R.edges[2].size();
-            A.reach = P.qreach;
             A.org = origins + cs_off[r];
             A.sweep = first_sweep + (uint32_t)js;
             A.replica = (uint32_t)r;
@@ -1194,22 +1196,25 @@ int smcx_sweep_qsro(smcx_lattice* h, int32_t n_sweeps, uint64_t seed, uint32_t f
             A.V = (const double*)(h->ws + P.off_qV);
             A.W = (const double*)(h->ws + P.off_qW);
             A.Z = (const int32_t*)(h->ws + P.off_qZ);
+            A.G = (const double*)(h->ws + P.off_qG);
             A.slots = (int64_t*)(h->ws + P.off_qslots);
             A.ties = ties_dev;
             A.tie_cap = tie_cap;
             A.tie_count = tie_count_dev;
             const int ncell = A.ncx * A.ncy * A.ncz;
             const int grid = std::min(ncell, kQsroGrid);
-            SMCX_HIP(launch_fill_i64(A.slots, 3 * (int64_t)grid, 0, st));
-            for (int tau = 0; tau < R.nA; ++tau) {
+            const int waves = std::min((grid + 7) / 8 * 8, kQsroGrid);  // whole workgroups
+            SMCX_HIP(launch_fill_i64(A.slots, 3 * (int64_t)waves, 0, st));
+            const bool staged = qsro_staged(P.lattice, A);
+            for (int tau = 0; tau < R.nA; tau += staged ? P.m : 1) {
                 A.b = tau % P.m;
                 const int rest = tau / P.m;
                 A.o0 = rest % R.M[0];
                 A.o1 = (rest / R.M[0]) % R.M[1];
                 A.o2 = rest / (R.M[0] * R.M[1]);
-                SMCX_HIP(launch_qsro_ministep(P.lattice, A, grid, st));
+                SMCX_HIP(staged ? launch_qsro_offset(P.lattice, A, grid, st) : launch_qsro_ministep(P.lattice, A, grid, st));
             }
-            SMCX_HIP(launch_qsro_reduce(A.slots, grid, stats_dev + 3 * (int64_t)r, st));
+            SMCX_HIP(launch_qsro_reduce(A.slots, waves, stats_dev + 3 * (int64_t)r, st));
         }
     return SMCX_OK;
 }

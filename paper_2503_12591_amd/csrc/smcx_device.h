@@ -423,6 +423,37 @@ __device__ __forceinline__ void log_tie(const SweepArgs& A, int r, uint32_t t, i
     }
 }
 
+// acc + p[0] + p[STRIDE] + ... + p[STRIDE (n - 1)] in that order; the next
+// reads are on their way during the adds.
+template <int STRIDE>
+__device__ __forceinline__ double sum_in_order(double acc, const double* p, int n)
+{
+    constexpr int U = 16;
+    const int full = n / U;
+    double v[2][U];
+    auto read = [&](int c, double(&x)[U]) {
+#pragma unroll
+        for (int k = 0; k < U; ++k) x[k] = p[STRIDE * (U * c + k)];
+    };
+    auto add = [&](const double(&x)[U]) {
+#pragma unroll
+        for (int k = 0; k < U; ++k) acc = acc + x[k];
+    };
+    if (full > 0) read(0, v[0]);
+    int c = 0;
+    for (; c + 1 < full; c += 2) {
+        read(c + 1, v[1]);
+        __builtin_amdgcn_sched_barrier(0);
+        add(v[0]);
+        read(min(c + 2, full - 1), v[0]);
+        __builtin_amdgcn_sched_barrier(0);
+        add(v[1]);
+    }
+    if (c < full) add(v[0]);
+    for (int i = full * U; i < n; ++i) acc = acc + p[STRIDE * i];
+    return acc;
+}
+
 // Per-thread trial statistics, flushed with one wave reduction and three
 // atomics per wave.
 struct Stats {

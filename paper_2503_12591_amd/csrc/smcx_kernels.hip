@@ -1341,37 +1341,6 @@ hipError_t launch_validate(const uint8_t* occ, int64_t n, int K, int32_t* bad, h
 // ---------------------------------------------------------------------------
 constexpr int kMaxTerms = kMaxShells * kMaxK * kMaxK;
 
-// acc + p[0] + p[STRIDE] + ... + p[STRIDE (n - 1)] in that order; the next
-// reads are on their way during the adds.
-template <int STRIDE>
-__device__ __forceinline__ double sum_in_order(double acc, const double* p, int n)
-{
-    constexpr int U = 16;
-    const int full = n / U;
-    double v[2][U];
-    auto read = [&](int c, double(&x)[U]) {
-#pragma unroll
-        for (int k = 0; k < U; ++k) x[k] = p[STRIDE * (U * c + k)];
-    };
-    auto add = [&](const double(&x)[U]) {
-#pragma unroll
-        for (int k = 0; k < U; ++k) acc = acc + x[k];
-    };
-    if (full > 0) read(0, v[0]);
-    int c = 0;
-    for (; c + 1 < full; c += 2) {
-        read(c + 1, v[1]);
-        __builtin_amdgcn_sched_barrier(0);
-        add(v[0]);
-        read(min(c + 2, full - 1), v[0]);
-        __builtin_amdgcn_sched_barrier(0);
-        add(v[1]);
-    }
-    if (c < full) add(v[0]);
-    for (int i = full * U; i < n; ++i) acc = acc + p[STRIDE * i];
-    return acc;
-}
-
 __global__ __launch_bounds__(64) void k_energy(const int64_t* C, const double* V, int R, int SKK, double* E)
 {
     __shared__ double p[kMaxTerms];
@@ -1768,338 +1737,6 @@ hipError_t launch_clusters(int lattice, const double* e, const int32_t* L, doubl
         hipLaunchKernelGGL(k_cluster_hook<SMCX_FCC>, dim3(nbc), dim3(kBlock), 0, st, label, L[0], L[1], L[2]);
     // a grid-stride grid of 4096 workgroups: one count atomic per wave, not per 256 sites
     hipLaunchKernelGGL(k_cluster_flatten, dim3(std::min(nbs, 4096u)), dim3(kBlock), 0, st, label, N, size, n_clusters);
-    return hipGetLastError();
-}
-
-// ---------------------------------------------------------------------------
-// qSRO model: trials whose energy change needs every local energy of the
-// swap's interaction zone.  E_i = sum_m sum_t V_m[p][t] (n_i[m][t] / Z_m)
-// + sum_m W_m[p] (n_i[m][p] / Z_m)^2 (p = sigma_i; m, then t, ascending,
-// binary64).  A wave takes one trial (the same Philox draw, partner and
-// acceptance rule as the pair model); its lanes take the sites of the
-// affected set (a, the partner and every shell neighbour of either, in the
-// host table's order), recount each one's neighbours before and after the
-// swap (the swap applied to the two sites on the fly) and leave
-// E_after - E_before in LDS; lane 0 adds the terms in table order, decides
-// and writes the swap.  The sites are read from the natural layout; the
-// partition keeps every read of a mini-step's trial clear of the other
-// trials' writes (interaction-zone rule).
-// ---------------------------------------------------------------------------
-
-__device__ __forceinline__ int qsro_site_of(const QsroArgs& A, int x, int y, int z, int32_t d, int m)
-{
-    // d packs (dx + 8) | (dy + 8) << 8 | (dz + 8) << 16 | basis << 24
-    int xx = x + (d & 0xff) - 8, yy = y + ((d >> 8) & 0xff) - 8, zz = z + ((d >> 16) & 0xff) - 8;
-    xx += xx < 0 ? A.L0 : (xx >= A.L0 ? -A.L0 : 0);
-    yy += yy < 0 ? A.L1 : (yy >= A.L1 ? -A.L1 : 0);
-    zz += zz < 0 ? A.L2 : (zz >= A.L2 ? -A.L2 : 0);
-    return (d >> 24) + m * (xx + A.L0 * (yy + A.L1 * zz));
-}
-
-// Tables of a qSRO launch in LDS: V and W, and every fraction n / Z_s
-// (n = 0 .. Z_s), each the correctly rounded quotient, so a lookup gives the
-// value the division would.
-constexpr int kQsroFrac = kMaxZ + 1;
-struct QsroTables {
-    double V[kMaxShells * 8 * 8];
-    double W[kMaxShells * 8];
-    double F[kMaxShells * kQsroFrac];
-};
-
-__device__ __forceinline__ void qsro_tables(const QsroArgs& A, QsroTables& T)
-{
-    for (int i = threadIdx.x; i < A.S * A.K * A.K; i += blockDim.x) T.V[i] = A.V[i];
-    for (int i = threadIdx.x; i < A.S * A.K; i += blockDim.x) T.W[i] = A.W[i];
-    for (int i = threadIdx.x; i < A.S * kQsroFrac; i += blockDim.x) {
-        const int s = i / kQsroFrac, n = i - s * kQsroFrac;
-        T.F[i] = (double)n / (double)A.Z[s];
-    }
-    __syncthreads();
-}
-
-__device__ __forceinline__ double qsro_energy(const QsroArgs& A, const QsroTables& T, int p,
-                                              const uint64_t (&n)[kMaxShells])
-{
-    double acc = 0.0;
-    for (int s = 0; s < A.S; ++s)
-        for (int t = 0; t < A.K; ++t)
-            acc = acc + T.V[(s * A.K + p) * A.K + t] * T.F[s * kQsroFrac + (int)((n[s] >> (8 * t)) & 0xff)];
-    for (int s = 0; s < A.S; ++s) {
-        const double f = T.F[s * kQsroFrac + (int)((n[s] >> (8 * p)) & 0xff)];
-        acc = acc + T.W[s * A.K + p] * (f * f);
-    }
-    return acc;
-}
-
-template <int LAT>
-__global__ __launch_bounds__(64) void k_qsro_ministep(QsroArgs A)
-{
-    constexpr int m = kGeom[LAT].m;
-    __shared__ double term[kQsroMaxAff];
-    __shared__ QsroTables tab;
-    qsro_tables(A, tab);
-    const int lane = threadIdx.x;
-    const int ncell = A.ncx * A.ncy * A.ncz;
-    const int32_t* ox = A.org;
-    const int32_t* oy = ox + A.ncx + 1;
-    const int32_t* oz = oy + A.ncy + 1;
-    int att = 0, nacc = 0, ntie = 0;
-    for (int c = blockIdx.x; c < ncell; c += gridDim.x) {
-        const int cx = c % A.ncx, cy = (c / A.ncx) % A.ncy, cz = c / (A.ncx * A.ncy);
-        if (A.o0 >= ox[cx + 1] - ox[cx] || A.o1 >= oy[cy + 1] - oy[cy] || A.o2 >= oz[cz + 1] - oz[cz]) continue;
-        const int x = ox[cx] + A.o0, y = oy[cy] + A.o1, z = oz[cz] + A.o2;
-        const int a = A.b + m * (x + A.L0 * (y + A.L1 * z));
-        uint32_t w0, w1, w2, w3;
-        philox4x32_10((uint32_t)a, 0u, A.sweep, A.replica, (uint32_t)A.seed, (uint32_t)(A.seed >> 32), w0, w1, w2, w3);
-        (void)w3;
-        const int k = (int)__umulhi(w0, (uint32_t)A.Z1);
-        const int bsite = qsro_site_of(A, x, y, z, A.nbr[A.b * A.sumZ + k], m);
-        const int p = A.occ[a], q = A.occ[bsite];
-        ++att;
-        if (p == q) continue;
-        const int32_t* list = A.aff + (int64_t)(A.b * A.Z1 + k) * (1 + A.naff_max);
-        const int naff = list[0];
-        for (int i = lane; i < naff; i += 64) {
-            const int j = qsro_site_of(A, x, y, z, list[1 + i], m);
-            const int jb = j % m, jc = j / m;
-            const int jx = jc % A.L0, jy = (jc / A.L0) % A.L1, jz = jc / (A.L0 * A.L1);
-            const int sj = A.occ[j];
-            const int sj2 = j == a ? q : (j == bsite ? p : sj);
-            uint64_t nb[kMaxShells], na[kMaxShells];
-            const int32_t* nl = A.nbr + jb * A.sumZ;
-            int off = 0;
-            for (int s = 0; s < kMaxShells; ++s) {
-                uint64_t cb = 0, ca = 0;
-                if (s < A.S) {
-                    for (int n = 0; n < A.Z[s]; ++n) {
-                        const int xs = qsro_site_of(A, jx, jy, jz, nl[off + n], m);
-                        const int v = A.occ[xs];
-                        const int v2 = xs == a ? q : (xs == bsite ? p : v);
-                        cb += (uint64_t)1 << (8 * (v & 7));
-                        ca += (uint64_t)1 << (8 * (v2 & 7));
-                    }
-                    off += A.Z[s];
-                }
-                nb[s] = cb;
-                na[s] = ca;
-            }
-            term[i] = qsro_energy(A, tab, min(sj2, A.K - 1), na) - qsro_energy(A, tab, min(sj, A.K - 1), nb);
-        }
-        __syncthreads();
-        if (lane == 0) {
-            double dE = 0.0;
-            for (int i = 0; i < naff; ++i) dE = dE + term[i];
-            bool acc = true, tie = false;
-            if (!(dE <= 0.0)) {
-                const double P = exp(-(A.beta * dE));
-                const double u = (double)(((uint64_t)w1 << 21) | (uint64_t)(w2 >> 11)) * 0x1p-53;
-                acc = u < P;
-                tie = fabs(u - P) < 1e-12;
-            }
-            if (tie) {
-                ++ntie;
-                const int slot = atomicAdd(A.tie_count, 1);
-                if (slot < A.tie_cap) {
-                    smcx_tie e;
-                    e.replica = (int32_t)A.replica;
-                    e.sweep = A.sweep;
-                    e.site = a;
-                    e.decision = acc ? 1 : 0;
-                    e.pad = 0;
-                    A.ties[slot] = e;
-                }
-            }
-            if (acc) {
-                ++nacc;
-                A.occ[a] = (uint8_t)q;
-                A.occ[bsite] = (uint8_t)p;
-            }
-        }
-        __syncthreads();  // the terms are free again
-    }
-    if (lane == 0) {
-        // this workgroup's own counter slot (no other workgroup of the
-        // launch writes it; launches on one stream follow each other), so no
-        // atomics: thousands of atomics on one address would serialise
-        int64_t* slot = A.slots + 3 * (int64_t)blockIdx.x;
-        slot[0] += att;
-        slot[1] += nacc;
-        slot[2] += ntie;
-    }
-}
-
-// The same trial with its neighbourhood staged: the wave first copies the box
-// of (2 reach + 1)^3 cells around the active site's cell (periodic, one load
-// per cell of m bytes) into LDS, then every read of the affected sites and
-// their neighbours is an LDS byte at a fixed offset from the site's own (no
-// wrap arithmetic, no scattered L2 loads).  Each lattice site appears once in
-// the box because every edge is at least 2 reach + 1 cells; sites of the box
-// that the trial does not read may be written by other trials of the
-// mini-step meanwhile, which is harmless.  Terms, order of the sum, decision
-// and the near-tie log are those of k_qsro_ministep.
-template <int LAT>
-__global__ __launch_bounds__(64) void k_qsro_win(QsroArgs A)
-{
-    constexpr int m = kGeom[LAT].m;
-    constexpr int WMAX = 2 * kQsroMaxReach + 1;
-    using Cell = typename std::conditional<m == 4, uint32_t, uint16_t>::type;
-    __shared__ double term[kQsroMaxAff];
-    __shared__ QsroTables tab;
-    __shared__ __align__(16) uint8_t win[WMAX * WMAX * WMAX * m];
-    __shared__ int16_t nof[4 * kMaxShells * kMaxZ];  // [basis][neighbour]: window byte offset from the site
-    qsro_tables(A, tab);
-    const int lane = threadIdx.x;
-    const int Rch = A.reach, W = 2 * Rch + 1, W3 = W * W * W;
-    for (int i = lane; i < m * A.sumZ; i += 64) {
-        const int b = i / A.sumZ;
-        const int32_t d = A.nbr[i];
-        const int dx = (d & 0xff) - 8, dy = ((d >> 8) & 0xff) - 8, dz = ((d >> 16) & 0xff) - 8;
-        nof[i] = (int16_t)(((dz * W + dy) * W + dx) * m + (d >> 24) - b);
-    }
-    __syncthreads();
-    const int ncell = A.ncx * A.ncy * A.ncz;
-    const int32_t* ox = A.org;
-    const int32_t* oy = ox + A.ncx + 1;
-    const int32_t* oz = oy + A.ncy + 1;
-    const int center = ((Rch * W + Rch) * W + Rch) * m;  // byte of basis site 0 of the active site's cell
-    int att = 0, nacc = 0, ntie = 0;
-    for (int c = blockIdx.x; c < ncell; c += gridDim.x) {
-        const int cx = c % A.ncx, cy = (c / A.ncx) % A.ncy, cz = c / (A.ncx * A.ncy);
-        if (A.o0 >= ox[cx + 1] - ox[cx] || A.o1 >= oy[cy + 1] - oy[cy] || A.o2 >= oz[cz + 1] - oz[cz]) continue;
-        const int x = ox[cx] + A.o0, y = oy[cy] + A.o1, z = oz[cz] + A.o2;
-        const int a = A.b + m * (x + A.L0 * (y + A.L1 * z));
-        uint32_t w0, w1, w2, w3;
-        philox4x32_10((uint32_t)a, 0u, A.sweep, A.replica, (uint32_t)A.seed, (uint32_t)(A.seed >> 32), w0, w1, w2, w3);
-        (void)w3;
-        const int k = (int)__umulhi(w0, (uint32_t)A.Z1);
-        const int bsite = qsro_site_of(A, x, y, z, A.nbr[A.b * A.sumZ + k], m);
-        // the box: cell (x, y, z) + (wx, wy, wz) - reach, one wrap per axis
-        // (edges >= W); its loads go out with those of the two sites, whose
-        // species may still show the trial to be void (p == q)
-        const int p = A.occ[a], q = A.occ[bsite];
-        for (int i = lane; i < W3; i += 64) {
-            const int wx = i % W, wy = (i / W) % W, wz = i / (W * W);
-            int xx = x + wx - Rch, yy = y + wy - Rch, zz = z + wz - Rch;
-            xx += xx < 0 ? A.L0 : (xx >= A.L0 ? -A.L0 : 0);
-            yy += yy < 0 ? A.L1 : (yy >= A.L1 ? -A.L1 : 0);
-            zz += zz < 0 ? A.L2 : (zz >= A.L2 ? -A.L2 : 0);
-            *(Cell*)(win + m * i) = *(const Cell*)(A.occ + m * (xx + A.L0 * (yy + A.L1 * zz)));
-        }
-        ++att;
-        __syncthreads();
-        if (p == q) continue;
-        const int abyte = center + A.b;
-        const int bbyte = abyte + nof[A.b * A.sumZ + k];
-        const int32_t* list = A.aff + (int64_t)(A.b * A.Z1 + k) * (1 + A.naff_max);
-        const int naff = list[0];
-        for (int i = lane; i < naff; i += 64) {
-            const int32_t d = list[1 + i];
-            const int jb = d >> 24;
-            const int jbyte = center + ((((d >> 16) & 0xff) - 8) * W + (((d >> 8) & 0xff) - 8)) * W * m +
-                              ((d & 0xff) - 8) * m + jb;
-            const int sj = win[jbyte];
-            const int sj2 = jbyte == abyte ? q : (jbyte == bbyte ? p : sj);
-            uint64_t nb[kMaxShells], na[kMaxShells];
-            const int16_t* nl = nof + jb * A.sumZ;
-            int off = 0;
-            for (int s = 0; s < kMaxShells; ++s) {
-                uint64_t cb = 0, ca = 0;
-                if (s < A.S) {
-                    for (int n = 0; n < A.Z[s]; ++n) {
-                        const int xb = jbyte + nl[off + n];
-                        const int v = win[xb];
-                        const int v2 = xb == abyte ? q : (xb == bbyte ? p : v);
-                        cb += (uint64_t)1 << (8 * (v & 7));
-                        ca += (uint64_t)1 << (8 * (v2 & 7));
-                    }
-                    off += A.Z[s];
-                }
-                nb[s] = cb;
-                na[s] = ca;
-            }
-            term[i] = qsro_energy(A, tab, min(sj2, A.K - 1), na) - qsro_energy(A, tab, min(sj, A.K - 1), nb);
-        }
-        __syncthreads();
-        if (lane == 0) {
-            double dE = 0.0;
-            for (int i = 0; i < naff; ++i) dE = dE + term[i];
-            bool acc = true, tie = false;
-            if (!(dE <= 0.0)) {
-                const double P = exp(-(A.beta * dE));
-                const double u = (double)(((uint64_t)w1 << 21) | (uint64_t)(w2 >> 11)) * 0x1p-53;
-                acc = u < P;
-                tie = fabs(u - P) < 1e-12;
-            }
-            if (tie) {
-                ++ntie;
-                const int slot = atomicAdd(A.tie_count, 1);
-                if (slot < A.tie_cap) {
-                    smcx_tie e;
-                    e.replica = (int32_t)A.replica;
-                    e.sweep = A.sweep;
-                    e.site = a;
-                    e.decision = acc ? 1 : 0;
-                    e.pad = 0;
-                    A.ties[slot] = e;
-                }
-            }
-            if (acc) {
-                ++nacc;
-                A.occ[a] = (uint8_t)q;
-                A.occ[bsite] = (uint8_t)p;
-            }
-        }
-        __syncthreads();  // the terms and the box are free again
-    }
-    if (lane == 0) {
-        int64_t* slot = A.slots + 3 * (int64_t)blockIdx.x;
-        slot[0] += att;
-        slot[1] += nacc;
-        slot[2] += ntie;
-    }
-}
-
-// Sum the workgroups' counter slots into a replica's counters.
-__global__ void k_qsro_reduce(const int64_t* slots, int n, int64_t* stats)
-{
-    int64_t v[3] = {0, 0, 0};
-    for (int i = threadIdx.x; i < n; i += blockDim.x)
-        for (int c = 0; c < 3; ++c) v[c] += slots[3 * (int64_t)i + c];
-    __shared__ int64_t red[3][kBlock];
-    for (int c = 0; c < 3; ++c) red[c][threadIdx.x] = v[c];
-    __syncthreads();
-    for (int w = kBlock / 2; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w)
-            for (int c = 0; c < 3; ++c) red[c][threadIdx.x] += red[c][threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0)
-        for (int c = 0; c < 3; ++c)
-            if (red[c][0]) atomicAdd((unsigned long long*)(stats + c), (unsigned long long)red[c][0]);
-}
-
-hipError_t launch_qsro_reduce(const int64_t* slots, int n, int64_t* stats, hipStream_t st)
-{
-    hipLaunchKernelGGL(k_qsro_reduce, dim3(1), dim3(kBlock), 0, st, slots, n, stats);
-    return hipGetLastError();
-}
-
-hipError_t launch_qsro_ministep(int lattice, const QsroArgs& A, int grid, hipStream_t st)
-{
-    // the windowed trial where the box fits the lattice and the kernel's LDS
-    // box (reach <= kQsroMaxReach), cells are aligned, and the neighbour
-    // table fits; the gather kernel otherwise
-    const int m = lattice == SMCX_BCC ? 2 : 4;
-    const int W = 2 * A.reach + 1;
-    const bool win = A.reach >= 1 && A.reach <= kQsroMaxReach && A.L0 >= W && A.L1 >= W && A.L2 >= W &&
-                     ((uintptr_t)A.occ % m) == 0 && m * A.sumZ <= 4 * kMaxShells * kMaxZ;
-    if (lattice == SMCX_BCC) {
-        if (win) hipLaunchKernelGGL(k_qsro_win<SMCX_BCC>, dim3((unsigned)grid), dim3(64), 0, st, A);
-        else hipLaunchKernelGGL(k_qsro_ministep<SMCX_BCC>, dim3((unsigned)grid), dim3(64), 0, st, A);
-    } else {
-        if (win) hipLaunchKernelGGL(k_qsro_win<SMCX_FCC>, dim3((unsigned)grid), dim3(64), 0, st, A);
-        else hipLaunchKernelGGL(k_qsro_ministep<SMCX_FCC>, dim3((unsigned)grid), dim3(64), 0, st, A);
-    }
     return hipGetLastError();
 }
 

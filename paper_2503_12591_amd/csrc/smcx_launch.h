@@ -40,9 +40,11 @@ hipError_t static_workspace(void** ptr);
 hipError_t launch_energy_grad(const int64_t* C, const double* g, int B, int SKK, double* grad, hipStream_t st);
 // Largest qSRO affected set a trial can have (entries of its LDS terms).
 constexpr int kQsroMaxAff = 256;
-// Largest reach (cells per axis) of the windowed qSRO trial: a box of
-// (2 reach + 1)^3 cells around the active site's cell.
-constexpr int kQsroMaxReach = 4;
+// Entries of a shell's table over neighbour counts n = 0 .. Z_s.
+constexpr int kQsroFrac = kMaxZ + 1;
+// Products of the local energies: V_s[p][t] (n / Z_s) as [S][K][K][kQsroFrac],
+// then W_s[p] (n / Z_s)^2 as [S][K][kQsroFrac].
+constexpr int qsro_products(int K, int S) { return (S * K * K + S * K) * kQsroFrac; }
 
 // Arguments of one qSRO mini-step launch over one replica.
 struct QsroArgs {
@@ -51,24 +53,29 @@ struct QsroArgs {
     const int32_t* org;    // cell origins: x (ncx + 1), y (ncy + 1), z (ncz + 1)
     int ncx, ncy, ncz;
     int o0, o1, o2, b;     // the mini-step's offsets and basis site
-    int reach;             // cells from the active site's cell to the farthest site a trial reads, per axis
     uint32_t sweep, replica;
     uint64_t seed;
     double beta;
-    const int32_t* aff;    // [m][Z1][1 + naff_max]: count, then packed displacements
+    const int32_t* aff;    // [m][Z1][1 + naff_max]: count, then packed displacements (low 26 bits), and the
+                           // 1-based shells of the site that hold the active site (3 bits), the partner (3 bits)
     const int32_t* nbr;    // [m][sumZ]: packed neighbour displacements, shells in order
     const double* V;       // [S][K][K]
     const double* W;       // [S][K]
     const int32_t* Z;      // [S]
-    int64_t* slots;        // [gridDim][3]: each workgroup's attempted / accepted / near-tie counts
+    const double* G;       // products (qsro_products)
+    int64_t* slots;        // [kQsroGrid][3]: each wave's attempted / accepted / near-tie counts
     smcx_tie* ties;
     int32_t tie_cap;
     int32_t* tie_count;
 };
 
+// One mini-step (offset and basis site of A), `grid` waves; or, where
+// qsro_staged allows, every basis site of A's offset.
 hipError_t launch_qsro_ministep(int lattice, const QsroArgs& A, int grid, hipStream_t st);
+bool qsro_staged(int lattice, const QsroArgs& A);
+hipError_t launch_qsro_offset(int lattice, const QsroArgs& A, int grid, hipStream_t st);
 hipError_t launch_qsro_reduce(const int64_t* slots, int n, int64_t* stats, hipStream_t st);
-// workgroups of a qSRO mini-step launch (each has a counter slot)
+// waves of a qSRO launch (each has a counter slot; a multiple of the waves per workgroup)
 constexpr int kQsroGrid = 8192;
 hipError_t launch_local_energy(int lattice, const uint8_t* occ, const int32_t* L, int K, int S, const double* V,
                                double* e, hipStream_t st);

@@ -61,3 +61,41 @@ def test_qsro_needs_the_interaction_zone_rule(smcx):
     with pytest.raises(smcx.SmcxError):
         lat.sweep_qsro(1, 0, [10.0])  # link cells of 4 < 5 for 4 BCC shells
     lat.close()
+
+
+@pytest.mark.parametrize("lattice,dims,K,S,ell", [
+    (BCC, (7, 9, 12), 4, 2, 4),        # boxes as wide as the lattice
+    (BCC, (9, 14, 10), 8, 1, 3),
+    (BCC, (13, 10, 16), 5, 3, 4),
+    (BCC, (10, 15, 11), 3, 4, 5),      # more affected sites than lanes
+    (BCC, (8, 8, 10), 4, 4, 5),        # narrower than the box: the gather kernel
+    (FCC, (8, 12, 9), 4, 1, 3),
+    (FCC, (16, 9, 13), 8, 2, 4),
+    (FCC, (8, 10, 12), 5, 3, 4),
+    (FCC, (9, 8, 9), 3, 4, 4),
+    (FCC, (6, 8, 8), 5, 2, 4),         # narrower than the box
+])
+def test_qsro_staged_trials(smcx, lattice, dims, K, S, ell):
+    """Every shell count and counter width of the staged trials, aligned and not."""
+    import torch
+    say(f"qsro staged lattice={lattice} dims={dims} K={K} S={S} ell={ell}")
+    V = sym_V(S, K, 0.05, 21)
+    W = np.random.default_rng(22).normal(0, 0.2, (S, K))
+    N = (2 if lattice == BCC else 4) * int(np.prod(dims))
+    occ = rand_occ(N, K, 30, equi=False)
+    betas = np.array([12.0, 25.0])
+    for shift in (0, 1):
+        buf = torch.zeros(N + 4, dtype=torch.uint8, device="cuda")
+        buf[shift:shift + N] = torch.from_numpy(occ).cuda()
+        lat = smcx.Lattice(lattice, dims, K, S, buf[shift:shift + N], ell=ell)
+        lat.set_qsro(V, W)
+        stats, ties, tc = lat.sweep_qsro(2, 5, betas, first_sweep=2)
+        tnp, nt = lat.ties_to_numpy(ties, tc)
+        sched = lat.schedule(0)[0]
+        ref = occ.copy()
+        res = O.run_qsro(lattice, dims, K, S, sched, ref, V, W, 5, betas, first_sweep=2, replica=0, replay=tnp,
+                         nthreads=NTHREADS)
+        assert np.array_equal(lat.occupancy(), ref)
+        s = stats.cpu().numpy()
+        assert s[0] == res.stats[0] and s[1] == res.stats[1]
+        lat.close()
