@@ -15,7 +15,7 @@ CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(PKG, "libsmcx.so")
 
-SOURCES = ["smcx_kernels.hip", "smcx_coop.hip", "smcx_counts.hip", "smcx_qsro.hip", "smcx_api.cpp"]
+SOURCES = ["smcx_kernels.hip", "smcx_coop.hip", "smcx_counts.hip", "smcx_qsro.hip", "smcx_sites.hip", "smcx_api.cpp"]
 
 # -ffp-contract=off: every binary64 multiply and add of dE is rounded on its
 # own, in the order written, so that trajectories are reproducible bit for bit.

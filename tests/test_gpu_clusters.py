@@ -78,3 +78,24 @@ def test_clusters_per_replica(smcx):
         assert np.array_equal(label.cpu().numpy(), rl) and np.array_equal(size.cpu().numpy(), rs)
         assert int(nc.item()) == rn
     lat.close()
+
+
+@pytest.mark.parametrize("lattice,dims", [(BCC, (32, 8, 8)), (BCC, (33, 9, 17)), (BCC, (31, 7, 24)), (BCC, (65, 8, 2)),
+                                          (FCC, (16, 8, 8)), (FCC, (17, 9, 7)), (FCC, (48, 16, 9)), (FCC, (3, 24, 25))])
+def test_clusters_across_tiles(smcx, lattice, dims):
+    """Lattices of whole and cut tiles; energies drawn at random, so that clusters
+    of every size wind through the tiles and round the periodic faces."""
+    import torch
+    say(f"clusters across tiles lattice={lattice} dims={dims}")
+    N = (2 if lattice == BCC else 4) * int(np.prod(dims))
+    lat = smcx.Lattice(lattice, dims, 4, 2, rand_occ(N, 4, 5))
+    e = np.random.default_rng(N).normal(size=N)
+    e[::97] = np.nan  # never marked
+    eg = torch.from_numpy(e).cuda()
+    for q in (0.05, 0.2, 0.25, 0.35, 0.9):
+        thr = float(np.nanquantile(e, q))
+        label, size, nc = lat.clusters(thr, e=eg)
+        rl, rs, rn = O.clusters(lattice, dims, np.where(np.isnan(e), np.inf, e), thr)
+        assert np.array_equal(label.cpu().numpy(), rl) and np.array_equal(size.cpu().numpy(), rs)
+        assert int(nc.item()) == rn
+    lat.close()
