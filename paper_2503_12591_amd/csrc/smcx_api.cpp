@@ -94,7 +94,7 @@ struct Plan {
     int rlanes;  // lanes per trial (1: k_rows, more: k_rows_coop)
     int row_preset;  // compile-time row window matching the plan, or -1
     LdsLayout rlds;
-    size_t off_rowoff, off_offP_r, off_offB_r;
+    size_t off_rowoff, off_offB_r;
     int64_t total_rowgroups;
     int preset; // compile-time window preset of the stream kernel, or -1
     // resident sweeps: every replica fits a workgroup's LDS; lanes per trial
@@ -105,7 +105,7 @@ struct Plan {
     std::vector<Replica> reps;
     int LP, WY, WZ;
     LdsLayout lds;
-    size_t off_reps, off_origins, off_tileoff, off_offP, off_offB, off_pd, off_D, off_Q, off_V, off_misc, off_slots, off_pad, total;
+    size_t off_reps, off_origins, off_tileoff, off_offB, off_pd, off_D, off_Q, off_V, off_misc, off_slots, off_pad, total;
     // qSRO model: affected-set and neighbour tables, V, W, Z
     size_t off_qaff, off_qnbr, off_qV, off_qW, off_qZ, off_qG, off_qslots;
     int n_origins;
@@ -293,7 +293,7 @@ int make_plan(const smcx_desc* d, Plan& P)
     if (P.LP > 4096) return fail(SMCX_E_UNSUPPORTED, "tile window rows longer than 4096 bytes; use a smaller tile");
     const int64_t win = (int64_t)P.LP * P.WY * P.WZ;
     if (win > 160 * 1024) return fail(SMCX_E_UNSUPPORTED, "tile window does not fit in LDS; use a smaller tile");
-    P.lds = lds_layout(P.lattice, P.K, P.S, P.Z1, P.sumZ, (int)win, P.nbuf);
+    P.lds = lds_layout(P.lattice, P.K, P.S, P.Z1, (int)win, P.nbuf);
     if (P.lds.total > 160 * 1024) return fail(SMCX_E_UNSUPPORTED, "tile window and tables exceed 160 KiB of LDS");
     const int64_t max_off = 2LL * P.LP * P.WY + 2LL * P.LP + 2 * P.m + 4;
     if (max_off > 32767) return fail(SMCX_E_UNSUPPORTED, "LDS offsets exceed 16 bits; use a smaller tile");
@@ -341,11 +341,9 @@ int make_plan(const smcx_desc* d, Plan& P)
         // score: busy lanes per block x waves per CU (12 make up for latency)
         // x a penalty when a single workgroup per CU leaves its staging
         // exposed x a small one for the 128-byte pitch
-        const int tables = lds_layout(P.lattice, P.K, P.S, P.Z1, P.sumZ, 0, 1).total;
+        const int tables = lds_layout(P.lattice, P.K, P.S, P.Z1, 0, 1).total;
         double best_score = 0.0;
         int best_lanes = 0, best_win = 0, best_prow = 0, best[4] = {0, 0, 0, 0};
-        // FCC partners count through a table of window offsets, which holds one
-        // column pitch; BCC partners derive theirs per replica
         P.rows_mixed = !same_m;
         // Short rows (fewer cells than a wave has lanes) put several cell
         // rows in one wave; their sites sit ell pitches apart in y and ell
@@ -368,7 +366,7 @@ int make_plan(const smcx_desc* d, Plan& P)
                 ell_lo = std::min(ell_lo, e);
                 ell_hi = std::max(ell_hi, e);
             }
-        if ((same_cp || P.lattice == SMCX_BCC) && ncx <= kMaxRowBlock)
+        if (ncx <= kMaxRowBlock)
           for (int prow : pitches)
             for (int ry : {1, 2, 4, 8, 16})
                 for (int rz : {1, 2, 4, 8, 16}) {
@@ -377,10 +375,7 @@ int make_plan(const smcx_desc* d, Plan& P)
                     int wy = 0, wz = 0;
                     const bool fits = rows_fit(ry, rz, wy, wz);
                     const int winb = prow * wy * wz;
-                    // FCC partners count through a table of 16-bit window offsets
-                    if (!fits || (P.lattice == SMCX_FCC &&
-                                  2LL * prow * wy + 2LL * prow + (P.m + 1) * (int64_t)P.reps[0].cp > 32767))
-                        continue;
+                    if (!fits) continue;
                     const int lds = tables + ((winb + 15) & ~15);
                     if (lds > 160 * 1024) continue;
                     const int block = (lanes + 63) / 64 * 64;
@@ -452,7 +447,7 @@ int make_plan(const smcx_desc* d, Plan& P)
             P.rWY = best[2];
             P.rWZ = best[3];
             P.rlds = P.rlanes > 1 ? coop_layout(P.K, P.S, P.m * P.Z1, 0, best_win)
-                                  : lds_layout(P.lattice, P.K, P.S, P.Z1, P.sumZ, best_win, 1);
+                                  : lds_layout(P.lattice, P.K, P.S, P.Z1, best_win, 1);
             P.row_preset = -1;
             // presets assume no partner has images in other shells
             bool images = false;
@@ -530,7 +525,6 @@ int make_plan(const smcx_desc* d, Plan& P)
         for (int a = 0; a < 3; ++a) P.n_origins += (int)R.origin[a].size();
     P.off_origins = o; o = align256(o + sizeof(int32_t) * P.n_origins);
     P.off_tileoff = o; o = align256(o + sizeof(int64_t) * (P.R + 1));
-    P.off_offP = o; o = align256(o + sizeof(int16_t) * P.m * P.Z1 * P.sumZ);
     P.off_offB = o; o = align256(o + sizeof(int32_t) * P.m * P.Z1);
     P.off_pd = o; o = align256(o + 4 * P.m * P.Z1);
     P.off_D = o; o = align256(o + sizeof(double) * P.K * P.K * P.S * P.K);
@@ -546,7 +540,6 @@ int make_plan(const smcx_desc* d, Plan& P)
     P.off_qG = o; o = align256(o + sizeof(double) * qsro_products(P.K, P.S));
     P.off_qslots = o; o = align256(o + sizeof(int64_t) * 3 * kQsroGrid);
     P.off_rowoff = o; o = align256(o + sizeof(int64_t) * (P.R + 1));
-    P.off_offP_r = o; o = align256(o + sizeof(int16_t) * P.m * P.Z1 * P.sumZ);
     P.off_offB_r = o; o = align256(o + sizeof(int32_t) * P.m * P.Z1);
     P.off_pad = o;
     P.total_tiles = 0;
@@ -609,7 +602,6 @@ SweepArgs base_args(smcx_lattice* h)
     a.reps = (const RepDev*)(h->ws + P.off_reps);
     a.origins = (const int32_t*)(h->ws + P.off_origins);
     a.tile_off = (const int64_t*)(h->ws + P.off_tileoff);
-    a.offP = (const int16_t*)(h->ws + P.off_offP);
     a.offB = (const int32_t*)(h->ws + P.off_offB);
     a.pdisp = (const int8_t*)(h->ws + P.off_pd);
     a.Dtab = (const double*)(h->ws + P.off_D);
@@ -630,7 +622,6 @@ SweepArgs base_args(smcx_lattice* h)
     a.WZ = P.WZ;
     a.lds_d = P.lds.d_off;
     a.lds_q = P.lds.q_off;
-    a.lds_offp = P.lds.offp_off;
     a.lds_offb = P.lds.offb_off;
     a.lds_pd = P.lds.pd_off;
     a.lds_win = P.lds.win_off;
@@ -650,7 +641,6 @@ SweepArgs row_args(smcx_lattice* h)
     const Plan& P = h->P;
     SweepArgs a = base_args(h);
     a.tile_off = (const int64_t*)(h->ws + P.off_rowoff);
-    a.offP = (const int16_t*)(h->ws + P.off_offP_r);
     a.offB = (const int32_t*)(h->ws + P.off_offB_r);
     for (int i = 0; i < 3; ++i) a.T[i] = P.RT[i];
     a.LP = P.rLP;
@@ -658,7 +648,6 @@ SweepArgs row_args(smcx_lattice* h)
     a.WZ = P.rWZ;
     a.lds_d = P.rlds.d_off;
     a.lds_q = P.rlds.q_off;
-    a.lds_offp = P.rlds.offp_off;
     a.lds_offb = P.rlds.offb_off;
     a.lds_pd = P.rlds.pd_off;
     a.lds_win = P.rlds.win_off;
@@ -850,7 +839,6 @@ int smcx_lattice_init(smcx_lattice** out, const smcx_desc* desc, uint8_t* occ_de
         tile_off[r + 1] = tile_off[r] + R.ntiles;
     }
     const Geometry& G = kGeom[P.lattice];
-    std::vector<int16_t> offP((size_t)P.m * P.Z1 * P.sumZ), offP_r(offP.size());
     std::vector<int32_t> offB((size_t)P.m * P.Z1), offB_r(offB.size());
     std::vector<int8_t> pd((size_t)4 * P.m * P.Z1);
     for (int b = 0; b < P.m; ++b)
@@ -861,15 +849,6 @@ int smcx_lattice_init(smcx_lattice** out, const smcx_desc* desc, uint8_t* occ_de
             const Nb nb = nb_of(G, b, d1[0], d1[1], d1[2]);
             int8_t* q = &pd[(b * P.Z1 + k) * 4];
             q[0] = (int8_t)nb.dx; q[1] = (int8_t)nb.dy; q[2] = (int8_t)nb.dz; q[3] = (int8_t)nb.bt;
-            int j = 0;
-            for (int s = 0; s < P.S; ++s)
-                for (int n = 0; n < G.Z[s]; ++n, ++j) {
-                    const int vx = d1[0] + G.v[s][n][0], vy = d1[1] + G.v[s][n][1], vz = d1[2] + G.v[s][n][2];
-                    offP[(b * P.Z1 + k) * P.sumZ + j] = (int16_t)lds_offset(P, P.LP, P.WY, b, vx, vy, vz);
-                    if (P.rows)
-                        offP_r[(b * P.Z1 + k) * P.sumZ + j] =
-                            (int16_t)lds_offset_planar(P, P.rLP, P.rWY, P.reps[0].cp, b, vx, vy, vz);
-                }
         }
     std::vector<int64_t> row_off(P.R + 1, 0);
     for (int r = 0; r < P.R; ++r) {
@@ -880,11 +859,9 @@ int smcx_lattice_init(smcx_lattice** out, const smcx_desc* desc, uint8_t* occ_de
     SMCX_HIP(hipMemcpyAsync(h->ws + P.off_reps, reps.data(), sizeof(RepDev) * P.R, hipMemcpyHostToDevice, st));
     SMCX_HIP(hipMemcpyAsync(h->ws + P.off_origins, origins.data(), sizeof(int32_t) * origins.size(), hipMemcpyHostToDevice, st));
     SMCX_HIP(hipMemcpyAsync(h->ws + P.off_tileoff, tile_off.data(), sizeof(int64_t) * tile_off.size(), hipMemcpyHostToDevice, st));
-    SMCX_HIP(hipMemcpyAsync(h->ws + P.off_offP, offP.data(), sizeof(int16_t) * offP.size(), hipMemcpyHostToDevice, st));
     SMCX_HIP(hipMemcpyAsync(h->ws + P.off_offB, offB.data(), sizeof(int32_t) * offB.size(), hipMemcpyHostToDevice, st));
     SMCX_HIP(hipMemcpyAsync(h->ws + P.off_pd, pd.data(), pd.size(), hipMemcpyHostToDevice, st));
     SMCX_HIP(hipMemcpyAsync(h->ws + P.off_rowoff, row_off.data(), sizeof(int64_t) * row_off.size(), hipMemcpyHostToDevice, st));
-    SMCX_HIP(hipMemcpyAsync(h->ws + P.off_offP_r, offP_r.data(), sizeof(int16_t) * offP_r.size(), hipMemcpyHostToDevice, st));
     SMCX_HIP(hipMemcpyAsync(h->ws + P.off_offB_r, offB_r.data(), sizeof(int32_t) * offB_r.size(), hipMemcpyHostToDevice, st));
     {
         // qSRO tables.  Neighbours of a basis-b site, shells in order; the

@@ -114,7 +114,6 @@ struct Lds {
     const int32_t* Q;  // integer dE terms [S][K][K][K], then bias sums [K][K]
     float qscale;      // value of one integer unit (a power of two)
     float qeps;        // bound on |integer dE - binary64 dE| before the float conversion
-    const int16_t* offP;
     const int32_t* offB;
     const int8_t* pd;
 };
@@ -129,7 +128,6 @@ __device__ __forceinline__ Lds lds_ptrs(const SweepArgs& A, uint8_t* smem)
     const int nq = A.S * A.K * A.K * A.K + A.K * A.K;
     l.qscale = __int_as_float(((CI*)A.Qtab)[nq]);
     l.qeps = __int_as_float(((CI*)A.Qtab)[nq + 1]);
-    l.offP = (const int16_t*)(smem + A.lds_offp);
     l.offB = (const int32_t*)(smem + A.lds_offb);
     l.pd = (const int8_t*)(smem + A.lds_pd);
     return l;
@@ -146,11 +144,6 @@ __device__ void load_tables(const SweepArgs& A, uint8_t* smem)
     int32_t* Q = (int32_t*)(smem + A.lds_q);
     const int nQ = nD + A.K * A.K;
     for (int i = threadIdx.x; i < nQ; i += blockDim.x) Q[i] = A.Qtab[i];
-    if constexpr (LAT == SMCX_FCC) {
-        int16_t* P = (int16_t*)(smem + A.lds_offp);
-        const int nP = m * A.Z1 * A.sumZ;
-        for (int i = threadIdx.x; i < nP; i += blockDim.x) P[i] = A.offP[i];
-    }
     int32_t* Bo = (int32_t*)(smem + A.lds_offb);
     int8_t* pd = (int8_t*)(smem + A.lds_pd);
     for (int i = threadIdx.x; i < m * A.Z1; i += blockDim.x) Bo[i] = A.offB[i];

@@ -74,12 +74,6 @@ __device__ __forceinline__ void store_site(uint8_t* pad, const RepDev& rep, int 
         }
 }
 
-// Packed neighbour counters of a basis-B site at LDS byte `base`: A[s] gets
-// 1 << (8 * species) per neighbour of shell s.  Offsets are compile-time
-// displacements times the launch-uniform window pitches.
-// The reads are rebased at the most negative offset (a window's neighbours lie
-// within two conventional cells on every axis), so that every per-neighbour
-// offset is a non-negative constant that fits the LDS instruction's immediate.
 // Smallest cell offset on each axis and smallest basis index over the
 // neighbours (all shells) of a basis-b site.
 constexpr Nb min_components(const Geometry& G, int b)
@@ -96,49 +90,12 @@ constexpr Nb min_components(const Geometry& G, int b)
     return r;
 }
 
-template <int LAT, int B, bool PLANAR, typename CT>
-__device__ __forceinline__ void count_uniform(const uint8_t* win, int base, int LP, int PL, int CP, int S,
-                                              CT (&A)[kMaxShells])
-{
-    constexpr Geometry G = kGeom[LAT];
-    // interleaved rows: x step m, basis step 1; basis-planar rows: x step 1, basis step CP
-    const int XS = PLANAR ? 1 : G.m, BS = PLANAR ? CP : 1;
-    // rebase at the smallest neighbour component on every axis (and basis):
-    // the window holds every neighbour, so base + lo stays inside it
-    constexpr Nb mn = min_components(G, B);
-    const int lo = mn.dz * PL + mn.dy * LP + XS * mn.dx + BS * (mn.bt - B);
-    // opaque to the compiler, so it keeps this base and every read's offset
-    // (non-negative, below 64 KiB) goes into the instruction's offset field
-    // instead of a per-read address add
-    int rb = base + lo;
-    asm("" : "+v"(rb));
-    const uint8_t* w = win + rb;
-    // all reads of a shell are issued before its counter chain starts, so
-    // their LDS latencies overlap
-#pragma unroll
-    for (int s = 0; s < kMaxShells; ++s) {
-        CT acc = 0;
-        if (s < S) {
-            uint32_t v[kMaxZ];
-#pragma unroll
-            for (int n = 0; n < G.Z[s]; ++n) {
-                const Nb nb = nb_of(G, B, G.v[s][n][0], G.v[s][n][1], G.v[s][n][2]);
-                const int off = nb.dz * PL + nb.dy * LP + XS * nb.dx + BS * (nb.bt - B);
-                v[n] = w[off - lo];
-            }
-            const int Z4 = G.Z[s] & ~3;
-#pragma unroll
-            for (int n = 0; n < Z4; n += 4) acc = shl1_add4(v[n], v[n + 1], v[n + 2], v[n + 3], acc);
-#pragma unroll
-            for (int n = Z4; n < G.Z[s]; ++n) acc = shl1_add(v[n], acc);
-        }
-        A[s] = acc;
-    }
-}
-
 // Both sites of a BCC trial (active site of basis B at `ba`, its partner of
-// the other basis at `bb`): the same counts as two count_uniform calls, with
-// the window reads software-pipelined in chunks of up to CHUNK neighbours of
+// the other basis at `bb`): packed neighbour counters, A[s] and Bc[s] get 1 <<
+// (F * species) per neighbour of shell s.  The reads are rebased at the most
+// negative offset (a window's neighbours lie within two conventional cells on
+// every axis), so that with compile-time pitches every offset is a non-negative
+// constant in the LDS instruction; they are software-pipelined in chunks of up to CHUNK neighbours of
 // one (site, shell): the reads of chunk g + 1 are issued before chunk g's
 // counter adds (scheduling barriers keep that order), so LDS latency
 // overlaps the adds.  Row windows (compile-time pitches in the benchmark's
@@ -233,22 +190,81 @@ __device__ __forceinline__ void count_pair(const uint8_t* win, int ba, int bb, i
     }
 }
 
-// Same for the partner of an FCC site: per-lane offsets (relative to the
-// active site) from an LDS table, since the partner basis varies per lane.
-template <int LAT, typename CT>
-__device__ __forceinline__ void count_table(const uint8_t* win, int base, const int16_t* offs, int S,
-                                            CT (&A)[kMaxShells])
+// Packed neighbour counters of one FCC site, given the window byte `base[t]`
+// that neighbour vectors of parity class t count from (a class is the basis
+// they lead to from basis 0; each odd component carries into the next cell
+// exactly when the site's own coordinate is odd, so a site of any basis needs
+// one base per class and compile-time displacements from there).  A shell's
+// vectors go by the window rows they lie in: one address per row, x in the
+// reads' offset fields.  Bound by VALU issue and LDS reads; against a table of
+// 16-bit offsets per (basis, partner, vector) in LDS, which cost an address
+// read per neighbour: FCC 200^3 (5 species, 4 shells) 1694 -> 1265 us per
+// sweep, 400^3 8089 -> 6950, 300x310x290 (4 species) 7234 -> 6415.
+struct ShellRows {
+    int n[kMaxZ];        // vectors of the shell in order of their rows
+    bool first[kMaxZ];   // the first of its row
+};
+constexpr ShellRows make_shell_rows(const Geometry& G, int s)
 {
-    constexpr Geometry G = kGeom[LAT];
-    int j = 0;
+    ShellRows R{};
+    auto key = [&G, s](int i) {
+        const Nb nb = nb_of(G, 0, G.v[s][i][0], G.v[s][i][1], G.v[s][i][2]);
+        return (nb.bt * 8 + nb.dz + 4) * 8 + nb.dy + 4;
+    };
+    for (int i = 0; i < G.Z[s]; ++i) {
+        int k = i;
+        while (k > 0 && key(R.n[k - 1]) > key(i)) {
+            R.n[k] = R.n[k - 1];
+            --k;
+        }
+        R.n[k] = i;
+    }
+    for (int k = 0; k < G.Z[s]; ++k) R.first[k] = k == 0 || key(R.n[k - 1]) != key(R.n[k]);
+    return R;
+}
+
+// Base per class of an FCC site of basis c at window byte `site`; X, LP, PL,
+// BS: window steps of a cell along x, y and z and of a basis site.
+__device__ __forceinline__ void class_bases(int site, int c, int X, int LP, int PL, int BS, int (&base)[4])
+{
+    // class 1 is odd in x and y, 2 in x and z, 3 in y and z
+    const int fx = c == 1 || c == 2 ? X : 0, fy = c & 1 ? LP - 2 * BS : 0, fz = c & 2 ? PL - 4 * BS : 0;
+    base[0] = site;
+    base[1] = site + fx + fy;
+    base[2] = site + fx + fz;
+    base[3] = site + fy + fz;
+}
+
+template <bool PLANAR, typename CT>
+__device__ __forceinline__ void count_classes(const uint8_t* win, const int (&base)[4], int LP, int PL, int BS, int S,
+                                              CT (&A)[kMaxShells])
+{
+    constexpr Geometry G = kGeom[SMCX_FCC];
+    constexpr int X = PLANAR ? 1 : G.m;
 #pragma unroll
     for (int s = 0; s < kMaxShells; ++s) {
         CT acc = 0;
         if (s < S) {
+            constexpr ShellRows RW[kMaxShells] = {make_shell_rows(G, 0), make_shell_rows(G, 1), make_shell_rows(G, 2),
+                                                  make_shell_rows(G, 3)};
+            uint32_t v[kMaxZ];
+            int row = 0;
 #pragma unroll
-            for (int n = 0; n < G.Z[s]; ++n) acc = shl1_add(win[base + offs[j + n]], acc);
+            for (int k = 0; k < G.Z[s]; ++k) {
+                const int* d = G.v[s][RW[s].n[k]];
+                const Nb nb = nb_of(G, 0, d[0], d[1], d[2]);
+                if (RW[s].first[k]) {
+                    row = base[nb.bt] + (nb.dz * PL + nb.dy * LP + nb.bt * BS - 2 * X);
+                    asm("" : "+v"(row));
+                }
+                v[k] = win[row + X * (nb.dx + 2)];
+            }
+            static_assert(G.Z[0] % 2 == 0 && G.Z[1] % 2 == 0 && G.Z[2] % 2 == 0 && G.Z[3] % 2 == 0, "pairs");
+            const int Z4 = G.Z[s] & ~3;
+#pragma unroll
+            for (int n = 0; n < Z4; n += 4) acc = shl1_add4(v[n], v[n + 1], v[n + 2], v[n + 3], acc);
+            if (G.Z[s] & 2) acc = shl1_add2(v[Z4], v[Z4 + 1], acc);
         }
-        j += G.Z[s];
         A[s] = acc;
     }
 }
@@ -409,12 +425,14 @@ __device__ __forceinline__ void trial_read(const SweepArgs& A, const RepDev& rep
     (void)w3;
     const int k = (int)__umulhi(w0, (uint32_t)Z1);
     const int p8 = win[la];
-    int offb;
-    if constexpr (Geo::own_cp && LAT == SMCX_BCC) {
-        // the partner's window offset from its cell displacement and this
-        // replica's column pitch (row windows of replicas of different widths)
-        const int8_t* q = T.pd + (B * Z1 + k) * 4;
-        offb = q[2] * PL + q[1] * LP + q[0] + (q[3] - B) * Geo::CP(rep);
+    int offb, bt = 1 - B;  // the partner's window offset and basis
+    if constexpr (Geo::own_cp || LAT == SMCX_FCC) {
+        // from its cell displacement (row windows: and this replica's column
+        // pitch, as replicas may differ in width)
+        const int d = *(const int32_t*)(T.pd + (B * Z1 + k) * 4);
+        bt = d >> 24;
+        offb = (int)(int8_t)(d >> 16) * PL + (int)(int8_t)(d >> 8) * LP + (int)(int8_t)d * (PLANAR ? 1 : m) +
+               (bt - B) * (PLANAR ? Geo::CP(rep) : 1);
     } else {
         offb = T.offB[B * Z1 + k];
     }
@@ -437,8 +455,13 @@ __device__ __forceinline__ void trial_read(const SweepArgs& A, const RepDev& rep
         // the partner of a BCC site always sits on the other sublattice
         count_pair<LAT, B, PLANAR, CT, Geo::rows ? 4 : kMaxZ>(win, la, la + offb, LP, PL, Geo::CP(rep), S, L.Ca, L.Cb);
     } else {
-        count_uniform<LAT, B, PLANAR, CT>(win, la, LP, PL, Geo::CP(rep), S, L.Ca);
-        count_table<LAT, CT>(win, la, T.offP + (B * Z1 + k) * A.sumZ, S, L.Cb);
+        constexpr int X = PLANAR ? 1 : m;
+        const int BS = PLANAR ? Geo::CP(rep) : 1;
+        int base[4];
+        class_bases(la, B, X, LP, PL, BS, base);
+        count_classes<PLANAR, CT>(win, base, LP, PL, BS, S, L.Ca);
+        class_bases(la + offb, bt, X, LP, PL, BS, base);
+        count_classes<PLANAR, CT>(win, base, LP, PL, BS, S, L.Cb);
     }
 }
 
