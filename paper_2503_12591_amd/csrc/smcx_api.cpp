@@ -6,6 +6,7 @@
 #include <algorithm>
 #include <array>
 #include <cmath>
+#include <limits>
 #include <cstdio>
 #include <cstring>
 #include <mutex>
@@ -338,9 +339,24 @@ int make_plan(const smcx_desc* d, Plan& P)
             }
             return fits;
         };
+        // compile-time window; presets assume no partner has images in other shells
+        bool images = false;
+        for (const Replica& R : P.reps)
+            for (int s = 0; s < kMaxShells; ++s)
+                for (int k = 0; k < P.Z1; ++k) images |= R.mult[s][k] != (s == 0 ? 1 : 0);
+        auto preset_of = [&](int ry, int rz, int prow, int wy, int wz) {
+            for (int pi = 0; pi < kNumRowPresets; ++pi) {
+                const RowPreset& q = kRowPresets[pi];
+                if (same_cp && !images && q.lattice == P.lattice && q.K == P.K && q.S == P.S && q.cp == P.reps[0].cp &&
+                    q.LP == prow && q.WY == wy && q.WZ == wz && q.rt0 == ncx && q.rt1 == ry && q.rt2 == rz)
+                    return pi;
+            }
+            return -1;
+        };
         // score: busy lanes per block x waves per CU (12 make up for latency)
         // x a penalty when a single workgroup per CU leaves its staging
-        // exposed x a small one for the 128-byte pitch
+        // exposed x a small one for the 128-byte pitch x a bonus for windows
+        // with a kernel of their own (BCC 800^3, 950 us a launch against 1095)
         const int tables = lds_layout(P.lattice, P.K, P.S, P.Z1, 0, 1).total;
         double best_score = 0.0;
         int best_lanes = 0, best_win = 0, best_prow = 0, best[4] = {0, 0, 0, 0};
@@ -388,7 +404,7 @@ int make_plan(const smcx_desc* d, Plan& P)
                                                 : 1;
                     const double banks = short_rows ? 1.0 / (0.75 + 0.25 * ways) : (prow % 256 ? 0.98 : 1.0);
                     const double score = (double)lanes / block * std::min(1.0, wgs * waves / 12.0) *
-                                         (wgs == 1 ? 0.88 : 1.0) * banks;
+                                         (wgs == 1 ? 0.88 : 1.0) * banks * (preset_of(ry, rz, prow, wy, wz) >= 0 ? 1.1 : 1.0);
                     if (score > best_score + 1e-12 || (std::fabs(score - best_score) <= 1e-12 && winb < best_win)) {
                         best_score = score;
                         best_lanes = lanes;
@@ -448,18 +464,7 @@ int make_plan(const smcx_desc* d, Plan& P)
             P.rWZ = best[3];
             P.rlds = P.rlanes > 1 ? coop_layout(P.K, P.S, P.m * P.Z1, 0, best_win)
                                   : lds_layout(P.lattice, P.K, P.S, P.Z1, best_win, 1);
-            P.row_preset = -1;
-            // presets assume no partner has images in other shells
-            bool images = false;
-            for (const Replica& R : P.reps)
-                for (int s = 0; s < kMaxShells; ++s)
-                    for (int k = 0; k < P.Z1; ++k) images |= R.mult[s][k] != (s == 0 ? 1 : 0);
-            for (int pi = 0; pi < kNumRowPresets; ++pi) {
-                const RowPreset& q = kRowPresets[pi];
-                if (P.rlanes == 1 && same_cp && !images && q.lattice == P.lattice && q.K == P.K && q.S == P.S && q.cp == P.reps[0].cp && q.LP == P.rLP &&
-                    q.WY == P.rWY && q.WZ == P.rWZ && q.rt0 == P.RT[0] && q.rt1 == P.RT[1] && q.rt2 == P.RT[2])
-                    P.row_preset = pi;
-            }
+            P.row_preset = P.rlanes == 1 ? preset_of(best[0], best[1], best_prow, best[2], best[3]) : -1;
             P.total_rowgroups = 0;
             for (Replica& R : P.reps) {
                 R.rg[0] = ((int)R.edges[1].size() + P.RT[1] - 1) / P.RT[1];
@@ -620,8 +625,6 @@ SweepArgs base_args(smcx_lattice* h)
     a.LP = P.LP;
     a.WY = P.WY;
     a.WZ = P.WZ;
-    a.lds_d = P.lds.d_off;
-    a.lds_q = P.lds.q_off;
     a.lds_offb = P.lds.offb_off;
     a.lds_pd = P.lds.pd_off;
     a.lds_win = P.lds.win_off;
@@ -646,8 +649,6 @@ SweepArgs row_args(smcx_lattice* h)
     a.LP = P.rLP;
     a.WY = P.rWY;
     a.WZ = P.rWZ;
-    a.lds_d = P.rlds.d_off;
-    a.lds_q = P.rlds.q_off;
     a.lds_offb = P.rlds.offb_off;
     a.lds_pd = P.rlds.pd_off;
     a.lds_win = P.rlds.win_off;
@@ -730,7 +731,6 @@ int persistent_launch(smcx_lattice* h, SweepArgs a, int64_t* stats_dev, hipStrea
     a.stats = stats_dev;
     a.stat_parts = 1;
     a.stat_stride = 3;
-    a.lds_q = P.res.q_off;
     a.lds_pd = P.res.pd_off;
     a.lds_offb = P.res.offb_off;
     a.lds_win = P.res.win_off;
@@ -1043,30 +1043,40 @@ int smcx_set_epi(smcx_lattice* h, const double* V, void* stream)
                 for (int t = 0; t < K; ++t)
                     h->Dhost[((s * K + t) * K + p) * K + q] = V[(s * K + q) * K + t] - V[(s * K + p) * K + t];
     // Integer screen of dE (the kernels' first test): every D rounded to a
-    // multiple of 2^-k, the largest k with all |D| 2^k below 2^23 (24-bit
-    // signed operands), plus for each (p, q) the sum of half * those integers
-    // (the counters' field bias), modulo 2^32.  A trial's integer sum is then
-    // within sum_t |c_t| 2^-(k+1) <= (sum_s Z_s) 2^-k of sum c D, which is
-    // within a few ulps of the binary64 dE; qeps bounds both.
+    // multiple of 2^-k, the largest k with all |D| 2^k below 2^23 and so too the
+    // terms D_t - D_last (24-bit signed operands), plus for each (p, q) the sum of
+    // half * those terms (the counters' field bias), modulo 2^32.  A trial's
+    // integer sum is then within sum_t |c_t| 2^-(k+1) <= (sum_s Z_s) 2^-k of
+    // sum c D, which is within a few ulps of the binary64 dE; qeps bounds both.
     {
-        double maxD = 0.0;
+        const int KP = counter_species(K), KT = KP - 1, pitch = qtab_pitch(KP, S);
+        auto Dof = [&](int s, int t, int p, int q) { return t < K ? h->Dhost[((s * K + t) * K + p) * K + q] : 0.0; };
+        double maxD = 0.0, maxT = 0.0;
         for (double v : h->Dhost) maxD = std::max(maxD, std::fabs(v));
+        for (int s = 0; s < S; ++s)
+            for (int t = 0; t < KT; ++t)
+                for (int p = 0; p < K; ++p)
+                    for (int q = 0; q < K; ++q) maxT = std::max(maxT, std::fabs(Dof(s, t, p, q) - Dof(s, KT, p, q)));
+        maxT = std::min(std::max(maxT, maxD), std::numeric_limits<double>::max());
         int kq = 0;
-        if (maxD > 0.0) {
-            kq = (int)std::floor(std::log2(8388607.0 / maxD));
-            while (std::ldexp(maxD, kq) > 8388607.0) --kq;
+        if (maxT > 0.0) {
+            kq = (int)std::floor(std::log2(8388606.0 / maxT));
+            while (std::ldexp(maxT, kq) > 8388606.0) --kq;  // both of a term's roundings stay below 2^23
             kq = std::max(-100, std::min(100, kq));
         }
-        const int half = K == 5 ? 32 : 128;
-        const size_t nD = h->Dhost.size();
+        const int half = field_bits_of(K) == 6 ? 32 : 128;
         h->Qhost.assign((size_t)qtab_entries(K, S) + 2, 0);
-        for (size_t i = 0; i < nD; ++i) h->Qhost[i] = (int32_t)std::nearbyint(std::ldexp(h->Dhost[i], kq));
+        auto Qof = [&](int s, int t, int p, int q) { return (int32_t)std::nearbyint(std::ldexp(Dof(s, t, p, q), kq)); };
         for (int p = 0; p < K; ++p)
             for (int q = 0; q < K; ++q) {
                 int64_t b = 0;
                 for (int s = 0; s < S; ++s)
-                    for (int t = 0; t < K; ++t) b += (int64_t)half * h->Qhost[((s * K + t) * K + p) * K + q];
-                h->Qhost[nD + p * K + q] = (int32_t)(uint32_t)(uint64_t)b;
+                    for (int t = 0; t < KT; ++t) {
+                        const int32_t v = Qof(s, t, p, q) - Qof(s, KT, p, q);
+                        h->Qhost[(p * K + q) * pitch + s * KT + t] = v;
+                        b += (int64_t)half * v;
+                    }
+                h->Qhost[(p * K + q) * pitch + S * KT] = (int32_t)(uint32_t)(uint64_t)b;
             }
         int sumZ = 0;
         for (int s = 0; s < S; ++s) sumZ += kGeom[P.lattice].Z[s];

@@ -155,7 +155,7 @@ constexpr uint32_t kSiteMask = (1u << 18) - 1, kSiteActive = 1u << 18;
 // holds: +1 within the halo's width of the low face, -1 of the high face.
 __device__ __forceinline__ uint32_t image_code(int c, int L) { return c < kHalo ? 1u : (c >= L - kHalo ? 3u : 0u); }
 
-template <int LAT, int E, int KK, int SS, int G>
+template <int LAT, int E, int SS, int G>
 struct Coop {
     using EN = Enc<E>;
     using CT = typename EN::T;
@@ -163,8 +163,9 @@ struct Coop {
     static constexpr int m = GM.m, Z1 = GM.Z[0], H = G / 2;
     static constexpr CoopSlots<H> SL = make_coop_slots<LAT, H>();
     static constexpr int NS = coop_slots_of(SL.s, SL.n, SS ? SS : kMaxShells);
-    // terms of dE: TW species by SW shells at a time over the lanes
-    static constexpr int TW = G < 4 ? G : 4, SW = G / TW;
+    // terms of dE: SW shells by TW species at a time over the lanes (shells
+    // first: a lane's shell is one pick for all its species' fields)
+    static constexpr int SP = SS == 1 ? 1 : (SS == 2 ? 2 : 4), SW = G < SP ? G : SP, TW = G / SW;
 
     int j, side, jj;      // lane in the group, 0: active site / 1: partner, lane in the half
     int LP, PL, CP;       // window pitches: row, plane, basis column
@@ -277,12 +278,11 @@ struct Coop {
         __builtin_amdgcn_sched_barrier(0);
         const int oth = (int)other_half<G>((uint32_t)own);
         const int p8 = side ? oth : own, q8 = side ? own : oth;
-        const int p = min(species_of(p8, EN::F), K - 1), q = min(species_of(q8, EN::F), K - 1);
-        const int pq = p * K + q, KK2 = K * K;
-        const int tj = j % TW, sj = j / TW;
-        constexpr int NT = (EN::KP + TW - 1) / TW, NSH = (kMaxShells + SW - 1) / SW;
-        const int32_t* Qp = Q + pq;
-        const int32_t qbias = Q[S * K * KK2 + pq];
+        const int pair = species_pair<E>(p8, q8, K);
+        const int tj = TW > 1 ? j % TW : 0, sj = j / TW;
+        constexpr int NT = (EN::KT + TW - 1) / TW, NSH = (kMaxShells + SW - 1) / SW;
+        const int32_t* Qp = qtab_row<E>(Q, pair, S);
+        const int32_t qbias = Qp[S * EN::KT];
         int32_t qv[NSH][NT];
 #pragma unroll
         for (int a = 0; a < NSH; ++a)
@@ -290,9 +290,9 @@ struct Coop {
             for (int t = 0; t < NT; ++t) {
                 const int s = a * SW + sj, tt = t * TW + tj;
                 qv[a][t] = 0;
-                if (a * SW < S && t * TW < K) {
-                    const bool in = s < S && tt < K;
-                    const int32_t x = Qp[in ? (s * K + tt) * KK2 : 0];
+                if (a * SW < S) {
+                    const bool in = ((a + 1) * SW <= S || s < S) && ((t + 1) * TW <= EN::KT || tt < EN::KT);
+                    const int32_t x = Qp[in ? s * EN::KT + tt : 0];
                     qv[a][t] = in ? x : 0;
                 }
             }
@@ -328,12 +328,12 @@ struct Coop {
             }
 #pragma unroll
             for (int t = 0; t < NT; ++t)
-                if (t * TW < K) part += (uint32_t)__mul24((int)((w >> (EN::F * (t * TW + tj))) & EN::mask), qv[a][t]);
+                part += (uint32_t)__mul24((int)((w >> ((EN::F * (t * TW + tj)) & (8 * sizeof(CT) - 1))) & EN::mask), qv[a][t]);
         }
         const uint32_t qacc = group_sum<G, uint32_t>(part);
         int f = 0;
         if (p8 != q8) {
-            f = metropolis<E>(qacc, qscale, qeps, D + pq, dsh[0], dsh[1], dsh[2], dsh[3], K, S, beta, d.w1, d.w2);
+            f = metropolis<E>(qacc, qscale, qeps, D, pair, dsh[0], dsh[1], dsh[2], dsh[3], K, S, beta, d.w1, d.w2);
             if (f & 2) on_tie(f & 1);
         }
         if (f & 1) {
@@ -390,22 +390,22 @@ __device__ __forceinline__ void step_barrier(bool waves)
 // ---------------------------------------------------------------------------
 constexpr int kResidentBlock = 1024;
 
-template <int LAT, int E, int KK, int SS, int G>
+template <int LAT, int E, int SS, int G>
 __global__ __launch_bounds__(kResidentBlock) void k_resident(SweepArgs A)
 {
-    using CO = Coop<LAT, E, KK, SS, G>;
+    using CO = Coop<LAT, E, SS, G>;
     constexpr int m = CO::m, F = Enc<E>::F;
     extern __shared__ __align__(16) uint8_t smem[];
     const int r = blockIdx.x;
     const RepDev& rep = rep_of(A, r);
-    const int K = KK ? KK : A.K, S = SS ? SS : A.S;
+    const int K = A.K, S = SS ? SS : A.S;
     const int Lx = scalar(rep.L[0]), Ly = scalar(rep.L[1]), Lz = scalar(rep.L[2]);
     const int CP = Lx + 2 * kHalo, LP = m * CP, WY = Ly + 2 * kHalo, WZ = Lz + 2 * kHalo, PL = LP * WY;
-    int32_t* Q = (int32_t*)(smem + A.lds_q);
+    int32_t* Q = (int32_t*)smem;
     int32_t* pdt = (int32_t*)(smem + A.lds_pd);
     int32_t* org = (int32_t*)(smem + A.lds_offb);
     uint8_t* win = smem + A.lds_win;
-    const int nQ = S * K * K * K + K * K;
+    const int nQ = qtab_entries(K, S);
     for (int i = threadIdx.x; i < nQ; i += blockDim.x) Q[i] = A.Qtab[i];
     for (int i = threadIdx.x; i < m * CO::Z1; i += blockDim.x) pdt[i] = ((const int32_t*)A.pdisp)[i];
     const int ncx = scalar(rep.nc[0]), ncy = scalar(rep.nc[1]), ncz = scalar(rep.nc[2]), ncell = ncx * ncy * ncz;
@@ -561,18 +561,18 @@ __global__ __launch_bounds__(kResidentBlock) void k_resident(SweepArgs A)
 // trial; 24 us with one lane) 2.8 are an empty launch, 4.8 the chain of
 // argument, table and window reads and the write-back, 0.54 each mini-step.
 // ---------------------------------------------------------------------------
-template <int LAT, int E, int KK, int SS, int G>
+template <int LAT, int E, int SS, int G>
 __global__ __launch_bounds__(kMaxCoopRowBlock) void k_rows_coop(SweepArgs A)
 {
-    using CO = Coop<LAT, E, KK, SS, G>;
-    using Geo = GeoRow<KK, SS>;
+    using CO = Coop<LAT, E, SS, G>;
+    using Geo = GeoRow<SS>;
     constexpr int m = CO::m;
     extern __shared__ __align__(16) uint8_t smem[];
-    const int K = KK ? KK : A.K, S = SS ? SS : A.S;
-    int32_t* Q = (int32_t*)(smem + A.lds_q);
+    const int K = A.K, S = SS ? SS : A.S;
+    int32_t* Q = (int32_t*)smem;
     int32_t* pdt = (int32_t*)(smem + A.lds_pd);
     uint8_t* win = smem + A.lds_win;
-    const int nQ = S * K * K * K + K * K;
+    const int nQ = qtab_entries(K, S);
     for (int i = threadIdx.x; i < nQ; i += blockDim.x) Q[i] = A.Qtab[i];
     for (int i = threadIdx.x; i < m * CO::Z1; i += blockDim.x) pdt[i] = ((const int32_t*)A.pdisp)[i];
     const float qscale = __int_as_float(ld_const(A.Qtab, nQ)), qeps = __int_as_float(ld_const(A.Qtab, nQ + 1));
@@ -734,34 +734,31 @@ __global__ __launch_bounds__(kMaxCoopRowBlock) void k_rows_coop(SweepArgs A)
     flush_stats_block(A, r_stats, st);
 }
 
-// Kernel with compile-time species / shell counts for the 4-species BCC and
-// 5-species FCC alloys with 4 or 2 shells, runtime counts otherwise.
-template <bool ROWS, int LAT, int E, int KK, int SS, int G>
-static const void* coop_kernel_ks()
+// Kernels with a compile-time shell count for 32-bit counters (up to 6
+// species), a runtime one for 64-bit counters.
+template <bool ROWS, int LAT, int E, int SS, int G>
+static const void* coop_kernel_s()
 {
-    if constexpr (ROWS) return (const void*)k_rows_coop<LAT, E, KK, SS, G>;
-    else return (const void*)k_resident<LAT, E, KK, SS, G>;
+    if constexpr (ROWS) return (const void*)k_rows_coop<LAT, E, SS, G>;
+    else return (const void*)k_resident<LAT, E, SS, G>;
 }
 
 template <bool ROWS, int LAT, int E, int G>
-static const void* coop_kernel_e(int K, int S)
+static const void* coop_kernel_e(int S)
 {
-    if constexpr (LAT == SMCX_BCC && E == 1) {
-        if (K == 4 && S == 4) return coop_kernel_ks<ROWS, LAT, E, 4, 4, G>();
-        if (K == 4 && S == 2) return coop_kernel_ks<ROWS, LAT, E, 4, 2, G>();
-    }
-    if constexpr (LAT == SMCX_FCC && E == 3) {
-        if (K == 5 && S == 4) return coop_kernel_ks<ROWS, LAT, E, 5, 4, G>();
-        if (K == 5 && S == 2) return coop_kernel_ks<ROWS, LAT, E, 5, 2, G>();
-    }
-    return coop_kernel_ks<ROWS, LAT, E, 0, 0, G>();
+    return S == 1   ? coop_kernel_s<ROWS, LAT, E, 1, G>()
+           : S == 2 ? coop_kernel_s<ROWS, LAT, E, 2, G>()
+           : S == 3 ? coop_kernel_s<ROWS, LAT, E, 3, G>()
+                    : coop_kernel_s<ROWS, LAT, E, 4, G>();
 }
 
 template <bool ROWS, int LAT, int G>
 static const void* coop_kernel_l(int K, int S)
 {
-    return K <= 4 ? coop_kernel_e<ROWS, LAT, 1, G>(K, S)
-                  : (K == 5 ? coop_kernel_e<ROWS, LAT, 3, G>(K, S) : coop_kernel_e<ROWS, LAT, 2, G>(K, S));
+    return K <= 4   ? coop_kernel_e<ROWS, LAT, 1, G>(S)
+           : K == 5 ? coop_kernel_e<ROWS, LAT, 3, G>(S)
+           : K == 6 ? coop_kernel_e<ROWS, LAT, 4, G>(S)
+                    : coop_kernel_s<ROWS, LAT, 2, 0, G>();
 }
 
 template <bool ROWS>

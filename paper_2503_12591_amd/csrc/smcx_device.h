@@ -48,26 +48,34 @@ __device__ __forceinline__ void philox4x32_10(uint32_t c0, uint32_t c1, uint32_t
 // species, biased by `half` when two counters are subtracted so that every
 // field of (n_a + bias - n_b) stays in [half - 24, half + 24] (a shell has at
 // most 24 sites) and no borrow crosses fields.  Encoding 1: K <= 4, 8-bit
-// fields in 32 bits; 3: K = 5, 6-bit fields in 32 bits; 2: K <= 8, 8-bit
-// fields in 64 bits.  The padded copy and the LDS window hold F * species.
+// fields in 32 bits; 3: K = 5, 6-bit fields in 32 bits; 4: K = 6, the same
+// with two bits left for species 5, whose difference follows from the others
+// (a shell's differences sum to zero); 2: K <= 8, 8-bit fields in 64 bits.
+// The padded copy and the LDS window hold F * species.
+// KP: species held, KT: those with a term of their own in the integer screen.
 template <int E> struct Enc;
 template <> struct Enc<1> {
     using T = uint32_t;
-    static constexpr int F = 8, KP = 4, half = 128;
+    static constexpr int F = 8, KP = 4, KT = 3, half = 128;
     static constexpr uint32_t bias = 0x80808080u, mask = 0xFF;
 };
 template <> struct Enc<3> {
     using T = uint32_t;
-    static constexpr int F = 6, KP = 5, half = 32;
+    static constexpr int F = 6, KP = 5, KT = 4, half = 32;
     static constexpr uint32_t bias = 32u | 32u << 6 | 32u << 12 | 32u << 18 | 32u << 24, mask = 0x3F;
+};
+template <> struct Enc<4> {
+    using T = uint32_t;
+    static constexpr int F = 6, KP = 6, KT = 5, half = 32;
+    static constexpr uint32_t bias = Enc<3>::bias, mask = 0x3F;
 };
 template <> struct Enc<2> {
     using T = uint64_t;
-    static constexpr int F = 8, KP = 8, half = 128;
+    static constexpr int F = 8, KP = 8, KT = 7, half = 128;
     static constexpr uint64_t bias = 0x8080808080808080ull, mask = 0xFF;
 };
 
-// species from its stored form F * species (F = 8 or 6, species < 8)
+// species from its stored form F * species (F = 8 or 6, species < 64)
 __device__ __forceinline__ int species_of(int v, int F) { return F == 8 ? v >> 3 : (v * 43) >> 8; }
 
 // acc + (1 << sh) in one instruction (v_lshl_add): the packed counter gains
@@ -110,8 +118,7 @@ __device__ __forceinline__ uint32_t shl1_add2(uint32_t a, uint32_t b, uint32_t a
 __device__ __forceinline__ uint64_t shl1_add2(uint32_t a, uint32_t b, uint64_t acc) { return shl1_add(b, shl1_add(a, acc)); }
 
 struct Lds {
-    const double* D;
-    const int32_t* Q;  // integer dE terms [S][K][K][K], then bias sums [K][K]
+    const int32_t* Q;  // integer dE terms and their bias sum, a row per species pair
     float qscale;      // value of one integer unit (a power of two)
     float qeps;        // bound on |integer dE - binary64 dE| before the float conversion
     const int32_t* offB;
@@ -121,11 +128,10 @@ struct Lds {
 __device__ __forceinline__ Lds lds_ptrs(const SweepArgs& A, uint8_t* smem)
 {
     Lds l;
-    l.D = (const double*)(smem + A.lds_d);
-    l.Q = (const int32_t*)(smem + A.lds_q);
+    l.Q = (const int32_t*)smem;
     // read at run time, like the tables, so that a captured graph follows smcx_set_epi
     using CI = const __attribute__((address_space(4))) int32_t;
-    const int nq = A.S * A.K * A.K * A.K + A.K * A.K;
+    const int nq = qtab_entries(A.K, A.S);
     l.qscale = __int_as_float(((CI*)A.Qtab)[nq]);
     l.qeps = __int_as_float(((CI*)A.Qtab)[nq + 1]);
     l.offB = (const int32_t*)(smem + A.lds_offb);
@@ -138,11 +144,8 @@ template <int LAT>
 __device__ void load_tables(const SweepArgs& A, uint8_t* smem)
 {
     constexpr int m = kGeom[LAT].m;
-    double* D = (double*)(smem + A.lds_d);
-    const int nD = A.K * A.K * A.S * A.K;
-    for (int i = threadIdx.x; i < nD; i += blockDim.x) D[i] = A.Dtab[i];
-    int32_t* Q = (int32_t*)(smem + A.lds_q);
-    const int nQ = nD + A.K * A.K;
+    int32_t* Q = (int32_t*)smem;
+    const int nQ = qtab_entries(A.K, A.S);
     for (int i = threadIdx.x; i < nQ; i += blockDim.x) Q[i] = A.Qtab[i];
     int32_t* Bo = (int32_t*)(smem + A.lds_offb);
     int8_t* pd = (int8_t*)(smem + A.lds_pd);
@@ -174,14 +177,13 @@ struct GeoRt {
 
 // Row windows: the window holds whole padded x-rows (periodic images of the
 // sites within two cells of the x faces included), so a written site must be
-// copied to its image in the window too.  KK / SS fix the species and shell
-// counts at compile time (0: taken from the launch).
-template <int KK, int SS>
+// copied to its image in the window too.  NS fixes the shell count at compile
+// time (0: taken from the launch).
+template <int NS>
 struct GeoRow : GeoRt {
     static constexpr bool rows = true;
     static constexpr bool own_cp = true;  // replicas may differ in column pitch
-    __device__ static int K(const SweepArgs& A) { return KK ? KK : A.K; }
-    __device__ static int S(const SweepArgs& A) { return SS ? SS : A.S; }
+    __device__ static int S(const SweepArgs& A) { return NS ? NS : A.S; }
 };
 
 struct TileGeom {
@@ -305,8 +307,12 @@ __device__ __noinline__ int decide_binary64(const double* Dp, typename Enc<E>::T
     for (int s = 0; s < S; ++s) {
         CT f = s == 0 ? d0 : (s == 1 ? d1 : (s == 2 ? d2 : d3));
         const double* Ds = Dp + s * K * K * K;
+        int rest = 0;
         for (int tt = 0; tt < K; ++tt) {
-            const int c = (int)(f & EN::mask) - EN::half;
+            // a species whose field has no room for it is what the others leave
+            const bool whole = EN::F * (tt + 1) <= 8 * (int)sizeof(CT);
+            const int c = whole ? (int)(f & EN::mask) - EN::half : -rest;
+            rest += c;
             const double term = (double)c * Ds[tt * K * K];
             dE = first ? term : dE + term;
             first = false;
@@ -383,10 +389,28 @@ __device__ __forceinline__ int screen_fine(uint32_t qacc, float qscale, float qe
     return uf < P ? 1 : 0;
 }
 
-// The decision of a trial: the screens, or decide_binary64 from the biased
-// count differences d0 .. d3.  Returns bit 0: accepted, bit 1: near-tie.
+// The species pair (p, q) of a trial from their stored forms: F (p K + q).
+// Species were checked < K at init; the clamp keeps table reads in bounds
+// regardless.
 template <int E>
-__device__ __forceinline__ int metropolis(uint32_t qacc, float qscale, float qeps, const double* Dp,
+__device__ __forceinline__ int species_pair(int p8, int q8, int K)
+{
+    return min(__mul24(p8, K) + q8, __mul24(Enc<E>::F, K * K - 1));
+}
+
+// Its row of the integer dE table.
+template <int E>
+__device__ __forceinline__ const int32_t* qtab_row(const int32_t* Q, int pair, int S)
+{
+    using EN = Enc<E>;
+    static_assert(EN::F == field_bits_of(EN::KP), "field width");
+    return (const int32_t*)((const uint8_t*)Q + __mul24(pair, 4 * qtab_pitch(EN::KP, S) / EN::F));
+}
+
+// The decision of a trial of species pair `pair`: the screens, or
+// decide_binary64 from the biased count differences d0 .. d3.  Returns bit 0: accepted, bit 1: near-tie.
+template <int E>
+__device__ __forceinline__ int metropolis(uint32_t qacc, float qscale, float qeps, const double* D, int pair,
                                           typename Enc<E>::T d0, typename Enc<E>::T d1, typename Enc<E>::T d2,
                                           typename Enc<E>::T d3, int K, int S, double beta, uint32_t w1, uint32_t w2)
 {
@@ -396,7 +420,7 @@ __device__ __forceinline__ int metropolis(uint32_t qacc, float qscale, float qep
         constexpr typename Enc<E>::T z = Enc<E>::bias;
         const bool same = ((d0 ^ z) | (S > 1 ? d1 ^ z : 0) | (S > 2 ? d2 ^ z : 0) | (S > 3 ? d3 ^ z : 0)) == 0;
         f = screen_fine(qacc, qscale, qeps, beta, w1, same, settled);
-        if (!settled) f = decide_binary64<E>(Dp, d0, d1, d2, d3, K, S, beta, w1, w2);
+        if (!settled) f = decide_binary64<E>(D + species_of(pair, Enc<E>::F), d0, d1, d2, d3, K, S, beta, w1, w2);
     }
     return f;
 }

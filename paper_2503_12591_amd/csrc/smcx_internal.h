@@ -237,8 +237,8 @@ struct SweepArgs {
     const int32_t* offB;       // [m][Z1] partner offset relative to the active site
     const int8_t* pdisp;       // [m][Z1][4] partner cell displacement and basis
     const double* Dtab;        // [S][K][K][K]: D[s][t][p][q] = V_s[q][t] - V_s[p][t]
-    const int32_t* Qtab;       // [S][K][K][K] D in integer units, [K][K] bias sums, then the unit and
-                               // the error bound as float bits (qtab_entries + 2 words)
+    const int32_t* Qtab;       // integer dE terms and bias sums, then the unit and the error bound
+                               // as float bits (qtab_entries + 2 words)
     uint8_t* occ;              // occupancy, natural layout (resident sweeps)
     uint8_t* ws;               // workspace base (padded copies)
     const double* beta;        // beta[js * beta_stride + r]
@@ -255,7 +255,7 @@ struct SweepArgs {
     int32_t R, K, S, Z1, sumZ;
     int32_t T[3];              // tile shape (link cells)
     int32_t LP, WY, WZ;        // LDS window: row pitch, rows per plane, planes
-    int32_t lds_d, lds_q, lds_offb, lds_pd, lds_win;  // dynamic-LDS byte offsets
+    int32_t lds_offb, lds_pd, lds_win;  // dynamic-LDS byte offsets
     int32_t win_bytes;         // one window buffer
     int32_t nbuf;              // window buffers: 2 = next tile streams in during the trials, 1 = staged in turn
     int32_t g;                 // mini-step (stream / plain launches)
@@ -269,21 +269,34 @@ struct SweepArgs {
 
 // Dynamic LDS layout helpers (byte offsets, 16-aligned).
 struct LdsLayout {
-    int d_off, q_off, offb_off, pd_off, win_off, win_bytes, total;
+    int offb_off, pd_off, win_off, win_bytes, total;
 };
 
-// Entries of the integer dE table: [S][K][K][K] terms, then [K][K] bias sums
-// (two float words follow them in memory: the unit and the error bound).
-inline int qtab_entries(int K, int S) { return S * K * K * K + K * K; }
+// Species that the packed counters of a K-species alloy hold.
+constexpr int counter_species(int K) { return K <= 4 ? 4 : (K <= 6 ? K : 8); }
+// Bits of a species' field in them.
+constexpr int field_bits_of(int K) { return K == 5 || K == 6 ? 6 : 8; }
+
+// Integer dE table: a row per species pair (p, q) with terms [S][KP - 1] for
+// counters of KP species (the last species' difference of counts is minus the
+// sum of the others', so its term is taken off theirs) and their bias sum; two
+// float words follow in memory: the unit and the error bound.  The words of a
+// row: a multiple of 2 (F = 8) or 3 (F = 6), so that the row of (p, q) starts
+// an integer times F (p K + q) bytes on, and no multiple of 4, so that reads
+// of different pairs spread over the LDS banks.
+constexpr int qtab_pitch(int KP, int S)
+{
+    const int n = S * (KP - 1) + 1, n3 = (n + 2) / 3 * 3;
+    return field_bits_of(KP) == 6 ? n3 + (n3 % 4 == 0 ? 3 : 0) : n + ((2 - n) & 3);
+}
+constexpr int qtab_entries(int K, int S) { return K * K * qtab_pitch(counter_species(K), S); }
 
 inline LdsLayout lds_layout(int lattice, int K, int S, int Z1, int win_bytes, int nbuf)
 {
     auto al = [](int v) { return (v + 15) & ~15; };
     const int m = lattice == SMCX_BCC ? 2 : 4;
     LdsLayout L{};
-    int o = 0;
-    L.d_off = o;    o = al(o + 8 * K * K * S * K);
-    L.q_off = o;    o = al(o + 4 * qtab_entries(K, S));
+    int o = al(4 * qtab_entries(K, S));  // the integer dE table comes first
     L.offb_off = o; o = al(o + 4 * m * Z1);
     L.pd_off = o;   o = al(o + 4 * m * Z1);
     L.win_off = o;
@@ -299,8 +312,7 @@ inline LdsLayout coop_layout(int K, int S, int n_partners, int n_origins, int wi
 {
     auto al = [](int v) { return (v + 15) & ~15; };
     LdsLayout L{};
-    int o = 0;
-    L.q_off = o;    o = al(o + 4 * qtab_entries(K, S));
+    int o = al(4 * qtab_entries(K, S));  // the integer dE table comes first
     L.pd_off = o;   o = al(o + 4 * n_partners);
     L.offb_off = o; o = al(o + 4 * n_origins);
     L.win_off = o;

@@ -479,8 +479,6 @@ __device__ __forceinline__ int trial_finish(const SweepArgs& A, const RepDev& re
     if (L.p8 == L.q8) return 1;
     const int K = Geo::K(A), S = Geo::S(A);
     const int p8 = L.p8, q8 = L.q8, k = L.k;
-    // species were checked < K at init; the clamp keeps table reads in bounds regardless
-    const int p = min(species_of(p8, EN::F), K - 1), q = min(species_of(q8, EN::F), K - 1);
     // the per-shell count differences, fields biased by `half`
     CT dsh[kMaxShells];
 #pragma unroll
@@ -489,37 +487,42 @@ __device__ __forceinline__ int trial_finish(const SweepArgs& A, const RepDev& re
         const CT mu = Geo::may_alias && rep.alias ? (CT)rep.mult[s][k] : (CT)(s == 0 ? 1 : 0);
         dsh[s] = s < S ? L.Ca[s] + EN::bias - L.Cb[s] + (mu << p8) - (mu << q8) : (CT)0;
     }
-    // Screen: dE in integers.  Qtab holds every D[s][t][p][q] rounded to a
-    // multiple of qscale (24-bit signed), so sum_t (c_t + half) Q - bias, bias
-    // = half sum Q, is sum_t c_t Q exactly (modulo 2^32, and it fits in 32
-    // bits), within qeps / qscale units of the binary64 dE.  It settles the
-    // decision whenever that uncertainty cannot change it; otherwise the
-    // binary64 sum and test below decide, as they always would.
-    const int32_t* Qp = T.Q + (p * K + q);
-    // every table read is issued before the first product, so the trial
-    // waits for the LDS once
-    int32_t qv[kMaxShells][EN::KP];
-    const int32_t qbias = T.Q[S * K * K * K + p * K + q];
+    // Screen: dE in integers.  With every D[s][t][p][q] rounded to a multiple
+    // of qscale, Qtab holds each shell's D_t - D_last (24-bit signed; a shell's
+    // count differences c_t sum to zero, so the last species needs no term), so
+    // sum_t (c_t + half) Q - bias, bias = half sum Q, is sum_t c_t D_t of the
+    // rounded D exactly (modulo 2^32, and it fits in 32 bits), within qeps /
+    // qscale units of the binary64 dE.  It settles the decision whenever that
+    // uncertainty cannot change it; otherwise the binary64 sum and test below
+    // decide, as they always would.
+    // Every table read is issued before the first product, so the trial waits
+    // for the LDS once; a pair's terms lie side by side at fixed offsets.
+    // Against tables [s][t][p][q] with one term more per shell and, but for
+    // two alloys, shell counts known only at run time, us per sweep: FCC 200^3 of
+    // 6 species 1930 -> 925 (2 shells; 64-bit counters before), 250x200x220 of
+    // 3 species and 3 shells 2175 -> 1490, BCC 250x260x270 of 3 species and 3
+    // shells 1397 -> 920, of 4 species and 4 shells 1172 -> 1030.
+    constexpr int KT = EN::KT;
+    const int pair = species_pair<E>(p8, q8, K);
+    const int32_t* Qp = qtab_row<E>(T.Q, pair, S);
+    int32_t qv[kMaxShells][KT];
+    const int32_t qbias = Qp[S * KT];
 #pragma unroll
     for (int s = 0; s < kMaxShells; ++s)
 #pragma unroll
-        for (int tt = 0; tt < EN::KP; ++tt) qv[s][tt] = s < S && tt < K ? Qp[(s * K + tt) * K * K] : 0;
+        for (int tt = 0; tt < KT; ++tt) qv[s][tt] = s < S ? Qp[s * KT + tt] : 0;
     __builtin_amdgcn_sched_barrier(0);
     uint32_t qacc = 0u - (uint32_t)qbias;
 #pragma unroll
     for (int s = 0; s < kMaxShells; ++s) {
         if (s < S) {
 #pragma unroll
-            for (int tt = 0; tt < EN::KP; ++tt) {
-                if (tt < K) {
-                    const int u = (int)((dsh[s] >> (EN::F * tt)) & EN::mask);
-                    qacc += (uint32_t)__mul24(u, qv[s][tt]);
-                }
-            }
+            for (int tt = 0; tt < KT; ++tt)
+                qacc += (uint32_t)__mul24((int)((dsh[s] >> (EN::F * tt)) & EN::mask), qv[s][tt]);
         }
     }
     static_assert(kMaxShells == 4, "four shell counters");
-    const int f = metropolis<E>(qacc, T.qscale, T.qeps, T.D + (p * K + q), dsh[0], dsh[1], dsh[2], dsh[3], K, S, beta,
+    const int f = metropolis<E>(qacc, T.qscale, T.qeps, A.Dtab, pair, dsh[0], dsh[1], dsh[2], dsh[3], K, S, beta,
                                 L.w1, L.w2);
     const bool acc = (f & 1) != 0, tie = (f & 2) != 0;
     if (tie) log_tie(A, r, t, L.ia, acc);
@@ -1200,8 +1203,15 @@ __global__ void k_fill_i32(int32_t* p, int64_t n, int32_t v)
 // Stream kernels exist for the runtime geometry and every preset of the
 // lattice; persistent kernels use the runtime geometry only.
 // ---------------------------------------------------------------------------
-int encoding_of(int K) { return K <= 4 ? 1 : (K == 5 ? 3 : 2); }
-int field_bits_of(int K) { return K == 5 ? 6 : 8; }
+// f with the counter encoding of K species as an integral constant
+template <typename F>
+static const void* with_encoding(int K, F f)
+{
+    if (K <= 4) return f(std::integral_constant<int, 1>{});
+    if (K == 5) return f(std::integral_constant<int, 3>{});
+    if (K == 6) return f(std::integral_constant<int, 4>{});
+    return f(std::integral_constant<int, 2>{});
+}
 
 template <int LAT, int E>
 static const void* stream_kernel(int preset, int nbuf)
@@ -1226,33 +1236,29 @@ static const void* persistent_kernel()
     return (const void*)k_persistent<LAT, E, GeoRt>;
 }
 
-// Row kernels: compile-time species / shell counts for the 4-species BCC
-// and 5-species FCC alloys with 4 or 2 shells, runtime counts otherwise (at
-// about half the speed: the 2-shell BCC lattice of 795^3 cells ran 2.2x
-// faster with its counts fixed).
+// Row kernels: a compile-time shell count for 32-bit counters (up to 6
+// species; with a runtime one the 2-shell BCC lattice of 795^3 cells took 2.2x
+// as long), a runtime one for 64-bit counters.
 template <int LAT, int E, int MAXB>
-static const void* row_kernel_e(int K, int S)
+static const void* row_kernel_e(int S)
 {
-    if constexpr (LAT == SMCX_BCC && E == 1) {
-        if (K == 4 && S == 4) return (const void*)k_rows<LAT, E, GeoRow<4, 4>, MAXB>;
-        if (K == 4 && S == 2) return (const void*)k_rows<LAT, E, GeoRow<4, 2>, MAXB>;
+    if constexpr (E != 2) {
+        if (S == 1) return (const void*)k_rows<LAT, E, GeoRow<1>, MAXB>;
+        if (S == 2) return (const void*)k_rows<LAT, E, GeoRow<2>, MAXB>;
+        if (S == 3) return (const void*)k_rows<LAT, E, GeoRow<3>, MAXB>;
+        return (const void*)k_rows<LAT, E, GeoRow<4>, MAXB>;
+    } else {
+        return (const void*)k_rows<LAT, E, GeoRow<0>, MAXB>;
     }
-    if constexpr (LAT == SMCX_FCC && E == 3) {
-        if (K == 5 && S == 4) return (const void*)k_rows<LAT, E, GeoRow<5, 4>, MAXB>;
-        if (K == 5 && S == 2) return (const void*)k_rows<LAT, E, GeoRow<5, 2>, MAXB>;
-    }
-    return (const void*)k_rows<LAT, E, GeoRow<0, 0>, MAXB>;
 }
 
 template <int MAXB>
 static const void* row_kernel_b(int lattice, int K, int S)
 {
-    const int e = encoding_of(K);
-    if (lattice == SMCX_BCC)
-        return e == 1 ? row_kernel_e<SMCX_BCC, 1, MAXB>(K, S)
-                      : (e == 3 ? row_kernel_e<SMCX_BCC, 3, MAXB>(K, S) : row_kernel_e<SMCX_BCC, 2, MAXB>(K, S));
-    return e == 1 ? row_kernel_e<SMCX_FCC, 1, MAXB>(K, S)
-                  : (e == 3 ? row_kernel_e<SMCX_FCC, 3, MAXB>(K, S) : row_kernel_e<SMCX_FCC, 2, MAXB>(K, S));
+    return with_encoding(K, [&](auto e) {
+        constexpr int E = decltype(e)::value;
+        return lattice == SMCX_BCC ? row_kernel_e<SMCX_BCC, E, MAXB>(S) : row_kernel_e<SMCX_FCC, E, MAXB>(S);
+    });
 }
 
 // The row kernel of compile-time row preset PI or a later one.
@@ -1280,13 +1286,11 @@ const void* row_kernel(int lattice, int K, int S, int block, int preset)
 
 const void* sweep_kernel(int lattice, int K, bool persistent, int preset, int nbuf)
 {
-    const int e = encoding_of(K);
-    if (lattice == SMCX_BCC) {
-        if (persistent) return e == 1 ? persistent_kernel<SMCX_BCC, 1>() : (e == 3 ? persistent_kernel<SMCX_BCC, 3>() : persistent_kernel<SMCX_BCC, 2>());
-        return e == 1 ? stream_kernel<SMCX_BCC, 1>(preset, nbuf) : (e == 3 ? stream_kernel<SMCX_BCC, 3>(preset, nbuf) : stream_kernel<SMCX_BCC, 2>(preset, nbuf));
-    }
-    if (persistent) return e == 1 ? persistent_kernel<SMCX_FCC, 1>() : (e == 3 ? persistent_kernel<SMCX_FCC, 3>() : persistent_kernel<SMCX_FCC, 2>());
-    return e == 1 ? stream_kernel<SMCX_FCC, 1>(preset, nbuf) : (e == 3 ? stream_kernel<SMCX_FCC, 3>(preset, nbuf) : stream_kernel<SMCX_FCC, 2>(preset, nbuf));
+    return with_encoding(K, [&](auto e) {
+        constexpr int E = decltype(e)::value;
+        if (persistent) return lattice == SMCX_BCC ? persistent_kernel<SMCX_BCC, E>() : persistent_kernel<SMCX_FCC, E>();
+        return lattice == SMCX_BCC ? stream_kernel<SMCX_BCC, E>(preset, nbuf) : stream_kernel<SMCX_FCC, E>(preset, nbuf);
+    });
 }
 
 hipError_t launch_sweep(const void* kernel, dim3 grid, int block, size_t lds, hipStream_t st, const SweepArgs& a)
