@@ -12,8 +12,8 @@
 // "The EPI and qSRO model".)
 //
 // Against one LDS byte read and shift-add per neighbour, and a histogram per
-// site: BCC 800^3 (4 species, 4 shells) 3.63 -> 1.04 ms, 64 x BCC 64^3 198 ->
-// 41 us, 4096 x BCC 16^3 271 -> 79 us, FCC 128^3 (5 species) 80 -> 41 us.
+// site: BCC 800^3 (4 species, 4 shells) 3.63 -> 0.79 ms, 64 x BCC 64^3 198 ->
+// 41 us, 4096 x BCC 16^3 271 -> 78 us, FCC 128^3 (5 species) 80 -> 41 us.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -27,7 +27,7 @@ namespace smcx {
 
 namespace {
 
-constexpr int kBitBlock = 256;
+constexpr int kBitBlock = 512;  // the most threads of a workgroup (512 or 256)
 
 // One direction of every +-d pair.
 constexpr bool positive(const int (&v)[3]) { return v[2] > 0 || (v[2] == 0 && (v[1] > 0 || (v[1] == 0 && v[0] > 0))); }
@@ -143,6 +143,17 @@ struct UnlikePairs {
         }
     }
 
+    // Pairs (k, l) from the totals of what add() counts (u[at(k, l)]).
+    __device__ static __forceinline__ uint32_t finish(const uint32_t* u, int k, int l)
+    {
+        uint32_t v = u[at(k, l)];
+        if constexpr (KT == 4) {
+            if (l == 1) v -= u[at(2, 3)] + u[at(0, 3)] + u[at(1, 2)];
+            if (k == 0 && l == 2) v -= u[at(1, 3)] + u[at(0, 3)] + u[at(1, 2)];
+        }
+        return v;
+    }
+
     __device__ __forceinline__ void add(const uint32_t (&o)[NP], const uint32_t (&n)[NP], uint32_t valid,
                                         uint32_t (&U)[NU]) const
     {
@@ -150,12 +161,14 @@ struct UnlikePairs {
             U[0] = bcnt((o[0] ^ n[0]) & valid, U[0]);
         } else if constexpr (KT <= 4) {
             // A, B: low, high species bit differs; pairs (0,1), (2,3) differ in
-            // the low bit only, (0,2), (1,3) in the high one, (0,3), (1,2) in both
+            // the low bit only, (0,2), (1,3) in the high one, (0,3), (1,2) in
+            // both.  Counted: A and B themselves, (0,3), (1,2), (2,3), (1,3);
+            // finish() takes (0,1) and (0,2) from them.
             const uint32_t A = __builtin_amdgcn_bitop3_b32(o[0], n[0], valid, 0x28);  // (a ^ b) & c
             const uint32_t B = __builtin_amdgcn_bitop3_b32(o[1], n[1], valid, 0x28);
             const uint32_t X = o[0] ^ o[1];
-            U[at(0, 1)] = bcnt(__builtin_amdgcn_bitop3_b32(A, o[1], n[1], 0x10), U[at(0, 1)]);  // a & ~b & ~c
-            U[at(0, 2)] = bcnt(__builtin_amdgcn_bitop3_b32(B, o[0], n[0], 0x10), U[at(0, 2)]);
+            U[at(0, 1)] = bcnt(A, U[at(0, 1)]);
+            U[at(0, 2)] = bcnt(B, U[at(0, 2)]);
             U[at(1, 2)] = bcnt(__builtin_amdgcn_bitop3_b32(A, B, X, 0x80), U[at(1, 2)]);  // a & b & c
             if constexpr (KT == 4) {
                 U[at(2, 3)] = bcnt(__builtin_amdgcn_bitop3_b32(A, o[1], n[1], 0x80), U[at(2, 3)]);
@@ -226,7 +239,7 @@ __device__ __forceinline__ void count_word(const uint32_t* cur, int b, int rowy,
 // on either side in y and two halo planes above.  Staging reads every byte of
 // the tile and its halo once, 16 bytes at a time, and writes a word of bits
 // per 32; a thread then counts the sites of one word of a row at a time.
-// Bound by VALU issue: 16 operations per direction and 32 bonds of 4 species
+// Bound by VALU issue: 14 operations per direction and 32 bonds of 4 species
 // (38 for 5), 25 directions per BCC site.  `bad` (may be NULL) gets its top
 // bit set when a byte is not a species below K.
 template <int LAT, int KT>
@@ -239,6 +252,7 @@ __global__ __launch_bounds__(kBitBlock) void k_pair_bits(const uint8_t* occ, int
     const uint8_t* o = occ + (int64_t)blockIdx.y * Nsites;
     const int L0 = T.L[0], L1 = T.L[1], L2 = T.L[2];
     const int RY = T.ty + 4, wpp = T.tw + 2;  // rows per staged plane; words per basis site and species bit
+    const int blk = blockDim.x;
     const bool split = T.nw > 1;
     const int wps = split ? wpp : T.tw;  // words staged per row
     const uint32_t addK = (uint32_t)(128 - K) * 0x01010101u;
@@ -256,7 +270,7 @@ __global__ __launch_bounds__(kBitBlock) void k_pair_bits(const uint8_t* occ, int
         const int nz = min(T.tz, L2 - z0), ny = min(T.ty, L1 - y0), nw = min(T.tw, T.W - w0);
         __syncthreads();  // the previous tile is counted
         const int nst = (nz + 2) * (ny + 4) * wps;
-        for (int i = threadIdx.x; i < nst; i += kBitBlock) {
+        for (int i = threadIdx.x; i < nst; i += blk) {
             const int w = i % wps, rr = i / wps, ry = rr % (ny + 4), rz = rr / (ny + 4);
             const int y = wrap(y0 + ry - 2, L1), z = wrap(z0 + rz, L2);
             const uint8_t* row = o + (int64_t)m * L0 * (y + (int64_t)L1 * z);
@@ -295,7 +309,7 @@ __global__ __launch_bounds__(kBitBlock) void k_pair_bits(const uint8_t* occ, int
         }
         __syncthreads();
         const int items = nz * ny * nw;
-        for (int i = threadIdx.x; i < items; i += kBitBlock) {
+        for (int i = threadIdx.x; i < items; i += blk) {
             const int w = i % nw, rr = i / nw, ry = rr % ny, rz = rr / ny;
             const int left = L0 - 32 * (w0 + w);
             const uint32_t valid = left >= 32 ? 0xFFFFFFFFu : (1u << left) - 1u;
@@ -311,7 +325,8 @@ __global__ __launch_bounds__(kBitBlock) void k_pair_bits(const uint8_t* occ, int
     }
     // wave sums into LDS, totals, one atomic per directed count
     __syncthreads();
-    constexpr int NV = kMaxShells * NU + KT, NWV = kBitBlock / 64;
+    constexpr int NV = kMaxShells * NU + KT;
+    const int NWV = blk / 64;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
 #pragma unroll
     for (int s = 0; s < kMaxShells; ++s)
@@ -328,7 +343,7 @@ __global__ __launch_bounds__(kBitBlock) void k_pair_bits(const uint8_t* occ, int
     if (bad && __ballot((over & 0x80808080u) != 0) && lane == 0) atomicOr(bad, 1ull << 63);
     __syncthreads();
     uint32_t* tot = bits + NWV * NV;
-    for (int i = threadIdx.x; i < NV; i += kBitBlock) {
+    for (int i = threadIdx.x; i < NV; i += blk) {
         uint32_t v = 0;
         for (int w = 0; w < NWV; ++w) v += bits[w * NV + i];
         tot[i] = v;
@@ -341,10 +356,10 @@ __global__ __launch_bounds__(kBitBlock) void k_pair_bits(const uint8_t* occ, int
         sites += (uint32_t)(m * min(32 * T.tw, L0 - 32 * tx * T.tw) * min(T.ty, L1 - ty * T.ty) * min(T.tz, L2 - tz * T.tz));
     }
     const uint32_t* n = tot + kMaxShells * NU;
-    for (int i = threadIdx.x; i < S * K * K; i += kBitBlock) {
+    for (int i = threadIdx.x; i < S * K * K; i += blk) {
         const int s = i / (K * K), k = (i / K) % K, l = i % K;
         uint32_t c;
-        auto pair = [&](int a, int b) { return tot[s * NU + (a < b ? UnlikePairs<KT>::at(a, b) : UnlikePairs<KT>::at(b, a))]; };
+        auto pair = [&](int a, int b) { return UnlikePairs<KT>::finish(tot + s * NU, min(a, b), max(a, b)); };
         if (k != l) {
             c = pair(k, l);
         } else {
@@ -400,8 +415,7 @@ hipError_t launch_pair_counts(int lattice, int K, int S, const uint8_t* occ, int
             const int tz = (L[2] + nz - 1) / nz;
             if ((int64_t)(ty + 4) * (tz + 2) * T.pitch > budget) continue;
             const int64_t items = (int64_t)ty * tz * T.tw, staged = (int64_t)(ty + 4) * (tz + 2) * T.tw;
-            const double rounds = (double)((items + kBitBlock - 1) / kBitBlock) * 400.0 +
-                                  (double)((staged + kBitBlock - 1) / kBitBlock) * 60.0 + 150.0;
+            const double rounds = (double)((items + 255) / 256) * 400.0 + (double)((staged + 255) / 256) * 60.0 + 150.0;
             const double tiles = (double)T.nw * ((L[1] + ty - 1) / ty) * ((L[2] + tz - 1) / tz) * B;
             const double cost = rounds * std::max(tiles, 768.0);
             if (cost < best) {
@@ -421,8 +435,12 @@ hipError_t launch_pair_counts(int lattice, int K, int S, const uint8_t* occ, int
     int64_t gx = std::max<int64_t>(1, std::min<int64_t>(tiles, 1536 / B));
     gx = std::max(gx, std::min<int64_t>(tiles, N / (1 << 26) + 1));
     const int NU = KT * (KT - 1) / 2, NV = kMaxShells * NU + KT;
-    const size_t lds = 4 * (size_t)std::max((T.ty + 4) * (T.tz + 2) * T.pitch, (kBitBlock / 64 + 1) * NV);
-    const dim3 g((unsigned)gx, (unsigned)B), blk(kBitBlock);
+    // Large tiles leave two workgroups per CU: eight waves each where their
+    // registers allow it (up to 4 species: BCC 800^3 1082 -> 845 us with the call,
+    // FCC 400^3 319 -> 254; 5 species, BCC 500^3: 514 -> 574)
+    const int threads = KT <= 4 && T.ty * T.tz * T.tw >= 1024 ? 512 : 256;
+    const size_t lds = 4 * (size_t)std::max((T.ty + 4) * (T.tz + 2) * T.pitch, (threads / 64 + 1) * NV);
+    const dim3 g((unsigned)gx, (unsigned)B), blk((unsigned)threads);
     unsigned long long* flag = (unsigned long long*)bad;
     auto go = [&](const void* kern) {
         (void)hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);

@@ -6,7 +6,7 @@ batched call in every position."""
 import numpy as np
 import pytest
 
-from gpu_cases import rand_occ, say
+from gpu_cases import NTHREADS, rand_occ, say
 from oracle import oracle as O
 
 pytestmark = pytest.mark.gpu
@@ -71,3 +71,15 @@ def test_species_check(smcx, K):
         bad[b, i] = v
         with pytest.raises(smcx.SmcxError):
             smcx.energy_backward_counts(BCC, dims, K, 2, torch.from_numpy(bad).cuda())
+
+
+@pytest.mark.parametrize("lattice,dims,K,S", [(BCC, (512, 256, 240), 4, 4), (BCC, (420, 300, 260), 2, 2),
+                                              (FCC, (500, 200, 260), 3, 2)])
+def test_counts_with_large_workgroups(smcx, lattice, dims, K, S):
+    """Tiles of a thousand words and more: 512 threads each."""
+    import torch
+    N = int(np.prod(dims)) * (2 if lattice == BCC else 4)
+    say(f"counts with large workgroups lattice={lattice} dims={dims} K={K}")
+    occ = rand_occ(N, K, 7 + K, equi=False)
+    C = smcx.energy_backward_counts(lattice, dims, K, S, torch.from_numpy(occ[None]).cuda()).cpu().numpy()
+    assert np.array_equal(C[0], O.pair_counts(lattice, dims, K, S, occ, NTHREADS))
