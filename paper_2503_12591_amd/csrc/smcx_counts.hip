@@ -240,11 +240,11 @@ __device__ __forceinline__ void count_word(const uint32_t* cur, int b, int rowy,
 // the tile and its halo once, 16 bytes at a time, and writes a word of bits
 // per 32; a thread then counts the sites of one word of a row at a time.
 // Bound by VALU issue: 14 operations per direction and 32 bonds of 4 species
-// (38 for 5), 25 directions per BCC site.  `bad` (may be NULL) gets its top
-// bit set when a byte is not a species below K.
+// (38 for 5), 25 directions per BCC site.  `bad` (may be NULL) is set
+// when a byte is not a species below K.
 template <int LAT, int KT>
 __global__ __launch_bounds__(kBitBlock) void k_pair_bits(const uint8_t* occ, int64_t Nsites, BitTile T, int K, int S,
-                                                         int64_t* counts, unsigned long long* bad)
+                                                         int64_t* counts, volatile uint32_t* bad)
 {
     constexpr Geometry G = kGeom[LAT];
     constexpr int m = G.m, NP = planes_of(KT), NU = UnlikePairs<KT>::NU;
@@ -340,7 +340,7 @@ __global__ __launch_bounds__(kBitBlock) void k_pair_bits(const uint8_t* occ, int
         const uint32_t v = wave_total(N[k]);
         if (lane == 63) bits[wave * NV + kMaxShells * NU + k] = v;
     }
-    if (bad && __ballot((over & 0x80808080u) != 0) && lane == 0) atomicOr(bad, 1ull << 63);
+    if (bad && __ballot((over & 0x80808080u) != 0) && lane == 0) *bad = 1;
     __syncthreads();
     uint32_t* tot = bits + NWV * NV;
     for (int i = threadIdx.x; i < NV; i += blk) {
@@ -386,7 +386,7 @@ __global__ __launch_bounds__(kBitBlock) void k_pair_bits(const uint8_t* occ, int
 }  // namespace
 
 hipError_t launch_pair_counts(int lattice, int K, int S, const uint8_t* occ, int64_t N, const int32_t* L, int B,
-                              int64_t* counts, int64_t* bad, hipStream_t st)
+                              int64_t* counts, volatile uint32_t* bad, hipStream_t st)
 {
     if (B > 65535) return hipErrorInvalidValue;
     const int m = lattice == SMCX_BCC ? 2 : 4;
@@ -441,10 +441,9 @@ hipError_t launch_pair_counts(int lattice, int K, int S, const uint8_t* occ, int
     const int threads = KT <= 4 && T.ty * T.tz * T.tw >= 1024 ? 512 : 256;
     const size_t lds = 4 * (size_t)std::max((T.ty + 4) * (T.tz + 2) * T.pitch, (threads / 64 + 1) * NV);
     const dim3 g((unsigned)gx, (unsigned)B), blk((unsigned)threads);
-    unsigned long long* flag = (unsigned long long*)bad;
     auto go = [&](const void* kern) {
         (void)hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        void* args[] = {(void*)&occ, (void*)&N, (void*)&T, (void*)&K, (void*)&S, (void*)&counts, (void*)&flag};
+        void* args[] = {(void*)&occ, (void*)&N, (void*)&T, (void*)&K, (void*)&S, (void*)&counts, (void*)&bad};
         return hipLaunchKernel(kern, g, blk, args, lds, st);
     };
     auto pick = [&](auto lat) -> const void* {

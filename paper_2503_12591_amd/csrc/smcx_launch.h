@@ -26,13 +26,12 @@ hipError_t launch_pack(int lattice, int K, bool unpack, bool planar, uint8_t* oc
                        int64_t* stats, hipStream_t st);
 hipError_t launch_validate(const uint8_t* occ, int64_t n, int K, int32_t* bad, hipStream_t st);
 hipError_t launch_fill_i64(int64_t* p, int64_t n, int64_t v, hipStream_t st);
-hipError_t launch_fill_i32(int32_t* p, int64_t n, int32_t v, hipStream_t st);
 hipError_t launch_advance_counter(uint32_t* counter, uint32_t n, hipStream_t st);
 // Pair counts of B configurations of N sites, added to counts (cleared by the
-// caller).  bad (may be NULL): its top bit is set when a species is not below
-// K; it may be a word of counts.
+// caller).  bad (may be NULL, may be host memory): set when a species is not
+// below K.
 hipError_t launch_pair_counts(int lattice, int K, int S, const uint8_t* occ, int64_t N, const int32_t* L, int B,
-                              int64_t* counts, int64_t* bad, hipStream_t st);
+                              int64_t* counts, volatile uint32_t* bad, hipStream_t st);
 hipError_t launch_energy(const int64_t* C, const double* V, int R, int SKK, double* E, hipStream_t st);
 // Device address of the static workspace on the current device (looked up
 // once per device with that device current).

@@ -83,3 +83,32 @@ def test_counts_with_large_workgroups(smcx, lattice, dims, K, S):
     occ = rand_occ(N, K, 7 + K, equi=False)
     C = smcx.energy_backward_counts(lattice, dims, K, S, torch.from_numpy(occ[None]).cuda()).cpu().numpy()
     assert np.array_equal(C[0], O.pair_counts(lattice, dims, K, S, occ, NTHREADS))
+
+
+def test_species_check_of_two_threads(smcx):
+    """Each thread's calls, on a stream of its own, see their own batch's check."""
+    import threading
+
+    import torch
+    dims, K, B, N = (35, 4, 5), 4, 6, 2 * 35 * 4 * 5
+    say("species check of two threads")
+    good = np.stack([rand_occ(N, K, b, equi=False) for b in range(B)])
+    bad = good.copy()
+    bad[3, 5] = K
+    seen = {"good": 0, "bad": 0}
+
+    def calls(name, occ):
+        with torch.cuda.stream(torch.cuda.Stream()):
+            occ = torch.from_numpy(occ).cuda()
+            for _ in range(50):
+                try:
+                    smcx.energy_backward_counts(BCC, dims, K, 2, occ)
+                except smcx.SmcxError:
+                    seen[name] += 1
+
+    threads = [threading.Thread(target=calls, args=a) for a in (("good", good), ("bad", bad))]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert seen == {"good": 0, "bad": 50}
