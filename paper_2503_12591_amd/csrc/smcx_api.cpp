@@ -497,21 +497,26 @@ int make_plan(const smcx_desc* d, Plan& P)
         }
         P.res = coop_layout(P.K, P.S, P.m * P.Z1, std::min(org_max, 1 << 16), (int)win_max);
         P.resident &= P.res.total + 64 <= 160 * 1024;
-        // as many lanes per trial as give every link cell its own lanes
+        // As many lanes per trial as give every link cell its own lanes; more
+        // than four only up to 512 in all (two waves per SIMD: beyond, the
+        // lanes' common work costs more than the shorter trial saves).  BCC
+        // 64 link cells, 8 lanes 112 us per sweep (16: 133, 4: 120), 125 cells,
+        // 4 lanes 144 (8: 168, 2: 183), 216 cells, 4 lanes 215 (2: 221); FCC 64
+        // cells, 8 lanes 222 (16: 273, 4: 244), 125 cells, 4 lanes 325 (8: 334).
         int G = 16;
-        while (G > P.m && (int64_t)cell_max * G > 1024) G /= 2;
+        while (G > P.m && (int64_t)cell_max * G > (G > 4 ? 512 : 1024)) G /= 2;
         P.res_lanes = G;
         P.res_block = (int)std::min<int64_t>(1024, ((int64_t)cell_max * G + 63) / 64 * 64);
         // Auto mode: us per mini-step of either form, fitted to measurements.
-        // Resident: the largest replica on its CU (8 link cells 0.6, 64 1.1,
-        // 216 1.7, 512 2.85; FCC about an eighth more), 256 replicas at a
+        // Resident: the largest replica on its CU (8 link cells 0.6, 64 0.9,
+        // 216 1.7, 512 2.8; FCC about an eighth more), 256 replicas at a
         // time.  Row launches: 7.6 us each, and mini-steps of 0.6 us growing
         // with the link cells of all replicas (14 thousand 1.3, 65 thousand
         // 2.3).  BCC 20^3 177 (resident) against 197 us per sweep, 24^3 222
         // against 194, 64 x 32^3 370 against 307, 256 x 32^3 370 against 668;
         // FCC 12^3 193 against 275, 16^3 290 against 281.
         const double c = cell_max, fcc = P.lattice == SMCX_FCC ? 1.12 : 1.0;
-        const double t_res = fcc * (0.55 + 0.0085 * std::min(c, 64.0) + 0.004 * std::max(c - 64.0, 0.0)) * ((P.R + 255) / 256);
+        const double t_res = fcc * (0.55 + 0.005 * std::min(c, 64.0) + 0.0048 * std::max(c - 64.0, 0.0)) * ((P.R + 255) / 256);
         double kcells = 0.0;
         int per_launch = 1 << 30;
         for (const Replica& R : P.reps) {
