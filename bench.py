@@ -666,7 +666,7 @@ def kernel_fingerprint() -> str:
     was taken on."""
     import hashlib
     h = hashlib.sha256()
-    for f in ("smcx_kernels.hip", "smcx_internal.h"):
+    for f in ("smcx_kernels.hip", "smcx_device.h", "smcx_internal.h"):
         with open(os.path.join(ROOT, "paper_2503_12591_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]
@@ -759,7 +759,7 @@ def summarize(args):
         fw, _ = _copy_factor(cwd, "WRITE_SIZE")
         names = sorted({r["Kernel_Name"] for r in _csv(fd, "counter_collection.csv") if "smcx::" in r["Kernel_Name"]})
         N = 2 * args.edge ** 3
-        algo = {"k_pair_counts_slab": (N, 0), "k_pair_counts_tiled": (N, 0), "k_pack": (N, None), "k_unpack": (None, N),
+        algo = {"k_pair_bits": (N, 0), "k_pack": (N, None), "k_unpack": (None, N),
                 "k_validate": (N, 0)}
         lines = [f"# HBM traffic of every library kernel: BCC {args.edge}^3 benchmark, link cell {args.ell}",
                  f"# command (one pass per counter): {cmd}",
@@ -767,7 +767,7 @@ def summarize(args):
                  "# bytes: the lattice read (pair counts, pack, validate) or written (unpack), N = sites", "",
                  f"{'kernel':58s} {'read GB':>9s} {'write GB':>9s} {'read / N':>9s}"]
         for n in names:
-            short = n.split("(")[0].replace("void ", "")
+            short = n.replace("(anonymous namespace)::", "").split("(")[0].replace("void ", "")
             rd = _per_dispatch(fd, "FETCH_SIZE", lambda k, n=n: k == n)[0] * 1024 * ff
             wr = _per_dispatch(wd, "WRITE_SIZE", lambda k, n=n: k == n)[0] * 1024 * fw
             base = short.split("::")[-1].split("<")[0]
@@ -814,7 +814,7 @@ def summarize(args):
             for r in _csv(d, "counter_collection.csv"):
                 if "smcx::" not in r["Kernel_Name"]:
                     continue
-                k = r["Kernel_Name"].split("(")[0].replace("void ", "")
+                k = r["Kernel_Name"].replace("(anonymous namespace)::", "").split("(")[0].replace("void ", "")
                 per.setdefault(k, {}).setdefault(r["Counter_Name"], []).append(float(r["Counter_Value"]))
         title = args.profile_name or "library kernels"
         lines = [f"# SQ counters of every library kernel: {title}",

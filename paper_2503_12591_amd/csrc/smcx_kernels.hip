@@ -1,5 +1,7 @@
 // gfx950 kernels of libsmcx: link-cell parallel swap Metropolis sweeps with a
-// multi-shell EPI energy, pair counting, and helpers.
+// multi-shell EPI energy over row and tile windows (sweeps with several lanes
+// per trial, pair counts, the qSRO model and local energies have files of their
+// own), packing, energies, replica exchange, and helpers.
 //
 // Trial (one lane per link cell of a tile):
 //   1. Philox4x32-10 on counter (site, sweep, replica) gives the partner
@@ -7,8 +9,8 @@
 //      bullet: one draw per trial);
 //   2. the tile window around the active sites is staged from the padded
 //      HBM copy into LDS with 16-byte loads, species stored pre-shifted
-//      (8 * sigma) so that a neighbour costs one LDS byte read and one
-//      shift-add into a packed per-shell counter (8 bits per species);
+//      (F * sigma) so that a neighbour costs one LDS byte read and one
+//      shift-add into a packed per-shell counter (F = 8 or 6 bits per species);
 //   3. dE = sum_s sum_t (n_a - n_b)[s][t] * (V_s[q][t] - V_s[p][t]) in binary64
 //      from the integer counters, s and t ascending, the a-b bond excluded
 //      (Methods, "The EPI and qSRO model": the energy change of a pair model
