@@ -416,11 +416,13 @@ int make_plan(const smcx_desc* d, Plan& P)
         // Several lanes per trial where the launch's link cells alone would
         // leave the chip's 65536 lane slots (one wave per SIMD) idle.  The
         // most lanes that keep a launch within two waves per SIMD, and two
-        // lanes (BCC) up to eight waves: BCC 64^3 16 lanes 215 us per sweep (one lane
-        // 397), 96^3 8 lanes 287 (398), 128^3 4 lanes 321 (403), 160^3 2 lanes
-        // 449 (471), 256 replicas of 16^3 to 48^3 2 lanes 1512 (1784),
-        // 256^3 2 lanes 967 (1001), 320^3 2 lanes 1944 (1489); FCC 64^3
-        // 16 lanes 297 (734), 128^3 4 lanes 509 (775), 160^3 4 lanes 970 (908).
+        // lanes (BCC; four for FCC: three waves) up to three and a half, or
+        // eight over replicas of different sizes, whose one-lane windows leave
+        // lanes idle.  us per sweep, one lane in brackets: BCC 64^3 16 lanes
+        // 199 (385), 96^3 8 lanes 267 (384), 128^3 4 lanes 276 (370), 160^3 2
+        // lanes 419 (429), 96^3 x 8 533 (532), 200^3 563 (508), 256^3 908
+        // (736), 256 replicas of 16^3 to 48^3 1393 (1478); FCC 64^3 16 lanes
+        // 300 (652), 128^3 4 lanes 440 (657), 144^3 715 (770), 160^3 874 (781).
         int64_t cells = 0;
         bool images_fit = true;  // a row shorter than twice the halo would hold a site's image on both sides
         for (const Replica& R : P.reps) {
@@ -429,7 +431,10 @@ int make_plan(const smcx_desc* d, Plan& P)
         }
         int G = 16;
         while (G > P.m && (cells * G > 131072 || ncx * G > kMaxCoopRowBlock)) G /= 2;
-        const int64_t most = P.lattice == SMCX_BCC ? 524288 : 196608;
+        bool one_size = true;
+        for (const Replica& R : P.reps)
+            for (int a = 0; a < 3; ++a) one_size &= R.L[a] == P.reps[0].L[a];
+        const int64_t most = P.lattice == SMCX_FCC ? 196608 : (one_size ? 229376 : 524288);
         if (images_fit && cells * G <= most && ncx * G <= kMaxCoopRowBlock) {
             // whole rows per workgroup: the fewest that keep three lanes in
             // four busy (few rows: many workgroups, little to stage before the
@@ -512,9 +517,9 @@ int make_plan(const smcx_desc* d, Plan& P)
         // 216 1.7, 512 2.8; FCC about an eighth more), 256 replicas at a
         // time.  Row launches: 7.6 us each, and mini-steps of 0.6 us growing
         // with the link cells of all replicas (14 thousand 1.3, 65 thousand
-        // 2.3).  BCC 20^3 177 (resident) against 197 us per sweep, 24^3 222
-        // against 194, 64 x 32^3 370 against 307, 256 x 32^3 370 against 668;
-        // FCC 12^3 193 against 275, 16^3 290 against 281.
+        // 2.3).  BCC 20^3 146 (resident) against 195 us per sweep, 24^3 221
+        // against 189, 64 x 32^3 360 against 298, 256 x 32^3 363 against 570;
+        // FCC 12^3 187 against 271, 16^3 229 against 277, 20^3 337 against 282.
         const double c = cell_max, fcc = P.lattice == SMCX_FCC ? 1.12 : 1.0;
         const double t_res = fcc * (0.55 + 0.005 * std::min(c, 64.0) + 0.0048 * std::max(c - 64.0, 0.0)) * ((P.R + 255) / 256);
         double kcells = 0.0;

@@ -386,7 +386,7 @@ __device__ __forceinline__ void step_barrier(bool waves)
 // cells, 16 lanes each), large ones by the CU's LDS and VALU issue (2.9 us at
 // 512 link cells, 2 lanes each).  Against tile windows staged anew for every
 // offset, one lane per trial: BCC 8^3 588 -> 67 us per sweep, FCC 18x13x11
-// 3150 -> 500 us; against row launches 256 BCC 32^3 replicas 583 -> 370 us.
+// 3150 -> 390 us; against row launches 256 BCC 32^3 replicas 570 -> 370 us.
 // ---------------------------------------------------------------------------
 constexpr int kResidentBlock = 1024;
 
