@@ -475,6 +475,10 @@ __global__ __launch_bounds__(kResidentBlock) void k_resident(SweepArgs A)
     };
     take_cell(grp);
     Stats st;
+    // one workgroup counts every trial of the call: the 32-bit sums go out
+    // before 2^30 of them (a sweep tries every site once)
+    const int flush_every = (1 << 30) / (m * Lx * Ly * Lz);
+    int until_flush = flush_every;
     for (int js = 0; js < A.n_sweeps; ++js) {
         const uint32_t t = first + (uint32_t)js;
         const double beta = ld_const(A.beta, (int64_t)js * A.beta_stride + r);
@@ -536,8 +540,13 @@ __global__ __launch_bounds__(kResidentBlock) void k_resident(SweepArgs A)
             }
             if (npass > 1) __syncthreads();
         }
+        if (--until_flush == 0) {
+            until_flush = flush_every;
+            if (co.j != 0) st = Stats();  // the group's lanes counted alike
+            flush_stats_block(A, r, st);
+        }
     }
-    if (co.j != 0) st = Stats();  // the group's lanes counted alike
+    if (co.j != 0) st = Stats();
     __syncthreads();
     flush_stats_block(A, r, st);
     for (int c = threadIdx.x; c < Lx * Ly * Lz; c += blockDim.x) {

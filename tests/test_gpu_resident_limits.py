@@ -34,3 +34,16 @@ def test_strongly_uneven_cells_near_the_lds_limit(smcx, lattice, dims, K, z, mod
     cells = [uniform(dims[0], 4), uniform(dims[1], 4), z]
     gpu_vs_oracle(lattice, dims, K, 4, rand_occ(N, K, 17, equi=False), sym_V(4, K, 0.04, 6), I.beta_of_T([1500.0, 800.0]),
                   seed=2 ** 33 + 5, mode=mode, cells=cells)
+
+
+def test_counters_past_32_bits_in_one_call(smcx):
+    """One workgroup counts every trial of a call: 2^31 and more of them."""
+    import torch
+    L, n = 32, 2 ** 31 // (2 * 32 ** 3) + 7
+    occ = torch.zeros(2 * L ** 3, dtype=torch.uint8, device="cuda")
+    lat = smcx.Lattice(BCC, (L, L, L), 2, 1, occ)
+    lat.set_epi(sym_V(1, 2, 0.03, 1))
+    betas = torch.full((n, 1), 10.0, dtype=torch.float64, device="cuda")
+    stats, _, ties = lat.sweep(n, 3, betas, mode="persistent")
+    assert stats.tolist() == [n * 2 * L ** 3, 0, 0] and int(ties) == 0
+    lat.close()
