@@ -1139,7 +1139,8 @@ __global__ __launch_bounds__(kBlock) void k_unpack(uint8_t* occ, const uint8_t* 
             }
 #pragma unroll
             for (int d = 32; d > 0; d >>= 1) v += __shfl_xor(v, d, 64);
-            if (threadIdx.x == 0) stats[3 * (int64_t)ri + k] += v;
+            // atomic: handles on other streams may count into the same words
+            if (threadIdx.x == 0 && v) atomicAdd((unsigned long long*)&stats[3 * (int64_t)ri + k], (unsigned long long)v);
         }
     }
     const RepDev& rep = rep_at(reps, ri);
