@@ -556,15 +556,15 @@ int make_plan(const smcx_desc* d, Plan& P)
     P.off_qV = o; o = align256(o + sizeof(double) * P.S * P.K * P.K);
     P.off_qW = o; o = align256(o + sizeof(double) * P.S * P.K);
     P.off_qG = o; o = align256(o + sizeof(double) * qsro_products(P.K, P.S));
-    P.off_qslots = o; o = align256(o + sizeof(int64_t) * 3 * kQsroGrid);
-    P.off_pad = o;
+    // qSRO sweeps count in the space of the padded copies, which they do not use
+    P.off_pad = P.off_qslots = o;
     P.total_tiles = 0;
     for (Replica& R : P.reps) {
         R.pad_off = (int64_t)o;
         o = align256(o + (size_t)R.pad_bytes);
         P.total_tiles += R.ntiles;
     }
-    P.total = o;
+    P.total = std::max(o, align256(P.off_qslots + sizeof(int64_t) * 3 * kQsroGrid));
     return SMCX_OK;
 }
 
@@ -611,9 +611,12 @@ struct smcx_lattice {
 
 namespace {
 
-SweepArgs base_args(smcx_lattice* h)
+// Counters go to the slots, which the unpacking adds to the caller's, or where
+// there are none straight there.
+SweepArgs base_args(smcx_lattice* h, int64_t* stats_dev)
 {
     const Plan& P = h->P;
+    const int parts = stat_parts_of(P.R);
     SweepArgs a{};
     a.reps = (const RepDev*)(h->ws + P.off_reps);
     a.origins = (const int32_t*)(h->ws + P.off_origins);
@@ -624,9 +627,9 @@ SweepArgs base_args(smcx_lattice* h)
     a.Qtab = (const int32_t*)(h->ws + P.off_Q);
     a.ws = h->ws;
     a.occ = h->occ;
-    a.stats = (int64_t*)(h->ws + P.off_slots);
-    a.stat_parts = stat_parts_of(P.R);
-    a.stat_stride = kStatStride;
+    a.stats = parts ? (int64_t*)(h->ws + P.off_slots) : stats_dev;
+    a.stat_parts = parts ? parts : 1;
+    a.stat_stride = parts ? kStatStride : 3;
     a.R = P.R;
     a.K = P.K;
     a.S = P.S;
@@ -650,10 +653,10 @@ SweepArgs base_args(smcx_lattice* h)
 
 // Launch arguments of the row kernel: row windows, their offset tables and
 // the prefix sums of row groups per replica.
-SweepArgs row_args(smcx_lattice* h)
+SweepArgs row_args(smcx_lattice* h, int64_t* stats_dev)
 {
     const Plan& P = h->P;
-    SweepArgs a = base_args(h);
+    SweepArgs a = base_args(h, stats_dev);
     a.tile_off = (const int64_t*)(h->ws + P.off_rowoff);
     a.offB = (const int32_t*)(h->ws + P.off_offB_r);
     for (int i = 0; i < 3; ++i) a.T[i] = P.RT[i];
@@ -1271,7 +1274,7 @@ static int run_sweeps(smcx_lattice* h, int32_t n_sweeps, uint64_t seed, uint32_t
     // decompositions share its launches only over whole sweeps
     const bool rows = mode == SMCX_MODE_STREAM && P.rows && (!P.rows_mixed || (tau_begin == 0 && tau_end >= P.max_nA));
     const bool planar = rows;
-    SweepArgs a = base_args(h);
+    SweepArgs a = base_args(h, stats_dev);
     a.seed = seed;
     a.ties = ties_dev;
     a.tie_cap = tie_cap;
@@ -1291,7 +1294,7 @@ static int run_sweeps(smcx_lattice* h, int32_t n_sweeps, uint64_t seed, uint32_t
     if (int rc = pack_all(h, false, planar, stats_dev, st)) return rc;
     if (rows) {
         // one launch per (o_y, o_z) group: every o_x and basis site
-        SweepArgs ra = row_args(h);
+        SweepArgs ra = row_args(h, stats_dev);
         ra.seed = a.seed;
         ra.ties = a.ties;
         ra.tie_cap = a.tie_cap;
@@ -1631,7 +1634,7 @@ int smcx_ladder_capture(smcx_lattice* h, int32_t n_sweeps, uint64_t seed, const 
     const Plan& P = h->P;
     hipStream_t st = (hipStream_t)stream;
     SMCX_HIP(hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal));
-    SweepArgs a = base_args(h);
+    SweepArgs a = base_args(h, stats_dev);
     a.seed = seed;
     a.ties = ties_dev;
     a.tie_cap = tie_cap;

@@ -225,9 +225,11 @@ constexpr bool preset_ok(const Preset& p) { return (p.tx * p.ell * preset_m(p)) 
 // into: atomics of the whole chip on one address run one after another at the
 // memory side (about 10 ns each: a launch of 256 workgroups over one replica
 // ended 5 us late), so each replica's counters are spread over this many
-// slots, 128 bytes apart, and added up once per call.
+// slots, 128 bytes apart, and added up once per call.  More than 1024 replicas
+// spread the atomics by themselves: none (their slots would be workspace that
+// descriptions near the static workspace's size do not have).
 constexpr int kStatStride = 16;  // int64 words per slot
-constexpr int stat_parts_of(int R) { return R >= 256 ? 1 : (R <= 4 ? 64 : 256 / R); }
+constexpr int stat_parts_of(int R) { return R > 1024 ? 0 : (R >= 256 ? 1 : (R <= 4 ? 64 : 256 / R)); }
 
 // Arguments of the sweep kernels (passed by value).
 struct SweepArgs {

@@ -1128,7 +1128,7 @@ __global__ __launch_bounds__(kBlock) void k_unpack(uint8_t* occ, const uint8_t* 
                                                    int64_t* slots, int parts, int64_t* stats)
 {
     const int ri = r < 0 ? (int)blockIdx.y : r;  // r < 0: one replica per grid row
-    if (blockIdx.x == 0 && threadIdx.x < 64) {
+    if (parts > 0 && blockIdx.x == 0 && threadIdx.x < 64) {
         // the sweep launches' counter slots (at most 64), added up and cleared
         for (int k = 0; k < 3; ++k) {
             int64_t* s = slots + ((int64_t)ri * parts + threadIdx.x) * kStatStride + k;

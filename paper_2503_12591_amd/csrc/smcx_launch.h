@@ -20,7 +20,7 @@ hipError_t sweep_occupancy(const void* kernel, int block, size_t lds, int* block
 // Natural layout <-> padded copy of replica r, or of every replica in one
 // launch when r < 0 (nrows, row16: the largest replica's rows and 16-cell
 // chunks per row; nrep replicas).
-// Unpacking also adds each replica's counter slots to stats and clears them.
+// Unpacking also adds each replica's counter slots (parts of them, 0: none) to stats and clears them.
 hipError_t launch_pack(int lattice, int K, bool unpack, bool planar, uint8_t* occ, uint8_t* ws,
                        const RepDev* reps, int r, int64_t nrows, int row16, int nrep, int64_t* slots, int parts,
                        int64_t* stats, hipStream_t st);
