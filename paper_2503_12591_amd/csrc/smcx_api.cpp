@@ -751,21 +751,38 @@ int persistent_launch(smcx_lattice* h, SweepArgs a, int64_t* stats_dev, hipStrea
     return timed_launch(h, h->k_resident, dim3(P.R), P.res_block, P.res.total, st, a);
 }
 
-// A word of host memory that kernels write, one per thread: a result that the
-// host waits for, without a copy from the device (energy_backward of 64 x BCC
-// 64^3 72 -> 63 us with the call, of one 42 -> 33).  Calls that use it end with a synchronisation.
-volatile uint32_t* host_word()
+// Words of host memory that kernels write: a result that the host waits for,
+// without a copy from the device (energy_backward of 64 x BCC 64^3 72 -> 63 us
+// with the call, of one 42 -> 33).  A call takes one and gives it back once its
+// stream is synchronised (after an error, with kernels that may still write it
+// on their way, never), so there are as many as calls were ever in flight
+// together.  They stay until the process ends: freed when a thread ends, say,
+// hipHostFree would break whatever another thread is capturing.
+struct HostWord {
+    HostWord* next;
+    uint32_t value;
+};
+std::mutex g_words_mu;
+HostWord* g_words = nullptr;  // those not in use
+
+HostWord* take_word()
 {
-    struct Word {
-        uint32_t* p = nullptr;
-        ~Word()
-        {
-            if (p) (void)hipHostFree(p);
+    {
+        std::lock_guard<std::mutex> lock(g_words_mu);
+        if (HostWord* w = g_words) {
+            g_words = w->next;
+            return w;
         }
-    };
-    thread_local Word w;
-    if (!w.p && hipHostMalloc((void**)&w.p, 64, hipHostMallocPortable) != hipSuccess) w.p = nullptr;
-    return w.p;
+    }
+    void* p = nullptr;
+    return hipHostMalloc(&p, sizeof(HostWord), hipHostMallocPortable) == hipSuccess ? (HostWord*)p : nullptr;
+}
+
+void give_word(HostWord* w)
+{
+    std::lock_guard<std::mutex> lock(g_words_mu);
+    w->next = g_words;
+    g_words = w;
 }
 
 // The handle that currently owns each device's static workspace (a later
@@ -1581,9 +1598,10 @@ int smcx_energy_backward(int32_t lattice, const int32_t* dims, int32_t n_species
     hipStream_t st = (hipStream_t)stream;
     const int64_t per = (int64_t)n_shells * n_species * n_species;
     // species check (a species >= K would be miscounted silently): the counting
-    // kernel sets this thread's word
-    volatile uint32_t* bad = host_word();
-    if (!bad) return fail(SMCX_E_HIP, "hipHostMalloc failed");
+    // kernel sets a word of host memory
+    HostWord* w = take_word();
+    if (!w) return fail(SMCX_E_HIP, "hipHostMalloc failed");
+    volatile uint32_t* bad = &w->value;
     *bad = 0;
     SMCX_HIP(launch_fill_i64(counts_dev, per * B, 0, st));
     for (int32_t b0 = 0; b0 < B; b0 += 65535) {
@@ -1592,7 +1610,9 @@ int smcx_energy_backward(int32_t lattice, const int32_t* dims, int32_t n_species
                                     counts_dev + per * b0, bad, st));
     }
     SMCX_HIP(hipStreamSynchronize(st));
-    if (*bad) return fail(SMCX_E_INVALID_ARG, "a configuration holds a species >= n_species");
+    const bool found = *bad != 0;
+    give_word(w);
+    if (found) return fail(SMCX_E_INVALID_ARG, "a configuration holds a species >= n_species");
     return SMCX_OK;
 }
 

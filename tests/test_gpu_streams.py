@@ -52,3 +52,73 @@ def test_handles_on_two_streams_share_counters(smcx, mode):
     assert counters(shared=True) == own
     for lat in lats:
         lat.close()
+
+
+def backward(smcx, occ, counts, dims, K, S, stream):
+    """smcx_energy_backward on a given stream."""
+    import ctypes as C
+    d = np.asarray(dims, np.int32)
+    return smcx.lib().smcx_energy_backward(BCC, d.ctypes.data_as(C.c_void_p), K, S, C.c_void_p(occ.data_ptr()), occ.shape[0],
+                                           C.c_void_p(counts.data_ptr()), C.c_void_p(stream.cuda_stream))
+
+
+def test_a_thread_that_counted_may_end_during_a_capture(smcx):
+    """What a call leaves with its thread takes no HIP call to go away."""
+    import threading
+
+    import torch
+    dims, K, S, B = (8, 8, 8), 4, 2, 5
+    occ = torch.randint(0, K, (B, 1024), dtype=torch.uint8, device="cuda")
+    counts = torch.zeros((B, S, K, K), dtype=torch.int64, device="cuda")
+    x = torch.zeros(4, device="cuda")
+    stream = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    counted, end, rc = threading.Event(), threading.Event(), []
+
+    def work():
+        torch.cuda.set_device(0)
+        rc.append(backward(smcx, occ, counts, dims, K, S, stream))
+        counted.set()
+        end.wait(30)
+
+    t = threading.Thread(target=work)
+    t.start()
+    assert counted.wait(30) and rc == [0]
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, capture_error_mode="global"):
+        x.add_(1)
+        end.set()
+        t.join()
+        x.add_(1)
+    for n in (1, 2):
+        g.replay()
+        torch.cuda.synchronize()
+        assert x.tolist() == [2.0 * n] * 4
+
+
+def test_counting_in_many_threads_at_once(smcx):
+    """Every call hears of its own species only."""
+    import threading
+
+    import torch
+    dims, K, S, B = (8, 9, 8), 4, 2, 3
+    good = torch.randint(0, K, (B, 2 * 576), dtype=torch.uint8, device="cuda")
+    bad = good.clone()
+    bad[B - 1, 1000] = K
+    streams = [torch.cuda.Stream() for _ in range(8)]
+    outs = [torch.zeros((B, S, K, K), dtype=torch.int64, device="cuda") for _ in range(8)]
+    torch.cuda.synchronize()
+    rcs = [[] for _ in range(8)]
+
+    def work(i):
+        torch.cuda.set_device(0)
+        for j in range(20):
+            rcs[i].append(backward(smcx, bad if (i + j) % 3 == 0 else good, outs[i], dims, K, S, streams[i]))
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(8)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    for i in range(8):
+        assert rcs[i] == [-1 if (i + j) % 3 == 0 else 0 for j in range(20)]
