@@ -379,7 +379,8 @@ __device__ __forceinline__ int screen_fine(uint32_t qacc, float qscale, float qe
 {
     const double e = (double)(int32_t)qacc * (double)qscale;  // exact: a 32-bit integer times a power of two
     const double eps = (double)qeps, y = beta * eps;
-    settled = same | (e <= -eps);
+    // (an infinite bound: some D may be infinite, and 0 times it is no zero)
+    settled = (same & (qeps < __builtin_inff())) | (e <= -eps);
     if (settled) return 1;
     const double x = beta * e * 1.4426950408889634, n = rint(x);
     if (!(e > eps && y >= 0.0 && y < 0.25 && x < 100.0)) return 0;

@@ -1,0 +1,33 @@
+"""Interaction tensors at the ends of what the integer screen takes, against
+the oracle's sums in binary64."""
+import numpy as np
+import pytest
+
+from gpu_cases import gpu_vs_oracle, rand_occ, sym_V
+from paper_2503_12591_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+BCC, FCC = 0, 1
+
+WINDOWS = [((9, 8, 10), "persistent", True), ((9, 8, 10), "stream", True), ((64, 60, 66), "stream", True),
+           ((9, 8, 10), "stream", False), ((2, 3, 2), "persistent", True)]
+
+
+def run(lattice, dims, K, V, mode, rows, T=(4000.0, 900.0)):
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    N = int(np.prod(dims)) * (2 if lattice == BCC else 4)
+    gpu_vs_oracle(lattice, dims, K, len(V), rand_occ(N, K, K, equi=False), V, I.beta_of_T(list(T)), seed=K, mode=mode, ell=4,
+                  rows=rows)
+
+
+@pytest.mark.parametrize("dims,mode,rows", WINDOWS)
+@pytest.mark.parametrize("lattice,K,value", [(BCC, 3, np.inf), (BCC, 6, -np.inf), (FCC, 5, np.inf), (BCC, 8, 1.7e308),
+                                             (FCC, 4, 1e300)])
+def test_infinite_differences(lattice, K, value, dims, mode, rows):
+    """Terms of 0 times an infinite difference are no zeros (the sum is not a
+    number, the trial not accepted), however alike two sites' neighbours are."""
+    V = sym_V(2, K, 0.03, K)
+    V[1, 0, 1] = V[1, 1, 0] = value
+    V[1, 0, 0] = -value
+    run(lattice, dims, K, V, mode, rows)
