@@ -1102,7 +1102,11 @@ int smcx_set_epi(smcx_lattice* h, const double* V, void* stream)
         const int KP = counter_species(K), KT = KP - 1, pitch = qtab_pitch(KP, S);
         auto Dof = [&](int s, int t, int p, int q) { return t < K ? h->Dhost[((s * K + t) * K + p) * K + q] : 0.0; };
         double maxD = 0.0, maxT = 0.0;
-        for (double v : h->Dhost) maxD = std::max(maxD, std::fabs(v));
+        bool fits = true;  // every term has a place in 24 bits
+        for (double v : h->Dhost) {
+            maxD = std::max(maxD, std::fabs(v));
+            fits &= std::isfinite(v);
+        }
         for (int s = 0; s < S; ++s)
             for (int t = 0; t < KT; ++t)
                 for (int p = 0; p < K; ++p)
@@ -1113,10 +1117,15 @@ int smcx_set_epi(smcx_lattice* h, const double* V, void* stream)
             kq = (int)std::floor(std::log2(8388606.0 / maxT));
             while (std::ldexp(maxT, kq) > 8388606.0) --kq;  // both of a term's roundings stay below 2^23
             kq = std::max(-100, std::min(100, kq));
+            fits &= std::ldexp(maxT, kq) <= 8388606.0;
         }
         const int half = field_bits_of(K) == 6 ? 32 : 128;
         h->Qhost.assign((size_t)qtab_entries(K, S) + 2, 0);
-        auto Qof = [&](int s, int t, int p, int q) { return (int32_t)std::nearbyint(std::ldexp(Dof(s, t, p, q), kq)); };
+        // beyond (differences of 1e37 and more): no terms and no bound, so that
+        // the binary64 sum decides every trial
+        auto Qof = [&](int s, int t, int p, int q) {
+            return fits ? (int32_t)std::nearbyint(std::ldexp(Dof(s, t, p, q), kq)) : 0;
+        };
         for (int p = 0; p < K; ++p)
             for (int q = 0; q < K; ++q) {
                 int64_t b = 0;
@@ -1131,7 +1140,8 @@ int smcx_set_epi(smcx_lattice* h, const double* V, void* stream)
         int sumZ = 0;
         for (int s = 0; s < S; ++s) sumZ += kGeom[P.lattice].Z[s];
         const float qscale = (float)std::ldexp(1.0, -kq);
-        const float qeps = (float)((sumZ * std::ldexp(1.0, -kq) + 1e-12 * (1.0 + 64.0 * maxD)) * 1.001);
+        const float qeps = fits ? (float)((sumZ * std::ldexp(1.0, -kq) + 1e-12 * (1.0 + 64.0 * maxD)) * 1.001)
+                                : std::numeric_limits<float>::infinity();
         std::memcpy(&h->Qhost[(size_t)qtab_entries(K, S)], &qscale, 4);
         std::memcpy(&h->Qhost[(size_t)qtab_entries(K, S) + 1], &qeps, 4);
     }

@@ -31,3 +31,15 @@ def test_infinite_differences(lattice, K, value, dims, mode, rows):
     V[1, 0, 1] = V[1, 1, 0] = value
     V[1, 0, 0] = -value
     run(lattice, dims, K, V, mode, rows)
+
+
+@pytest.mark.parametrize("dims,mode,rows", WINDOWS)
+@pytest.mark.parametrize("lattice,K,value", [(BCC, 4, 1e36), (BCC, 4, 3e37), (FCC, 5, 1e40), (BCC, 6, 1e45), (BCC, 2, 1e60),
+                                             (BCC, 7, np.inf)])
+def test_differences_past_the_terms_range(lattice, K, value, dims, mode, rows):
+    """Large differences (all of them infinite at 7 species) beside ordinary ones."""
+    V = sym_V(2, K, 0.03, K)
+    V[0, 0, 0] = V[1, K - 1, K - 1] = value
+    if K == 7:
+        V[:] = value
+    run(lattice, dims, K, V, mode, rows)
