@@ -1601,7 +1601,7 @@ int smcx_energy_backward(int32_t lattice, const int32_t* dims, int32_t n_species
     for (int s = 0; s < n_shells; ++s)
         for (int n = 0; n < G.Z[s]; ++n) {
             bool self = true;
-            for (int a = 0; a < 3; ++a) self &= (G.v[s][n][a] % (2 * dims[a])) == 0;
+            for (int a = 0; a < 3; ++a) self &= (G.v[s][n][a] % (2 * (int64_t)dims[a])) == 0;
             if (self) return fail(SMCX_E_INVALID_ARG, "lattice too small: a site would be its own neighbour");
         }
     const int64_t N = (int64_t)lattice_m(lattice) * dims[0] * dims[1] * dims[2];

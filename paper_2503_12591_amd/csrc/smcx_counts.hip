@@ -278,7 +278,8 @@ __global__ __launch_bounds__(kBitBlock) void k_pair_bits(const uint8_t* occ, int
             const int g = w0 + w - (split ? 1 : 0);  // word of the row; -1 and W: periodic images
             // bits x = 0, 1 and x = L0 - 2, L0 - 1 of every basis site and plane
             auto edge = [&](int x, int b, int q) {
-                return (((uint32_t)row[m * x + b] >> q) & 1u) | (((uint32_t)row[m * (x + 1) + b] >> q) & 1u) << 1;
+                const uint8_t* c = row + (int64_t)m * x + b;
+                return (((uint32_t)c[0] >> q) & 1u) | (((uint32_t)c[m] >> q) & 1u) << 1;
             };
             const int slot = split ? w : w + 1;
             if (g >= 0 && g < T.W) {
@@ -394,39 +395,39 @@ hipError_t launch_pair_counts(int lattice, int K, int S, const uint8_t* occ, int
     const int NP = planes_of(KT);
     BitTile T{};
     for (int a = 0; a < 3; ++a) T.L[a] = L[a];
-    T.W = (L[0] + 31) / 32;
+    T.W = (int)(((int64_t)L[0] + 31) / 32);
     // Rows whole, unless 5 x 3 of them pass the LDS budget (two or more
     // workgroups per CU), then in pieces of 64 words.
     const int budget = 20000;  // words
-    auto pitch_of = [&](int tw) { return (m * NP * (tw + 2)) | 1; };
+    auto pitch_of = [&](int64_t tw) { return (m * NP * (tw + 2)) | 1; };
     T.tw = pitch_of(T.W) * 15 <= budget ? T.W : std::min(T.W, 64);
-    T.pitch = pitch_of(T.tw);
+    T.pitch = (int)pitch_of(T.tw);
     T.nw = (T.W + T.tw - 1) / T.tw;
     // Tile of rows x planes: the smallest cost of a pass over the lattice,
     // staging (about 60 operations per word and basis site) and counting
     // (about 400 per word and basis site, in rounds of the workgroup's
-    // threads), with no fewer workgroups than a third of a thousand where
-    // the batch has that many rows.
+    // threads), where fewer than 768 tiles in the batch cost as much as 768.
     double best = 1e300;
     T.ty = T.tz = 1;
-    for (int ny = 1; ny <= L[1]; ny = ny < 8 ? ny + 1 : ny + (ny + 3) / 4) {
-        const int ty = (L[1] + ny - 1) / ny;
-        for (int nz = 1; nz <= L[2]; nz = nz < 8 ? nz + 1 : nz + (nz + 3) / 4) {
-            const int tz = (L[2] + nz - 1) / nz;
-            if ((int64_t)(ty + 4) * (tz + 2) * T.pitch > budget) continue;
-            const int64_t items = (int64_t)ty * tz * T.tw, staged = (int64_t)(ty + 4) * (tz + 2) * T.tw;
-            const double rounds = (double)((items + 255) / 256) * 400.0 + (double)((staged + 255) / 256) * 60.0 + 150.0;
-            const double tiles = (double)T.nw * ((L[1] + ty - 1) / ty) * ((L[2] + tz - 1) / tz) * B;
+    auto parts = [](int64_t n, int64_t d) { return (n + d - 1) / d; };  // 64 bits: an axis may pass 2^30 cells
+    for (int64_t ny = 1; ny <= L[1]; ny = ny < 8 ? ny + 1 : ny + (ny + 3) / 4) {
+        const int64_t ty = parts(L[1], ny);
+        for (int64_t nz = 1; nz <= L[2]; nz = nz < 8 ? nz + 1 : nz + (nz + 3) / 4) {
+            const int64_t tz = parts(L[2], nz);
+            if ((ty + 4) * (tz + 2) * T.pitch > budget) continue;
+            const int64_t items = ty * tz * T.tw, staged = (ty + 4) * (tz + 2) * T.tw;
+            const double rounds = (double)parts(items, 256) * 400.0 + (double)parts(staged, 256) * 60.0 + 150.0;
+            const double tiles = (double)T.nw * parts(L[1], ty) * parts(L[2], tz) * B;
             const double cost = rounds * std::max(tiles, 768.0);
             if (cost < best) {
                 best = cost;
-                T.ty = ty;
-                T.tz = tz;
+                T.ty = (int)ty;
+                T.tz = (int)tz;
             }
         }
     }
-    T.ny = (L[1] + T.ty - 1) / T.ty;
-    T.nz = (L[2] + T.tz - 1) / T.tz;
+    T.ny = (int)parts(L[1], T.ty);
+    T.nz = (int)parts(L[2], T.tz);
     const int64_t tiles = (int64_t)T.nw * T.ny * T.nz;
     if (tiles > 0x7fffffff) return hipErrorInvalidValue;
     T.tiles = (int)tiles;
