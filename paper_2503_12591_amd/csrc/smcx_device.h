@@ -237,8 +237,9 @@ __device__ __forceinline__ void stage_async(const SweepArgs& A, const RepDev& re
     const int block = __builtin_amdgcn_readfirstlane(Geo::block(A));
     const int n1 = __builtin_amdgcn_readfirstlane(tg.n[1]), n2 = __builtin_amdgcn_readfirstlane(tg.n[2]);
     const uint64_t off = (uint64_t)(((int64_t)(tg.w0[2] + kHalo) * rep.prows + (tg.w0[1] + kHalo)) * grow + tg.gx0);
-    const uint8_t* base = pad + (int64_t)(((uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(off >> 32)) << 32) |
-                                          __builtin_amdgcn_readfirstlane((uint32_t)off));
+    // (the builtin returns a signed word: its sign must not reach the upper one)
+    const uint8_t* base = pad + (int64_t)((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(off >> 32)) << 32 |
+                                          (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)off));
     const int64_t plane = (int64_t)rep.prows * grow;
     if (n16 >= 40) {
         const int nwaves = block >> 6;
