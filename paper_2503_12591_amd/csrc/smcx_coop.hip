@@ -499,13 +499,12 @@ __global__ __launch_bounds__(kResidentBlock) void k_resident(SweepArgs A)
                     const int dx = (int8_t)pd, dy = (int8_t)(pd >> 8), dz = (int8_t)(pd >> 16), bt = pd >> 24;
                     const int la = (z + kHalo) * PL + (y + kHalo) * LP + x + kHalo + b * CP;
                     const int lb = la + dz * PL + dy * LP + dx + (bt - b) * CP;
-                    mine.a = (uint32_t)la | kSiteActive | (uint32_t)b << 19 | image_code(x, Lx) << 21 |
-                             image_code(y, Ly) << 23 | image_code(z, Lz) << 25;
+                    // a cell that sits the mini-step out: its offset may lie past
+                    // the lattice, and the byte there must not reach into the flags
+                    mine.a = ((uint32_t)la & kSiteMask) | (has ? kSiteActive : 0u) | (uint32_t)b << 19 |
+                             image_code(x, Lx) << 21 | image_code(y, Ly) << 23 | image_code(z, Lz) << 25;
                     mine.b = (uint32_t)lb | (uint32_t)bt << 19 | image_code(x + dx, Lx) << 21 |
                              image_code(y + dy, Ly) << 23 | image_code(z + dz, Lz) << 25;
-                    // a cell that sits the mini-step out: its offset may lie past
-                    // the lattice, and the byte there reach into the flags
-                    if (!has) mine.a = mine.b = 0u;
                 }
                 auto step = [&](const CoopDraw& d, int i) {
                     if (d.a & kSiteActive) {
@@ -540,15 +539,13 @@ __global__ __launch_bounds__(kResidentBlock) void k_resident(SweepArgs A)
             }
             if (npass > 1) __syncthreads();
         }
-        if (--until_flush == 0) {
+        if (--until_flush == 0 || js + 1 == A.n_sweeps) {
             until_flush = flush_every;
             if (co.j != 0) st = Stats();  // the group's lanes counted alike
+            __syncthreads();
             flush_stats_block(A, r, st);
         }
     }
-    if (co.j != 0) st = Stats();
-    __syncthreads();
-    flush_stats_block(A, r, st);
     for (int c = threadIdx.x; c < Lx * Ly * Lz; c += blockDim.x) {
         const int x = c % Lx, cr = c / Lx, y = cr % Ly, z = cr / Ly;
         const uint8_t* src = win + ((z + kHalo) * WY + (y + kHalo)) * LP + x + kHalo;

@@ -974,12 +974,11 @@ __global__ __launch_bounds__(kBlock) void k_persistent(SweepArgs A)
                                    smem + A.lds_win + A.win_bytes, tile_of, beta_of, st, r_stats);
             tau += nb;
         }
-        if (--until_flush == 0) {
+        if (--until_flush == 0 || js + 1 == A.n_sweeps) {
             until_flush = flush_every;
             flush_stats(A, r, st);
         }
     }
-    flush_stats(A, r_stats, st);
 }
 
 __global__ void k_advance_counter(uint32_t* counter, uint32_t n)
