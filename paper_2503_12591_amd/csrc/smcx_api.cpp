@@ -1121,8 +1121,9 @@ int smcx_set_epi(smcx_lattice* h, const double* V, void* stream)
         }
         const int half = field_bits_of(K) == 6 ? 32 : 128;
         h->Qhost.assign((size_t)qtab_entries(K, S) + 2, 0);
-        // beyond (differences of 1e37 and more): no terms and no bound, so that
-        // the binary64 sum decides every trial
+        // beyond (differences of 1e37 and more, infinities): no terms and no
+        // bound, so that the binary64 sum decides every trial, and a bias of one
+        // so that no sum is zero
         auto Qof = [&](int s, int t, int p, int q) {
             return fits ? (int32_t)std::nearbyint(std::ldexp(Dof(s, t, p, q), kq)) : 0;
         };
@@ -1135,7 +1136,7 @@ int smcx_set_epi(smcx_lattice* h, const double* V, void* stream)
                         h->Qhost[(p * K + q) * pitch + s * KT + t] = v;
                         b += (int64_t)half * v;
                     }
-                h->Qhost[(p * K + q) * pitch + S * KT] = (int32_t)(uint32_t)(uint64_t)b;
+                h->Qhost[(p * K + q) * pitch + S * KT] = fits ? (int32_t)(uint32_t)(uint64_t)b : 1;
             }
         int sumZ = 0;
         for (int s = 0; s < S; ++s) sumZ += kGeom[P.lattice].Z[s];

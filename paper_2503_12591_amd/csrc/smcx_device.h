@@ -380,8 +380,7 @@ __device__ __forceinline__ int screen_fine(uint32_t qacc, float qscale, float qe
 {
     const double e = (double)(int32_t)qacc * (double)qscale;  // exact: a 32-bit integer times a power of two
     const double eps = (double)qeps, y = beta * eps;
-    // (an infinite bound: some D may be infinite, and 0 times it is no zero)
-    settled = (same & (qeps < __builtin_inff())) | (e <= -eps);
+    settled = same | (e <= -eps);
     if (settled) return 1;
     const double x = beta * e * 1.4426950408889634, n = rint(x);
     if (!(e > eps && y >= 0.0 && y < 0.25 && x < 100.0)) return 0;
@@ -420,7 +419,9 @@ __device__ __forceinline__ int metropolis(uint32_t qacc, float qscale, float qep
     int f = screen(qacc, qscale, qeps, beta, w1, settled);
     if (!settled) {
         constexpr typename Enc<E>::T z = Enc<E>::bias;
-        const bool same = ((d0 ^ z) | (S > 1 ? d1 ^ z : 0) | (S > 2 ? d2 ^ z : 0) | (S > 3 ? d3 ^ z : 0)) == 0;
+        // (a sum that is not zero all the same marks a tensor that the screen must
+        // not judge: it may hold infinities, and 0 times one is no zero)
+        const bool same = ((d0 ^ z) | (S > 1 ? d1 ^ z : 0) | (S > 2 ? d2 ^ z : 0) | (S > 3 ? d3 ^ z : 0) | qacc) == 0;
         f = screen_fine(qacc, qscale, qeps, beta, w1, same, settled);
         if (!settled) f = decide_binary64<E>(D + species_of(pair, Enc<E>::F), d0, d1, d2, d3, K, S, beta, w1, w2);
     }
