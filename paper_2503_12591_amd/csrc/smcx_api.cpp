@@ -1141,8 +1141,14 @@ int smcx_set_epi(smcx_lattice* h, const double* V, void* stream)
         int sumZ = 0;
         for (int s = 0; s < S; ++s) sumZ += kGeom[P.lattice].Z[s];
         const float qscale = (float)std::ldexp(1.0, -kq);
-        const float qeps = fits ? (float)((sumZ * std::ldexp(1.0, -kq) + 1e-12 * (1.0 + 64.0 * maxD)) * 1.001)
-                                : std::numeric_limits<float>::infinity();
+        // differences that are whole numbers of units (energies in halves, say):
+        // the integer sum is the binary64 sum, which is exact too (below 2^53
+        // units), and many a trial of such a tensor ends at dE = 0
+        bool whole = fits;
+        for (double v : h->Dhost) whole &= std::ldexp(v, kq) == std::nearbyint(std::ldexp(v, kq));
+        const float qeps = whole  ? 0.0f
+                           : fits ? (float)((sumZ * std::ldexp(1.0, -kq) + 1e-12 * (1.0 + 64.0 * maxD)) * 1.001)
+                                  : std::numeric_limits<float>::infinity();
         std::memcpy(&h->Qhost[(size_t)qtab_entries(K, S)], &qscale, 4);
         std::memcpy(&h->Qhost[(size_t)qtab_entries(K, S) + 1], &qeps, 4);
     }

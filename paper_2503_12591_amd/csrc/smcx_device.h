@@ -290,35 +290,59 @@ __device__ __forceinline__ void stage_async(const SweepArgs& A, const RepDev& re
 
 // The decision of a trial the integer screen leaves open (a few in 1e5 at
 // the benchmark's temperature): dE summed in binary64, s and t ascending, from
-// D[s][t][p][q] (Dp points at the lane's (p, q) entry), then the float screen
+// D[s][t][p][q] (pq: the lane's (p, q) entry), then the float screen
 // and, where that cannot decide either, exp in binary64, the test u < P and
 // the near-tie check.  The sum starts from the first product rather than from
 // +0.0 + it: the two differ only in the sign of a zero sum, and dE <= 0
 // accepts either.  Out of line: inlined, its registers would weigh on every
 // trial's code.  Returns bit 0: accepted, bit 1: near-tie.
 template <int E>
-__device__ __noinline__ int decide_binary64(const double* Dp, typename Enc<E>::T d0, typename Enc<E>::T d1,
+__device__ __noinline__ int decide_binary64(const double* Dtab, int pq, typename Enc<E>::T d0, typename Enc<E>::T d1,
                                             typename Enc<E>::T d2, typename Enc<E>::T d3, int K, int S, double beta,
                                             uint32_t w1, uint32_t w2)
 {
     using EN = Enc<E>;
     using CT = typename EN::T;
+    // Three or four terms are read together (one by one, each waited for: up to 10 % more
+    // for a whole sweep of a tensor with many a dE of zero; more at a time would
+    // take registers that every caller has to keep free).  One table for all
+    // lanes: a scalar base and 32-bit offsets.
+    using CD = const __attribute__((address_space(1))) double;
+    using CB = const __attribute__((address_space(1))) uint8_t;
+    const uint64_t base = (uint64_t)Dtab;
+    CB* D = (CB*)((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(base >> 32)) << 32 |
+                  (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)base));
+    constexpr int U = EN::KP == 5 || EN::KP == 6 ? 3 : 4;
+    const uint32_t step = 8u * (uint32_t)(K * K);
+    uint32_t at = 8u * (uint32_t)pq;
     double dE = 0.0;
-    bool first = true;
     for (int s = 0; s < S; ++s) {
         CT f = s == 0 ? d0 : (s == 1 ? d1 : (s == 2 ? d2 : d3));
-        const double* Ds = Dp + s * K * K * K;
         int rest = 0;
-        for (int tt = 0; tt < K; ++tt) {
-            // a species whose field has no room for it is what the others leave
-            const bool whole = EN::F * (tt + 1) <= 8 * (int)sizeof(CT);
-            const int c = whole ? (int)(f & EN::mask) - EN::half : -rest;
-            rest += c;
-            const double term = (double)c * Ds[tt * K * K];
-            dE = first ? term : dE + term;
-            first = false;
-            f >>= EN::F;
+#pragma unroll 1
+        for (int t0 = 0; t0 < EN::KP; t0 += U) {
+            double v[U];
+#pragma unroll
+            for (int j = 0; j < U; ++j) {
+                v[j] = *(CD*)(D + at);
+                at += t0 + j < K - 1 ? step : 0u;
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int j = 0; j < U; ++j) {
+                const int tt = t0 + j;
+                // a species whose field has no room for it is what the others leave
+                const bool whole = EN::F * EN::KP <= 8 * (int)sizeof(CT) || tt < EN::KP - 1;
+                const int c = whole ? (int)(f & EN::mask) - EN::half : -rest;
+                rest += c;
+                f >>= EN::F;
+                if (tt < K) {
+                    const double term = (double)c * v[j];
+                    dE = s == 0 && tt == 0 ? term : dE + term;
+                }
+            }
         }
+        at += step;
     }
     if (dE <= 0.0) return 1;
     const double x = beta * dE;
@@ -423,7 +447,7 @@ __device__ __forceinline__ int metropolis(uint32_t qacc, float qscale, float qep
         // not judge: it may hold infinities, and 0 times one is no zero)
         const bool same = ((d0 ^ z) | (S > 1 ? d1 ^ z : 0) | (S > 2 ? d2 ^ z : 0) | (S > 3 ? d3 ^ z : 0) | qacc) == 0;
         f = screen_fine(qacc, qscale, qeps, beta, w1, same, settled);
-        if (!settled) f = decide_binary64<E>(D + species_of(pair, Enc<E>::F), d0, d1, d2, d3, K, S, beta, w1, w2);
+        if (!settled) f = decide_binary64<E>(D, species_of(pair, Enc<E>::F), d0, d1, d2, d3, K, S, beta, w1, w2);
     }
     return f;
 }

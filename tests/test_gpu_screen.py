@@ -43,3 +43,23 @@ def test_differences_past_the_terms_range(lattice, K, value, dims, mode, rows):
     if K == 7:
         V[:] = value
     run(lattice, dims, K, V, mode, rows)
+
+
+def one_energy_per_shell(S, K, J):
+    V = np.zeros((S, K, K))
+    for s in range(S):
+        V[s] = J[s] * (1.0 - np.eye(K))
+    return V
+
+
+@pytest.mark.parametrize("dims,mode,rows", WINDOWS)
+@pytest.mark.parametrize("lattice,K,S,J", [
+    (BCC, 4, 4, (1 / 64, 1 / 128, -1 / 256, 1 / 512)),   # whole units: the integer sum is the energy change
+    (FCC, 5, 2, (1 / 64, -1 / 64)), (BCC, 8, 3, (0.25, 0.125, 3 / 64)), (BCC, 6, 1, (1 / 32,)),
+    (BCC, 4, 4, (0.021, 0.011, -0.0047, 0.0023)),        # the binary64 sum decides where the integer sum is zero
+    (FCC, 5, 4, (0.021, 0.011, -0.0047, 0.0023)), (BCC, 7, 2, (0.021, 0.011)), (FCC, 6, 3, (0.021, 0.011, 0.0031)),
+    (BCC, 2, 2, (0.021, -0.011)), (BCC, 3, 2, (0.0, 0.0)),
+])
+def test_one_energy_per_shell(lattice, K, S, J, dims, mode, rows):
+    """Many an energy change is zero though the neighbours differ."""
+    run(lattice, dims, K, one_energy_per_shell(S, K, J), mode, rows, T=(1500.0, 300.0))
