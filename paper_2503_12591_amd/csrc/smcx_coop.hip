@@ -475,10 +475,6 @@ __global__ __launch_bounds__(kResidentBlock) void k_resident(SweepArgs A)
     };
     take_cell(grp);
     Stats st;
-    // one workgroup counts every trial of the call: the 32-bit sums go out
-    // before 2^30 of them (a sweep tries every site once)
-    const int flush_every = (1 << 30) / (m * Lx * Ly * Lz);
-    int until_flush = flush_every;
     for (int js = 0; js < A.n_sweeps; ++js) {
         const uint32_t t = first + (uint32_t)js;
         const double beta = ld_const(A.beta, (int64_t)js * A.beta_stride + r);
@@ -539,8 +535,9 @@ __global__ __launch_bounds__(kResidentBlock) void k_resident(SweepArgs A)
             }
             if (npass > 1) __syncthreads();
         }
-        if (--until_flush == 0 || js + 1 == A.n_sweeps) {
-            until_flush = flush_every;
+        // one workgroup counts every trial of the call: the 32-bit sums go out
+        // before 2^30 of them (a sweep tries each of at most 160 K sites once)
+        if ((js & 4095) == 4095 || js + 1 == A.n_sweeps) {
             if (co.j != 0) st = Stats();  // the group's lanes counted alike
             __syncthreads();
             flush_stats_block(A, r, st);

@@ -957,10 +957,6 @@ __global__ __launch_bounds__(kBlock) void k_persistent(SweepArgs A)
     Stats st;
     int r_stats = r;
     const int tau_end = min(A.tau_end, rep.nA);
-    // the 32-bit sums of a wave go out before 2^30 trials of the workgroup (a
-    // sweep tries every site once)
-    const int flush_every = (int)max((int64_t)1, ((int64_t)1 << 30) / rep.N);
-    int until_flush = flush_every;
     for (int js = 0; js < A.n_sweeps; ++js) {
         const uint32_t t = first + (uint32_t)js;
         const double beta = ld_const(A.beta, (int64_t)js * A.beta_stride + r);
@@ -974,10 +970,9 @@ __global__ __launch_bounds__(kBlock) void k_persistent(SweepArgs A)
                                    smem + A.lds_win + A.win_bytes, tile_of, beta_of, st, r_stats);
             tau += nb;
         }
-        if (--until_flush == 0 || js + 1 == A.n_sweeps) {
-            until_flush = flush_every;
-            flush_stats(A, r, st);
-        }
+        // the 32-bit sums of a wave go out before 2^30 trials of the workgroup (a
+        // sweep tries every site once)
+        if ((js & 63) == 63 || rep.N > 1 << 24 || js + 1 == A.n_sweeps) flush_stats(A, r, st);
     }
 }
 
