@@ -440,6 +440,7 @@ int make_plan(const smcx_desc* d, Plan& P)
             // four busy (few rows: many workgroups, little to stage before the
             // first trial), at the smallest pitch
             const int prow = (prowp + 15) & ~15;
+            const std::array<int, 7> one_lane = {best_lanes, best_win, best_prow, best[0], best[1], best[2], best[3]};
             double best_busy = 0.0;
             for (const auto& g : {std::array<int, 2>{1, 1}, {2, 1}, {1, 2}, {2, 2}, {4, 1}, {4, 2}, {4, 4}, {8, 4}, {8, 8}}) {
                 const int lanes = ncx * g[0] * g[1] * G;
@@ -456,6 +457,26 @@ int make_plan(const smcx_desc* d, Plan& P)
                 best_prow = prow;
                 best[0] = g[0]; best[1] = g[1]; best[2] = wy; best[3] = wz;
                 P.rlanes = G;
+            }
+            // Two lanes with 64-bit counters (7, 8 species) take 185 registers:
+            // past two waves per SIMD they lose to one lane, unless its windows
+            // leave lanes and CUs idle (score).  us per sweep of 7 species and 4
+            // shells, one lane in brackets: BCC 64^3 x 16 (eight waves per CU)
+            // 643 (738), 112^3 x 2 (seven) 596 (980), 140^3 (ten) 984 (717), 96^3
+            // x 4 (nine) 935 (766), 180^3 (fifteen) 1292 (806); at a score of
+            // 0.42, 24^3 x 400 1136 (1479).
+            if (P.K >= 7 && P.rlanes == 2 && best_score >= 0.58) {
+                int64_t groups = 0;
+                for (const Replica& R : P.reps)
+                    groups += (int64_t)(((int)R.edges[1].size() + best[0] - 1) / best[0]) *
+                              (((int)R.edges[2].size() + best[1] - 1) / best[1]);
+                if ((groups + 255) / 256 * ((best_lanes + 63) / 64) > 8) {
+                    best_lanes = one_lane[0];
+                    best_win = one_lane[1];
+                    best_prow = one_lane[2];
+                    std::copy(one_lane.begin() + 3, one_lane.end(), best);
+                    P.rlanes = 1;
+                }
             }
         }
         if (best_lanes > 0) {
