@@ -551,6 +551,20 @@ int make_plan(const smcx_desc* d, Plan& P)
         }
         const double t_rows = 7.6 / per_launch + 0.6 + 0.05 * std::min(kcells, 14.0) + 0.02 * std::max(kcells - 14.0, 0.0);
         P.auto_resident = P.resident && (!P.rows || t_res <= t_rows);
+        // No row windows: the other form of a replica beyond 65536 sites is tile
+        // launches over the chip.  With 64-bit counters these win where most of
+        // the link cells are active at once; us per mini-step, fitted, cells and
+        // active cells per mini-step.  us per sweep of 7 species, tiles in
+        // brackets: BCC of link cells 3, 4 shells, 36^3 1125 (727); 3 shells 36^3
+        // 907 (470), 34^3 (cells of 3 and 4, half of them active) 1340 (1063);
+        // link cells of 4, 3 shells, 36^3 1123 (about 1110).  With 32-bit counters
+        // resident sweeps took 0.4 to 0.84 of the time of tiles at every size.
+        if (!P.rows && P.R == 1 && P.total_sites > 65536 && P.K >= 7) {
+            const double shells[kMaxShells] = {0.58, 0.6, 0.8, 1.0};
+            const double tiles[kMaxShells] = {7.5, 7.9, 8.6, 13.5 + 1.1 * (P.K - 7)};
+            const double active = (double)P.reps[0].N / P.reps[0].nA;
+            P.auto_resident &= shells[P.S - 1] * (4.4 + 0.0045 * c + 0.0051 * active) <= tiles[P.S - 1];
+        }
     }
 
     // workspace layout
