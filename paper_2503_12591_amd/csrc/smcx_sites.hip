@@ -90,10 +90,16 @@ __global__ __launch_bounds__(kBlock) void k_local_energy(const uint8_t* occ, int
                 const double* row = Vs + p * K;
 #pragma unroll
                 for (int s = 0; s < kMaxShells; ++s)
-                    if (s < S)
+                    if (s < S) {
+                        int left = G.Z[s];  // a species whose field has no room for it is what the others leave
 #pragma unroll
-                        for (int t = 0; t < EN::KP; ++t)
-                            if (t < K) en = en + (double)(int)((h[s] >> (F * t)) & EN::mask) * row[s * KK + t];
+                        for (int t = 0; t < EN::KP; ++t) {
+                            const bool whole = F * (t + 1) <= 8 * (int)sizeof(CT);
+                            const int c = whole ? (int)((h[s] >> (whole ? F * t : 0)) & EN::mask) : left;
+                            left -= c;
+                            if (t < K) en = en + (double)c * row[s * KK + t];
+                        }
+                    }
                 out[b] = 0.5 * en;
             }
             __builtin_memcpy(e + m * cell, out, sizeof(out));
@@ -101,11 +107,77 @@ __global__ __launch_bounds__(kBlock) void k_local_energy(const uint8_t* occ, int
     }
 }
 
+// The same for lattices of few sites and 5 or more species, a thread per cell
+// and every neighbour from memory: no window to stage first, and one cell's
+// chain instead of a column's.  us, tiles in brackets: FCC 9^3 of 8 species and
+// 4 shells 11.8 (30.5), 48^3 19.0 (32.4), BCC 64^3 17.2 (20.1), of 5 species and 2
+// shells 7.7 (11.6), 16^3 4.4 (10.3).  Rows of 17 to 20 cells, a third of whose
+// two tiles would be empty, take it at every size (FCC 20x20x2000 of 8 species
+// 82 (104)).
+template <int LAT, int B>
+__device__ __forceinline__ void local_energy_cell(const uint8_t* occ, int c, int x, int y, int z, int L0, int L1, int L2,
+                                                  int K, int S, const double* Vs, double* e)
+{
+    constexpr Geometry G = kGeom[LAT];
+    constexpr int m = G.m;
+    if constexpr (B < m) {
+        uint64_t acc[kMaxShells];
+#pragma unroll
+        for (int s = 0; s < kMaxShells; ++s) {
+            uint64_t a = 0;
+            if (s < S) {
+#pragma unroll
+                for (int n = 0; n < G.Z[s]; ++n) {
+                    const Nb nb = nb_of(G, B, G.v[s][n][0], G.v[s][n][1], G.v[s][n][2]);
+                    int xx = x + nb.dx, yy = y + nb.dy, zz = z + nb.dz;
+                    xx += xx < 0 ? L0 : (xx >= L0 ? -L0 : 0);
+                    yy += yy < 0 ? L1 : (yy >= L1 ? -L1 : 0);
+                    zz += zz < 0 ? L2 : (zz >= L2 ? -L2 : 0);
+                    const uint32_t t = occ[nb.bt + m * (xx + L0 * (yy + L1 * zz))] & 7u;  // species < K <= 8
+                    a += (uint64_t)1 << (8 * t);
+                }
+            }
+            acc[s] = a;
+        }
+        const int p = min((int)occ[B + m * c], K - 1);  // checked < K at init
+        double en = 0.0;
+#pragma unroll
+        for (int s = 0; s < kMaxShells; ++s)
+            if (s < S)
+                for (int t = 0; t < K; ++t)
+                    en = en + (double)(int)((acc[s] >> (8 * t)) & 0xff) * Vs[(s * K + p) * K + t];
+        e[B + m * c] = 0.5 * en;
+        local_energy_cell<LAT, B + 1>(occ, c, x, y, z, L0, L1, L2, K, S, Vs, e);
+    }
+}
+
+template <int LAT>
+__global__ __launch_bounds__(kBlock) void k_local_energy_cells(const uint8_t* occ, int L0, int L1, int L2, int K, int S,
+                                                               const double* V, double* e)
+{
+    __shared__ double Vs[kMaxShells * kMaxK * kMaxK];
+    for (int i = threadIdx.x; i < S * K * K; i += kBlock) Vs[i] = V[i];
+    __syncthreads();
+    const int ncell = L0 * L1 * L2;
+    for (int c = blockIdx.x * kBlock + threadIdx.x; c < ncell; c += gridDim.x * kBlock) {
+        const int cr = c / L0, x = c - cr * L0, z = cr / L1, y = cr - z * L1;
+        local_energy_cell<LAT, 0>(occ, c, x, y, z, L0, L1, L2, K, S, Vs, e);
+    }
+}
+
 template <int LAT, int E>
 static void local_energy_go(const uint8_t* occ, const int32_t* L, int K, int S, const double* V, double* e, hipStream_t st)
 {
-    // shallower tiles for lattices that would leave CUs idle; narrow ones for
-    // narrow lattices
+    // shallower tiles for lattices that would leave CUs idle (the shallowest
+    // where a lane's chain is longest, past 4 species: FCC 64^3 of 5 species and 2
+    // shells 11.8 us against 17.2, BCC 80^3 11.8 against 13.5; at twice the sites
+    // the staging costs as much); narrow ones for narrow lattices
+    const int64_t ncell = (int64_t)L[0] * L[1] * L[2], sites = kGeom[LAT].m * ncell;
+    if (E != 1 && (sites <= 1 << 19 || (L[0] > 16 && L[0] <= 20))) {
+        hipLaunchKernelGGL(k_local_energy_cells<LAT>, dim3((unsigned)((ncell + kBlock - 1) / kBlock)), dim3(kBlock), 0, st, occ,
+                           L[0], L[1], L[2], K, S, V, e);
+        return;
+    }
     auto tiles = [&](int TX, int TZ) {
         const int TY = kBlock / TX;
         return (int64_t)((L[0] + TX - 1) / TX) * ((L[1] + TY - 1) / TY) * ((L[2] + TZ - 1) / TZ);
@@ -117,6 +189,7 @@ static void local_energy_go(const uint8_t* occ, const int32_t* L, int K, int S, 
     };
     using std::integral_constant;
     if (L[0] <= 20) go(integral_constant<int, 16>{}, integral_constant<int, 4>{});
+    else if (E != 1 && sites <= 3 << 19) go(integral_constant<int, 32>{}, integral_constant<int, 2>{});
     else if (tiles(32, 8) < 2048) go(integral_constant<int, 32>{}, integral_constant<int, 4>{});
     else go(integral_constant<int, 32>{}, integral_constant<int, 8>{});
 }
@@ -128,6 +201,7 @@ hipError_t launch_local_energy(int lattice, const uint8_t* occ, const int32_t* L
         constexpr int LAT = decltype(lat)::value;
         if (K <= 4) local_energy_go<LAT, 1>(occ, L, K, S, V, e, st);
         else if (K == 5) local_energy_go<LAT, 3>(occ, L, K, S, V, e, st);
+        else if (K == 6) local_energy_go<LAT, 4>(occ, L, K, S, V, e, st);
         else local_energy_go<LAT, 2>(occ, L, K, S, V, e, st);
     };
     if (lattice == SMCX_BCC) go(std::integral_constant<int, SMCX_BCC>{});
