@@ -44,11 +44,13 @@ struct QsroTables {
     double F[kMaxShells * kQsroFrac];
 };
 
+// (for workgroups of one wave: the launch's block size is a load from a cache
+// line of its own, 0.2 us at the start of every launch)
 __device__ __forceinline__ void qsro_tables(const QsroArgs& A, QsroTables& T)
 {
-    for (int i = threadIdx.x; i < A.S * A.K * A.K; i += blockDim.x) T.V[i] = A.V[i];
-    for (int i = threadIdx.x; i < A.S * A.K; i += blockDim.x) T.W[i] = A.W[i];
-    for (int i = threadIdx.x; i < A.S * kQsroFrac; i += blockDim.x) {
+    for (int i = threadIdx.x; i < A.S * A.K * A.K; i += 64) T.V[i] = A.V[i];
+    for (int i = threadIdx.x; i < A.S * A.K; i += 64) T.W[i] = A.W[i];
+    for (int i = threadIdx.x; i < A.S * kQsroFrac; i += 64) {
         const int s = i / kQsroFrac, n = i - s * kQsroFrac;
         T.F[i] = (double)n / (double)A.Z[s];
     }
@@ -231,7 +233,7 @@ __global__ __launch_bounds__(64 * kQsroWaves) void k_qsro_cell(QsroArgs A)
     __shared__ double term[kQsroWaves][NL * 64];
     __shared__ __align__(16) uint8_t boxes[kQsroWaves][(W3 * m + 15) & ~15];
     const int K = A.K, KF = K * kQsroFrac, SKKF = S * K * KF;
-    for (int i = threadIdx.x; i < SKKF + S * KF; i += blockDim.x) gtab[i] = A.G[i];
+    for (int i = threadIdx.x; i < SKKF + S * KF; i += 64 * kQsroWaves) gtab[i] = A.G[i];
     __syncthreads();
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     uint8_t* box = boxes[wave];
