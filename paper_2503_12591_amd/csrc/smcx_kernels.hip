@@ -1111,7 +1111,7 @@ __global__ __launch_bounds__(kBlock) void k_pack(const uint8_t* occ, uint8_t* ws
 }
 
 // Four species from their stored form F * species: v / 6 = ((v / 2) 11) / 32
-// for v in 0, 6, .. 24, and no product leaves its byte.
+// for v in 0, 6, .. 30, and no product leaves its byte.
 __device__ __forceinline__ uint32_t species_of4(uint32_t v, int F)
 {
     return F == 8 ? (v >> 3) & 0x1F1F1F1Fu : ((((v >> 1) & 0x0F0F0F0Fu) * 11u) >> 5) & 0x07070707u;
@@ -1227,19 +1227,28 @@ static const void* with_encoding(int K, F f)
     return f(std::integral_constant<int, 2>{});
 }
 
+// Preset PI for counters of encoding E, where its species count has that
+// encoding (others are never asked for).
+template <int LAT, int E, int PI>
+static const void* preset_kernel()
+{
+    constexpr Preset q = kPresets[PI];
+    constexpr int e = q.K <= 4 ? 1 : (q.K == 5 ? 3 : (q.K == 6 ? 4 : 2));
+    if constexpr (q.lattice == LAT && e == E) return (const void*)k_ministep<LAT, E, GeoFix<PI>, 1>;
+    else return nullptr;
+}
+
 template <int LAT, int E>
 static const void* stream_kernel(int preset, int nbuf)
 {
-    if constexpr (E != 2) {
-        if constexpr (LAT == SMCX_BCC) {
-            if (preset == 0) return (const void*)k_ministep<LAT, E, GeoFix<0>, 1>;
-            if (preset == 1) return (const void*)k_ministep<LAT, E, GeoFix<1>, 1>;
-        } else {
-            if (preset == 2) return (const void*)k_ministep<LAT, E, GeoFix<2>, 1>;
-            if (preset == 3) return (const void*)k_ministep<LAT, E, GeoFix<3>, 1>;
-        }
+    static_assert(kNumPresets == 4, "presets by number");
+    switch (preset) {
+    case 0: return preset_kernel<LAT, E, 0>();
+    case 1: return preset_kernel<LAT, E, 1>();
+    case 2: return preset_kernel<LAT, E, 2>();
+    case 3: return preset_kernel<LAT, E, 3>();
+    default: break;
     }
-    if (preset >= 0) return nullptr;
     if (nbuf == 2) return (const void*)k_ministep<LAT, E, GeoRt, 2>;
     return (const void*)k_ministep<LAT, E, GeoRt, 1>;
 }
