@@ -863,6 +863,29 @@ int smcx_workspace_size(const smcx_desc* desc, size_t* bytes)
     return SMCX_OK;
 }
 
+// The launch forms of a description, for tests that mean one of them (not part
+// of the interface in smcx.h): form[0] lanes per trial of resident sweeps (0:
+// a replica does not fit the LDS), form[1] auto mode takes them, form[2] lanes
+// per trial of row launches (0: no row windows), form[3] bits of the packed
+// neighbour counters, form[4] passes of a resident workgroup over the link
+// cells.
+int smcx_internal_forms(const smcx_desc* desc, int32_t* form)
+{
+    if (!form) return fail(SMCX_E_INVALID_ARG, "form is NULL");
+    Plan P;
+    if (int rc = make_plan(desc, P)) return rc;
+    int64_t cells = 0;
+    for (const Replica& R : P.reps)
+        cells = std::max<int64_t>(cells, (int64_t)R.edges[0].size() * (int64_t)R.edges[1].size() * (int64_t)R.edges[2].size());
+    const int64_t at_once = P.res_block / P.res_lanes;
+    form[0] = P.resident ? P.res_lanes : 0;
+    form[1] = P.auto_resident;
+    form[2] = P.rows ? P.rlanes : 0;
+    form[3] = P.K >= 7 ? 64 : 32;
+    form[4] = (int32_t)((cells + at_once - 1) / at_once);
+    return SMCX_OK;
+}
+
 int smcx_lattice_init(smcx_lattice** out, const smcx_desc* desc, uint8_t* occ_dev, void* ws_dev, size_t ws_bytes,
                       void* stream)
 {
