@@ -316,8 +316,11 @@ __device__ __noinline__ int decide_binary64(const double* Dtab, int pq, typename
     const uint32_t step = 8u * (uint32_t)(K * K);
     uint32_t at = 8u * (uint32_t)pq;
     double dE = 0.0;
-    for (int s = 0; s < S; ++s) {
-        CT f = s == 0 ? d0 : (s == 1 ? d1 : (s == 2 ? d2 : d3));
+    for (int s = 0, s_end = __builtin_amdgcn_readfirstlane(S); s < s_end; ++s) {
+        CT f = d0;
+        d0 = d1;
+        d1 = d2;
+        d2 = d3;
         int rest = 0;
 #pragma unroll 1
         for (int t0 = 0; t0 < EN::KP; t0 += U) {
