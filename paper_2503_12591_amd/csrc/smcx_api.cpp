@@ -1203,7 +1203,10 @@ int smcx_set_epi(smcx_lattice* h, const double* V, void* stream)
         // the integer sum is the binary64 sum, which is exact too (below 2^53
         // units), and many a trial of such a tensor ends at dE = 0
         bool whole = fits;
-        for (double v : h->Dhost) whole &= std::ldexp(v, kq) == std::nearbyint(std::ldexp(v, kq));
+        for (size_t i = 0; whole && i < h->Dhost.size(); ++i) {
+            const double units = std::ldexp(h->Dhost[i], kq);
+            whole = units == std::nearbyint(units);
+        }
         const float qeps = whole  ? 0.0f
                            : fits ? (float)((sumZ * std::ldexp(1.0, -kq) + 1e-12 * (1.0 + 64.0 * maxD)) * 1.001)
                                   : std::numeric_limits<float>::infinity();
