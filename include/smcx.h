@@ -70,10 +70,13 @@ extern "C" {
 #define SMCX_FCC 1
 
 /* sweep execution modes (all give the same trajectory) */
-#define SMCX_MODE_AUTO 0        /* persistent for lattices of at most 65536 sites, else stream where
-                                   row windows apply or R == 1, else persistent */
-#define SMCX_MODE_STREAM 1      /* one launch per mini-step, batched over replicas */
-#define SMCX_MODE_PERSISTENT 2  /* one launch for all sweeps, one workgroup per replica */
+#define SMCX_MODE_AUTO 0        /* persistent where every replica fits a CU's LDS whole and a fitted
+                                   cost says that it is faster; else stream where row windows apply, or
+                                   for one replica of more than 65536 sites; else persistent */
+#define SMCX_MODE_STREAM 1      /* launches over all replicas: one for the mini-steps with the same
+                                   (o_y, o_z) where row windows apply, else one per offset */
+#define SMCX_MODE_PERSISTENT 2  /* one launch for all sweeps, one workgroup per replica (the replica held
+                                   in LDS where it fits) */
 #define SMCX_MODE_PLAIN 3       /* one launch per replica per mini-step (baseline loop) */
 
 typedef struct smcx_lattice smcx_lattice;
@@ -196,8 +199,9 @@ int smcx_get_schedule(const smcx_lattice *h, int32_t replica, int32_t *ncell_out
  * qSRO model", Eq. Linear_EPI and Eq. Total_EPI, with the energy written as
  * E = 1/2 sum_i sum_s sum_{d in D_s} V_s[sigma_i][sigma_{i+d}]).  V must be
  * symmetric in (k, l) exactly.  Tables D[s][t][p][q] = V_s[q][t] - V_s[p][t]
- * are uploaded on `stream`, which is synchronised.  Errors:
- * SMCX_E_INVALID_ARG (NULL, asymmetric or non-finite V), SMCX_E_HIP. */
+ * are uploaded on `stream`, which is synchronised.  Entries may be infinite: a
+ * trial whose energy change is then not a number is not accepted.  Errors:
+ * SMCX_E_INVALID_ARG (NULL, asymmetric V, or one with a NaN), SMCX_E_HIP. */
 int smcx_set_epi(smcx_lattice *h, const double *V, void *stream);
 
 /*

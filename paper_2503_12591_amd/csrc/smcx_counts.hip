@@ -437,7 +437,7 @@ hipError_t launch_pair_counts(int lattice, int K, int S, const uint8_t* occ, int
     gx = std::max(gx, std::min<int64_t>(tiles, N / (1 << 26) + 1));
     const int NU = KT * (KT - 1) / 2, NV = kMaxShells * NU + KT;
     // Large tiles leave two workgroups per CU: eight waves each where their
-    // registers allow it (up to 4 species: BCC 800^3 1082 -> 845 us with the call,
+    // registers allow it (up to 4 species: BCC 800^3 1104 -> 845 us with the call,
     // FCC 400^3 319 -> 254; 5 species, BCC 500^3: 514 -> 574)
     const int threads = KT <= 4 && T.ty * T.tz * T.tw >= 1024 ? 512 : 256;
     const size_t lds = 4 * (size_t)std::max((T.ty + 4) * (T.tz + 2) * T.pitch, (threads / 64 + 1) * NV);
